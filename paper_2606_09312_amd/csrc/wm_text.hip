@@ -20,6 +20,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "wm_device.h"
 #include "wm_internal.h"
 
 using namespace wm;
@@ -35,10 +36,6 @@ struct wm_text_model {
 
 namespace wm {
 namespace text {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float LN_EPS = 1e-5f;
 
@@ -69,20 +66,6 @@ __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) x = fmaxf(x, __shfl_xor(x, m));
   return x;
-}
-
-// GELU(x) = x Phi(x) with erf from Abramowitz & Stegun 7.1.26 (|error| <=
-// 1.5e-7), the same form as the evaluator's kernels.
-__device__ __forceinline__ float gelu(float x) {
-  const float ax = fabsf(x);
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, ax, 1.0f));
-  float p = fmaf(1.061405429f, t, -1.453152027f);
-  p = fmaf(p, t, 1.421413741f);
-  p = fmaf(p, t, -0.284496736f);
-  p = fmaf(p, t, 0.254829592f);
-  const float ex = __builtin_amdgcn_exp2f((x * x) * (-0.5f * 1.4426950408889634f));
-  const float erf_a = fmaf(-(p * t), ex, 1.0f);
-  return 0.5f * fmaf(ax, erf_a, x);
 }
 
 // Programs and their chunks (host-built, passed by value).
@@ -351,9 +334,14 @@ __global__ __launch_bounds__(256) void gemm_kernel(const GemmArgs g) {
 // bf16 dense product with operands stored as bf16 (the product-operand
 // values themselves):  C = epi(A . W^T), A [M][K] and W [N][K] row-major,
 // epilogue + bias[n], GELU, + residual R[m][n] (fp32), C fp32 or bf16.
-// Workgroup = 8 wavefronts on a 256 x 128 tile (each 64 x 64, 2 x 2
-// matrix-core tiles); 32-deep stages, 16-byte loads straight into LDS rows
-// (contraction contiguous), the next stage's loads in flight meanwhile.
+//
+// Both kernels stage 32-deep slices of A and W in a ring of four LDS buffers
+// by loads straight to LDS, three slices ahead.  A slice row is 64 bytes (four
+// 16-byte units); unit u of row r holds contraction unit u ^ ((r >> 2) & 3),
+// so that the 16 lanes that the LDS serves together read 16 different bank
+// groups.  LDS row 32 j + c of a wavefront's 32 TN columns holds column
+// TN c + j: a lane then owns TN neighbouring columns of C and stores them
+// together.
 struct Gemm16Args {
   const __bf16* A;
   const __bf16* W;
@@ -362,81 +350,270 @@ struct Gemm16Args {
   const float* res;
   int M, N, K, tiles_n, gelu;
 };
-constexpr int G16_BM = 256, G16_BN = 128, G16_LDW = GK + 8;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) void lds_void;
 
-template <bool OUT16>
-__global__ __launch_bounds__(512) void gemm16_kernel(const Gemm16Args g) {
-  __shared__ __attribute__((aligned(16))) __bf16 As[G16_BM * G16_LDW];
-  __shared__ __attribute__((aligned(16))) __bf16 Bs[G16_BN * G16_LDW];
-  const int m0 = (blockIdx.x / g.tiles_n) * G16_BM, n0 = (blockIdx.x % g.tiles_n) * G16_BN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // A: 2 units of 8 bf16 per thread, B: 1 unit
-  bf16x8 ra[2], rb;
-  auto load = [&](int k0) {
+// Buffer resource of `bytes` bytes at p (wave-uniform).
+__device__ __forceinline__ u32x4 buffer_of(const void* p, uint32_t bytes) {
+  const uint64_t a = (uint64_t)p;
+  return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a),
+               (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)),
+               (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
+}
+// 16 bytes per lane from byte vo (per lane) + so (uniform) of a buffer into
+// LDS at d + lane * 16.  Inline assembly, because the compiler otherwise waits
+// for every outstanding copy before an LDS read of another slice of the ring;
+// the kernels wait for the copies themselves (the instruction has no register
+// output, so nothing can be overwritten while it is in flight).  m0 is listed
+// as clobbered for the compiler's own uses of it; the warning that it is a
+// reserved register does not apply to a value nobody keeps there.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void copy16(u32x4 r, __bf16* d, uint32_t vo, int so) {
+  const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)d);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(l), "v"(vo), "s"(r), "s"(so) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+// Wait until at most VM vector-memory operations are outstanding, and (LGKM)
+// for every LDS read.
+template <int VM, bool LGKM>
+__device__ __forceinline__ void wait_counts() {
+  __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | ((LGKM ? 0 : 15) << 8) | ((VM >> 4) << 14));
+}
+// Barrier without the waits of __syncthreads; nothing moves across it.
+__device__ __forceinline__ void raw_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
+template <int P>
+__device__ __forceinline__ void wave_priority() { __builtin_amdgcn_s_setprio(P); }
+
+// Tile of a workgroup: workgroups go to the 8 XCDs in turn, so XCD x takes a
+// contiguous run of tiles (columns fastest) and its L2 holds one A panel and W.
+__device__ __forceinline__ int xcd_tile(int bid, int total) {
+  const int per = total >> 3, rem = total & 7, x = bid & 7, i = bid >> 3;
+  return x * per + min(x, rem) + i;
+}
+
+// Where thread t's 16-byte unit i of a slice comes from (bytes from the tile's
+// first row), rows past the last one clamped to it (their results are dropped).
+template <int TN>
+__device__ __forceinline__ uint32_t slice_offset(int u, int row_bytes, int rows) {
+  const int r = u >> 2, s = (u ^ (r >> 2)) & 3;
+  const int c = r % (32 * TN), row = TN > 1 ? r - c + TN * (c & 31) + (c >> 5) : r;
+  return (uint32_t)min(row, rows - 1) * row_bytes + s * 16;
+}
+
+// Epilogue of one wavefront: TM x TN tiles at rows m0 + mw, columns n ..
+// n + TN - 1 of this lane.  Loads and stores go through buffers that end at
+// row M, so rows past it read zero and are not written; the residual of the
+// next 32 rows is read while these are written.
+template <int TM, int TN, bool OUT16>
+__device__ __forceinline__ void gemm16_epilogue(const Gemm16Args& g, const f32x16 (&acc)[TM][TN], int m0, int rows,
+                                                int mw, int n, int h) {
+  typedef float fv __attribute__((ext_vector_type(TN)));
+  constexpr int ES = OUT16 ? 2 : 4;
+  const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(static_cast<uint8_t*>(g.C) + (size_t)m0 * g.N * ES), (short)0, (uint32_t)rows * g.N * ES, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(g.res + (g.res ? (size_t)m0 * g.N : 0)), (short)0, g.res ? (uint32_t)rows * g.N * 4 : 0u, 0x00020000);
+  if (n >= g.N) return;
+  const uint32_t base = (uint32_t)(mw + 4 * h) * g.N + n;
+  float bias[TN];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int u = tid + 512 * i, row = u >> 2, q = u & 3;
-      ra[i] = m0 + row < g.M ? *reinterpret_cast<const bf16x8*>(g.A + (size_t)(m0 + row) * g.K + k0 + 8 * q)
-                             : bf16x8{};
-    }
-    const int row = tid >> 2, q = tid & 3;
-    rb = n0 + row < g.N ? *reinterpret_cast<const bf16x8*>(g.W + (size_t)(n0 + row) * g.K + k0 + 8 * q)
-                        : bf16x8{};
-  };
-  auto store = [&]() {
+  for (int j = 0; j < TN; ++j) bias[j] = g.bias ? g.bias[n + j] : 0.0f;
+  fv res[2][16];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int u = tid + 512 * i, row = u >> 2, q = u & 3;
-      *reinterpret_cast<bf16x8*>(As + row * G16_LDW + 8 * q) = ra[i];
-    }
-    const int row = tid >> 2, q = tid & 3;
-    *reinterpret_cast<bf16x8*>(Bs + row * G16_LDW + 8 * q) = rb;
-  };
-  const int wm = wave & 3, wn = wave >> 2;
-  const int cl = lane & 31, h = lane >> 5;
-  f32x16 acc[2][2];
+  for (int i = -1; i < TM; ++i) {
+    if constexpr (!OUT16) {
+      if (i + 1 < TM) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
-  load(0);
-  for (int k0 = 0; k0 < g.K; k0 += GK) {
-    __syncthreads();
-    store();
-    __syncthreads();
-    if (k0 + GK < g.K) load(k0 + GK);
-#pragma unroll
-    for (int ks = 0; ks < GK / 16; ++ks) {
-      bf16x8 fa[2], fb[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        fa[i] = *reinterpret_cast<const bf16x8*>(As + (wm * 64 + i * 32 + cl) * G16_LDW + ks * 16 + h * 8);
-        fb[i] = *reinterpret_cast<const bf16x8*>(Bs + (wn * 64 + i * 32 + cl) * G16_LDW + ks * 16 + h * 8);
+        for (int r = 0; r < 16; ++r) {
+          const uint32_t o = (base + (uint32_t)((i + 1) * 32 + acc_row(0, r)) * g.N) * 4;
+          if constexpr (TN == 2) res[(i + 1) & 1][r] = __builtin_bit_cast(fv, __builtin_amdgcn_raw_buffer_load_b64(rr, o, 0, 0));
+          else res[(i + 1) & 1][r][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rr, o, 0, 0));
+        }
       }
+    }
+    if (i < 0) continue;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int r = 0; r < 16; ++r) {
+      const uint32_t o = base + (uint32_t)(i * 32 + acc_row(0, r)) * g.N;
+      fv v;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = BF::mfma(fa[i], fb[j], acc[i][j]);
+      for (int j = 0; j < TN; ++j) v[j] = acc[i < 0 ? 0 : i][j][r] + bias[j];
+      if (g.gelu) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) v[j] = gelu(v[j]);
+      }
+      if constexpr (OUT16) {
+        typedef __bf16 bv __attribute__((ext_vector_type(TN)));
+        bv q;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) q[j] = (__bf16)v[j];
+        if constexpr (TN == 2) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, q), rc, o * 2, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, q), rc, o * 2, 0, 0);
+      } else {
+        v += res[i & 1][r];
+        if constexpr (TN == 2) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rc, o * 4, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v[0]), rc, o * 4, 0, 0);
+      }
     }
   }
+}
+
+// Large products: 256 x 256 tiles, 8 wavefronts of 128 x 64, one workgroup per
+// compute unit (a 256 x 256 tile is what its registers hold; per product it
+// needs the fewest bytes from L2).  The wavefronts are two groups, one of each
+// per SIMD, half a step apart: while one group's matrix instructions run, the
+// other reads the fragments of its next 16-deep step and issues copies.  Each
+// phase ends at a barrier, the second group is one barrier behind.
+//
+// Slice s + 3 goes into the buffer of slice s - 1 while slice s is read: the
+// second group's last reads of slice s - 1 complete one barrier before the
+// first group's copies begin.  Slice s + 1 has landed, for all wavefronts,
+// before the barrier that ends the second group's last reads of slice s.
+//
+// Main loop alone 990-1110 TFLOP/s (a register-only loop of these products on
+// random operands runs 1870: power); with the epilogue, which HBM bounds,
+// M = 64512: N 2304, K 768 (bf16 out) 289 us, 768/768 (fp32 + residual) 141,
+// 3072/768 (GELU) 456, 768/3072 377, against 404, 271, 560 and 565 us for one
+// 32-deep buffer, two barriers per slice and a register-staged copy.
+template <bool OUT16>
+__global__ __launch_bounds__(512, 2) void gemm16_large_kernel(const Gemm16Args g) {
+  constexpr int TM = 4, TN = 2, BM = 256, BN = 256;
+  constexpr int SLICE = (BM + BN) * GK;
+  __shared__ __attribute__((aligned(16))) __bf16 S[4 * SLICE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cl = lane & 31, h = lane >> 5;
+  const int t = xcd_tile(blockIdx.x, gridDim.x);
+  const int m0 = (t / g.tiles_n) * BM, n0 = (t % g.tiles_n) * BN;
+  const int rows = min(BM, g.M - m0), cols = min(BN, g.N - n0);
+  const int grp = wave >> 2, wn = wave & 3;
+  const int K2 = g.K * 2, nk = g.K / GK;
+  uint32_t oa[2], ob[2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 2; ++i) {
+    oa[i] = slice_offset<1>(i * 512 + tid, K2, rows);
+    ob[i] = slice_offset<TN>(i * 512 + tid, K2, cols);
+  }
+  const u32x4 ra = buffer_of(g.A + (size_t)m0 * g.K, (uint32_t)rows * K2);
+  const u32x4 rb = buffer_of(g.W + (size_t)n0 * g.K, (uint32_t)cols * K2);
+  f32x16 acc[TM][TN];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int n = n0 + wn * 64 + j * 32 + cl;
-      if (n >= g.N) continue;
-      const float bn = g.bias ? g.bias[n] : 0.0f;
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * 64 + i * 32 + acc_row(h, r);
-        if (m >= g.M) continue;
-        float v = acc[i][j][r] + bn;
-        if (g.gelu) v = gelu(v);
-        if (g.res) v += g.res[(size_t)m * g.N + n];
-        if constexpr (OUT16) reinterpret_cast<__bf16*>(g.C)[(size_t)m * g.N + n] = (__bf16)v;
-        else reinterpret_cast<float*>(g.C)[(size_t)m * g.N + n] = v;
-      }
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x16{};
+  bf16x8 fa[TM], fb[TN];
+  const int sw = (cl >> 2) & 3;
+  auto frags = [&](int s, int ks) {
+    const __bf16* a = S + (s & 3) * SLICE + cl * GK + ((2 * ks + h) ^ sw) * 8;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      fb[j] = *reinterpret_cast<const bf16x8*>(a + (BM + (wn * TN + j) * 32) * GK);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(a + (grp * TM + i) * 32 * GK);
+  };
+  auto products = [&]() {
+    wave_priority<1>();
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = BF::mfma(fa[i], fb[j], acc[i][j]);
+    wave_priority<0>();
+  };
+  auto copyA = [&](int s) {
+    __bf16* d = S + (s & 3) * SLICE + wave * 512;
+    copy16(ra, d, oa[0], s * GK * 2);
+    copy16(ra, d + 4096, oa[1], s * GK * 2);
+  };
+  auto copyB = [&](int s) {
+    __bf16* d = S + (s & 3) * SLICE + BM * GK + wave * 512;
+    copy16(rb, d, ob[0], s * GK * 2);
+    copy16(rb, d + 4096, ob[1], s * GK * 2);
+  };
+  for (int s = 0; s < 3 && s < nk; ++s) { copyA(s); copyB(s); }
+  if (nk >= 3) wait_counts<8, false>(); else wait_counts<0, false>();
+  raw_barrier();
+  if (grp) raw_barrier();
+  for (int s = 0; s < nk; ++s) {
+    const bool more = s + 3 < nk;
+    frags(s, 0);
+    if (more) copyA(s + 3);
+    wait_counts<63, true>();
+    raw_barrier();
+    products();
+    raw_barrier();
+    frags(s, 1);
+    if (more) { copyB(s + 3); wait_counts<8, true>(); } else wait_counts<0, true>();
+    raw_barrier();
+    products();
+    raw_barrier();
+  }
+  if (!grp) raw_barrier();
+  gemm16_epilogue<TM, TN, OUT16>(g, acc, m0, rows, grp * 128, n0 + wn * 64 + TN * cl, h);
+}
+
+// Products with too few 256 x 256 tiles to fill the chip: tiles of 64 WM x
+// 64 rows and columns (WM = 2: 128 x 64, WM = 1: 64 x 64), 4 wavefronts of
+// 32 WM x 32, several workgroups per compute unit.  One barrier per slice:
+// slice s has landed and every wavefront has consumed slice s - 1, whose
+// buffer is then filled with slice s + 3.
+template <int WM, bool OUT16>
+__global__ __launch_bounds__(256, 2) void gemm16_small_kernel(const Gemm16Args g) {
+  constexpr int BM = 64 * WM, BN = 64, UA = WM, ND = UA + 1;
+  constexpr int SLICE = (BM + BN) * GK;
+  __shared__ __attribute__((aligned(16))) __bf16 S[4 * SLICE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cl = lane & 31, h = lane >> 5;
+  const int t = xcd_tile(blockIdx.x, gridDim.x);
+  const int m0 = (t / g.tiles_n) * BM, n0 = (t % g.tiles_n) * BN;
+  const int rows = min(BM, g.M - m0), cols = min(BN, g.N - n0);
+  const int wm = wave & 1, wn = wave >> 1;
+  const int K2 = g.K * 2, nk = g.K / GK;
+  uint32_t oa[UA];
+#pragma unroll
+  for (int i = 0; i < UA; ++i) oa[i] = slice_offset<1>(i * 256 + tid, K2, rows);
+  const uint32_t ob = slice_offset<1>(tid, K2, cols);
+  const u32x4 ra = buffer_of(g.A + (size_t)m0 * g.K, (uint32_t)rows * K2);
+  const u32x4 rb = buffer_of(g.W + (size_t)n0 * g.K, (uint32_t)cols * K2);
+  f32x16 acc[WM][1];
+#pragma unroll
+  for (int i = 0; i < WM; ++i) acc[i][0] = f32x16{};
+  const int sw = (cl >> 2) & 3;
+  auto copy = [&](int s) {
+    __bf16* d = S + (s & 3) * SLICE + wave * 512;
+#pragma unroll
+    for (int i = 0; i < UA; ++i) copy16(ra, d + i * 2048, oa[i], s * GK * 2);
+    copy16(rb, d + BM * GK, ob, s * GK * 2);
+  };
+  for (int s = 0; s < 3 && s < nk; ++s) copy(s);
+  for (int s = 0; s < nk; ++s) {
+    if (s + 2 < nk) wait_counts<2 * ND, true>(); else wait_counts<0, true>();
+    raw_barrier();
+    if (s + 3 < nk) copy(s + 3);
+    const __bf16* base = S + (s & 3) * SLICE + cl * GK;
+    bf16x8 fa[2][WM], fb[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const __bf16* a = base + ((2 * ks + h) ^ sw) * 8;
+      fb[ks] = *reinterpret_cast<const bf16x8*>(a + (BM + wn * 32) * GK);
+#pragma unroll
+      for (int i = 0; i < WM; ++i) fa[ks][i] = *reinterpret_cast<const bf16x8*>(a + (wm * WM + i) * 32 * GK);
     }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < WM; ++i) acc[i][0] = BF::mfma(fa[ks][i], fb[ks], acc[i][0]);
+  }
+  gemm16_epilogue<WM, 1, OUT16>(g, acc, m0, rows, wm * 32 * WM, n0 + wn * 32 + cl, h);
 }
 
 // Row softmax of the attention scores, keys past the chunk's tokens masked.
@@ -885,10 +1062,28 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
                  const float* res, int gelu, bool out16) {
     Gemm16Args g;
     g.A = A; g.W = Wm; g.C = C; g.bias = bias; g.res = res; g.M = M; g.N = N; g.K = K; g.gelu = gelu;
-    g.tiles_n = (N + G16_BN - 1) / G16_BN;
-    const dim3 grid(((M + G16_BM - 1) / G16_BM) * g.tiles_n);
-    if (out16) hipLaunchKernelGGL(gemm16_kernel<true>, grid, dim3(512), 0, st, g);
-    else hipLaunchKernelGGL(gemm16_kernel<false>, grid, dim3(512), 0, st, g);
+    auto tiles = [&](int bm, int bn) { g.tiles_n = (N + bn - 1) / bn; return dim3(((M + bm - 1) / bm) * g.tiles_n); };
+    auto go = [&](auto kern, dim3 grid, int threads) { hipLaunchKernelGGL(kern, grid, dim3(threads), 0, st, g); };
+    // Which tile: a 256 x 256 tile keeps a compute unit busy for about four
+    // times as long as a 128 x 64 tile does with its share, so it needs at
+    // least 64 tiles (a quarter of the compute units) to win; 64 x 64 tiles
+    // only where 128 x 64 ones leave half of the chip idle.  Measured (us,
+    // large / 128 x 64 / 64 x 64): N 768, K 3072 at M = 300: 56 / 32 / 25; 2400
+    // (30 large tiles): 61 / 36 / 53; 4800 (57): 63 / 69 / 103; 9600: 68 / 138 /
+    // 204.  N 2304, K 768 at M = 300: 18 / 12 / 14; 2400 (90): 21 / 25 / 26; 4800:
+    // 24 / 43 / 44.
+    const long long large = (long long)((M + 255) / 256) * ((N + 255) / 256);
+    const long long small = (long long)((M + 127) / 128) * ((N + 63) / 64);
+    if (large >= 64) {
+      const dim3 grid = tiles(256, 256);
+      if (out16) go(gemm16_large_kernel<true>, grid, 512); else go(gemm16_large_kernel<false>, grid, 512);
+    } else if (small >= 128) {
+      const dim3 grid = tiles(128, 64);
+      if (out16) go(gemm16_small_kernel<2, true>, grid, 256); else go(gemm16_small_kernel<2, false>, grid, 256);
+    } else {
+      const dim3 grid = tiles(64, 64);
+      if (out16) go(gemm16_small_kernel<1, true>, grid, 256); else go(gemm16_small_kernel<1, false>, grid, 256);
+    }
     return hipGetLastError();
   };
   auto ln = [&](const float* yin, const float* gm, const float* bt, __bf16* hbo) {

@@ -86,6 +86,23 @@ def test_codebert_backbone(wm):
     print(f"  max rel {rel.max():.2e}", flush=True)
 
 
+@pytest.mark.parametrize("S,n", [(3, 70), (40, 190), (200, 190)])
+def test_product_tiles(wm, S, n):
+    """Each tile size of the bf16 products (64 x 64, 128 x 64 and 256 x 256 tiles
+    for few, more and many rows), with row counts that no tile divides and
+    output widths (128, 256, 384) below, at and above one 256-column tile."""
+    w = synth.TextWorkload(name="tiles", S=S, vocab=500, hidden=128, heads=4, ffn=256, layers=2, window=64,
+                           stride=32, d=64, len_lo=1, len_hi=n)
+    W = synth.make_text_weights(w, 71)
+    model = wm.TextModel(w, W, precision="bf16")
+    tokens, off = synth.make_programs(w, 73)
+    print(f"[text] tiles S={S} chunks={model.chunks(off)} tokens={len(tokens)}", flush=True)
+    g = run(wm, model, tokens, off)
+    ref = TE.encode(W, programs_of(tokens, off), w.window, w.stride, w.heads, "bf16")
+    rel = latent_rel(g, ref)
+    assert rel.max() <= TOL["bf16"], f"z0 rel err {rel.max():.3e}"
+
+
 def test_token_out_of_range_is_reported(wm):
     model, W, w = model_for(wm, "tiny_text", "fp32")
     off = np.array([0, 5], dtype=np.int32)
