@@ -3,13 +3,14 @@
 // CodeBERT (RoBERTa) shape on every chunk, masked mean pooling per chunk, the
 // mean over a program's chunks, and a linear projection head to the latent.
 //
-// All chunks of all programs are one batch of rows r = c * window + p (chunk
-// c, position p; positions past a chunk's tokens are padding: never pooled,
-// masked as attention keys).  Dense products run in one LDS-tiled
-// matrix-core kernel (128 x 128 output tiles, 32-deep stages, operands
-// rounded as product operands while they are staged); attention is the same
-// kernel batched over (chunk, head) for the scores and for probabilities x
-// values, with a row softmax in between.
+// All chunks of all programs are one batch of rows, one row per (chunk,
+// position).  bf16: the rows are the chunks' tokens and nothing else; dense
+// products on bf16-stored operands, attention fused per (chunk, head).
+// float32: every chunk takes `window` rows (positions past its tokens are
+// padding: never pooled, masked as attention keys); the dense products run in
+// an LDS-tiled matrix-core kernel (128 x 128 output tiles, 32-deep stages),
+// and attention is the same kernel batched over (chunk, head) for the scores
+// and for probabilities x values, with a row softmax in between.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -68,11 +69,17 @@ __device__ __forceinline__ float wave_max(float x) {
   return x;
 }
 
+// One LayerNorm output (the same value wherever it is recomputed).
+__device__ __forceinline__ float ln_value(float x, float mean, float rs, float g, float b) {
+  return fmaf((x - mean) * rs, g, b);
+}
+
 // Programs and their chunks (host-built, passed by value).
 struct TTable {
   int32_t S;
   int32_t chunk_off[WM_TEXT_MAX_PROGRAMS + 1];   // first chunk of each program
   int32_t tok_off[WM_TEXT_MAX_PROGRAMS + 1];     // first token of each program
+  int32_t row_off[WM_TEXT_MAX_PROGRAMS + 1];     // first row of each program
 };
 
 __device__ __forceinline__ int program_of(const TTable& tt, int c) {
@@ -83,18 +90,58 @@ __device__ __forceinline__ int program_of(const TTable& tt, int c) {
   }
   return lo;
 }
-// First token and token count of chunk c.
+// First token, token count and first row of chunk c.  A program's chunks are
+// `window` rows apart; only its last chunk can hold fewer tokens, and on the
+// bf16 path the next program's rows follow them directly.
 __device__ __forceinline__ void chunk_span(const TTable& tt, int c, int window, int stride,
-                                           int& first, int& len) {
-  const int s = program_of(tt, c);
-  first = tt.tok_off[s] + (c - tt.chunk_off[s]) * stride;
+                                           int& first, int& len, int& row) {
+  const int s = program_of(tt, c), k = c - tt.chunk_off[s];
+  first = tt.tok_off[s] + k * stride;
   len = min(window, tt.tok_off[s + 1] - first);
+  row = tt.row_off[s] + k * window;
+}
+// Chunk and position of row r.
+__device__ __forceinline__ void row_place(const TTable& tt, int r, int window, int& c, int& p) {
+  int lo = 0, hi = tt.S - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (tt.row_off[mid] <= r) lo = mid; else hi = mid - 1;
+  }
+  const int k = min((r - tt.row_off[lo]) / window, tt.chunk_off[lo + 1] - tt.chunk_off[lo] - 1);
+  c = tt.chunk_off[lo] + k;
+  p = r - tt.row_off[lo] - k * window;
 }
 
 // ---------------------------------------------------------------------------
-// h[r] = LN(tok_emb[id] + pos_emb[p]); padding rows are zero.  One wavefront
-// per row, lanes over the features.
+// Row sums before LayerNorm.  y[r] = tok_emb[id] + pos_emb[p] (padding rows
+// zero), then as ln_kernel.  One wavefront per row, lanes over the features.
 constexpr int LN_MAX_PER_LANE = 16;               // hidden <= 1024
+
+// LayerNorm of one row held as x[i] = feature lane + 64 i.  bf16 path: writes
+// the normalised row as the next product's operand (hb) and its mean and
+// 1/deviation (stats); the residual path and the pooling recompute the float32
+// values from y and those two, so they are never stored (10 -> 6 bytes per
+// feature; 68,608 rows of 768: 85 -> 60 us).  fp32 path: writes h.
+__device__ __forceinline__ void ln_row(const float (&x)[LN_MAX_PER_LANE], float s, int H, const float* g,
+                                       const float* b, size_t r, float* h, __bf16* hb, float2* stats) {
+  const int lane = threadIdx.x & 63;
+  const float mean = wave_sum(s) / (float)H;
+  float v = 0.0f;
+#pragma unroll
+  for (int i = 0; i < LN_MAX_PER_LANE; ++i)
+    if (lane + 64 * i < H) v = fmaf(x[i] - mean, x[i] - mean, v);
+  const float rs = rsqrtf(wave_sum(v) / (float)H + LN_EPS);
+  if (stats && lane == 0) stats[r] = make_float2(mean, rs);
+#pragma unroll
+  for (int i = 0; i < LN_MAX_PER_LANE; ++i) {
+    const int f = lane + 64 * i;
+    if (f < H) {
+      const float o = ln_value(x[i], mean, rs, g[f], b[f]);
+      if (hb) hb[r * H + f] = (__bf16)o;
+      else h[r * H + f] = o;
+    }
+  }
+}
 
 __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t* __restrict__ tokens,
                                                        const TTable tt, int window, int stride,
@@ -102,20 +149,17 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t* __restrict
                                                        const float* __restrict__ pos_emb,
                                                        const float* __restrict__ g,
                                                        const float* __restrict__ b, int H, int vocab,
-                                                       int rows, float* __restrict__ h,
-                                                       __bf16* __restrict__ hb, int32_t* err) {
+                                                       int rows, float* __restrict__ y, float* __restrict__ h,
+                                                       __bf16* __restrict__ hb, float2* __restrict__ stats,
+                                                       int32_t* err) {
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= rows) return;
-  const int c = r / window, p = r - c * window;
-  int first, len;
-  chunk_span(tt, c, window, stride, first, len);
-  float* out = h + (size_t)r * H;
-  if (p >= len) {
-    for (int f = lane; f < H; f += 64) {
-      out[f] = 0.0f;
-      if (hb) hb[(size_t)r * H + f] = (__bf16)0.0f;
-    }
+  int c, p, first, len, row;
+  row_place(tt, r, window, c, p);
+  chunk_span(tt, c, window, stride, first, len, row);
+  if (p >= len) {                                 // fp32 path only: padding
+    for (int f = lane; f < H; f += 64) h[(size_t)r * H + f] = 0.0f;
     return;
   }
   int id = tokens[first + p];
@@ -129,32 +173,18 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t* __restrict
   for (int i = 0; i < LN_MAX_PER_LANE; ++i) {
     const int f = lane + 64 * i;
     x[i] = f < H ? tok_emb[(size_t)id * H + f] + pos_emb[(size_t)p * H + f] : 0.0f;
+    if (hb && f < H) y[(size_t)r * H + f] = x[i];
     s += x[i];
   }
-  const float mean = wave_sum(s) / (float)H;
-  float v = 0.0f;
-#pragma unroll
-  for (int i = 0; i < LN_MAX_PER_LANE; ++i) {
-    const int f = lane + 64 * i;
-    if (f < H) v = fmaf(x[i] - mean, x[i] - mean, v);
-  }
-  const float rs = rsqrtf(wave_sum(v) / (float)H + LN_EPS);
-#pragma unroll
-  for (int i = 0; i < LN_MAX_PER_LANE; ++i) {
-    const int f = lane + 64 * i;
-    if (f < H) {
-      const float o = (x[i] - mean) * rs * g[f] + b[f];
-      out[f] = o;
-      if (hb) hb[(size_t)r * H + f] = (__bf16)o;
-    }
-  }
+  ln_row(x, s, H, g, b, r, h, hb, stats);
 }
 
-// h[r] = LN(y[r]) (the residual sum is formed by the product's epilogue).
+// LN(y[r]) (the residual sum is formed by the product's epilogue).
 __global__ __launch_bounds__(256) void ln_kernel(const float* __restrict__ y,
                                                  const float* __restrict__ g,
                                                  const float* __restrict__ b, int H, int rows,
-                                                 float* __restrict__ h, __bf16* __restrict__ hb) {
+                                                 float* __restrict__ h, __bf16* __restrict__ hb,
+                                                 float2* __restrict__ stats) {
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= rows) return;
@@ -167,24 +197,7 @@ __global__ __launch_bounds__(256) void ln_kernel(const float* __restrict__ y,
     x[i] = f < H ? in[f] : 0.0f;
     s += x[i];
   }
-  const float mean = wave_sum(s) / (float)H;
-  float v = 0.0f;
-#pragma unroll
-  for (int i = 0; i < LN_MAX_PER_LANE; ++i) {
-    const int f = lane + 64 * i;
-    if (f < H) v = fmaf(x[i] - mean, x[i] - mean, v);
-  }
-  const float rs = rsqrtf(wave_sum(v) / (float)H + LN_EPS);
-  float* out = h + (size_t)r * H;
-#pragma unroll
-  for (int i = 0; i < LN_MAX_PER_LANE; ++i) {
-    const int f = lane + 64 * i;
-    if (f < H) {
-      const float o = (x[i] - mean) * rs * g[f] + b[f];
-      out[f] = o;
-      if (hb) hb[(size_t)r * H + f] = (__bf16)o;
-    }
-  }
+  ln_row(x, s, H, g, b, r, h, hb, stats);
 }
 
 // ---------------------------------------------------------------------------
@@ -333,7 +346,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(const GemmArgs g) {
 
 // bf16 dense product with operands stored as bf16 (the product-operand
 // values themselves):  C = epi(A . W^T), A [M][K] and W [N][K] row-major,
-// epilogue + bias[n], GELU, + residual R[m][n] (fp32), C fp32 or bf16.
+// epilogue + bias[n], GELU, + LN(y)[m][n] (the residual, recomputed from the
+// previous row sums y, their mean and 1/deviation), C fp32 or bf16.  With a
+// residual C is y itself: each element is read and then written by one lane.
 //
 // Both kernels stage 32-deep slices of A and W in a ring of four LDS buffers
 // by loads straight to LDS, three slices ahead.  A slice row is 64 bytes (four
@@ -347,7 +362,9 @@ struct Gemm16Args {
   const __bf16* W;
   void* C;
   const float* bias;
-  const float* res;
+  const float* res;        // y, or null
+  const float2* stats;     // [M] mean, 1/deviation of y
+  const float *ln_g, *ln_b;
   int M, N, K, tiles_n, gelu;
 };
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -412,7 +429,7 @@ __device__ __forceinline__ uint32_t slice_offset(int u, int row_bytes, int rows)
 // Epilogue of one wavefront: TM x TN tiles at rows m0 + mw, columns n ..
 // n + TN - 1 of this lane.  Loads and stores go through buffers that end at
 // row M, so rows past it read zero and are not written; the residual of the
-// next 32 rows is read while these are written.
+// next rows is read while these are written.
 template <int TM, int TN, bool OUT16>
 __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args& g, const f32x16 (&acc)[TM][TN], int m0, int rows,
                                                 int mw, int n, int h) {
@@ -424,29 +441,42 @@ __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args& g, const f32x1
       (void*)(g.res + (g.res ? (size_t)m0 * g.N : 0)), (short)0, g.res ? (uint32_t)rows * g.N * 4 : 0u, 0x00020000);
   if (n >= g.N) return;
   const uint32_t base = (uint32_t)(mw + 4 * h) * g.N + n;
-  float bias[TN];
+  float bias[TN], lg[TN], lb[TN];
 #pragma unroll
-  for (int j = 0; j < TN; ++j) bias[j] = g.bias ? g.bias[n + j] : 0.0f;
-  fv res[2][16];
-#pragma unroll
-  for (int i = -1; i < TM; ++i) {
+  for (int j = 0; j < TN; ++j) {
+    bias[j] = g.bias[n + j];
     if constexpr (!OUT16) {
-      if (i + 1 < TM) {
+      lg[j] = g.ln_g[n + j];
+      lb[j] = g.ln_b[n + j];
+    }
+  }
+  fv res[2][8];
+  u32x2 st[2][8];
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(g.stats + (g.stats ? m0 : 0)), (short)0, g.stats ? (uint32_t)rows * 8u : 0u, 0x00020000);
+  // half a tile (8 of a lane's 16 rows) at a time
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const uint32_t o = (base + (uint32_t)((i + 1) * 32 + acc_row(0, r)) * g.N) * 4;
+  for (int i = -1; i < 2 * TM; ++i) {
+    if constexpr (!OUT16) {
+      if (i + 1 < 2 * TM) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const uint32_t row = ((i + 1) >> 1) * 32 + acc_row(0, 8 * ((i + 1) & 1) + r);
+          const uint32_t o = (base + row * g.N) * 4;
           if constexpr (TN == 2) res[(i + 1) & 1][r] = __builtin_bit_cast(fv, __builtin_amdgcn_raw_buffer_load_b64(rr, o, 0, 0));
           else res[(i + 1) & 1][r][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rr, o, 0, 0));
+          st[(i + 1) & 1][r] = __builtin_amdgcn_raw_buffer_load_b64(rs, (uint32_t)(mw + 4 * h + row) * 8, 0, 0);
         }
       }
     }
     if (i < 0) continue;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const uint32_t o = base + (uint32_t)(i * 32 + acc_row(0, r)) * g.N;
+    for (int r = 0; r < 8; ++r) {
+      const uint32_t row = (i >> 1) * 32 + acc_row(0, 8 * (i & 1) + r);
+      const uint32_t o = base + row * g.N;
       fv v;
 #pragma unroll
-      for (int j = 0; j < TN; ++j) v[j] = acc[i < 0 ? 0 : i][j][r] + bias[j];
+      for (int j = 0; j < TN; ++j) v[j] = acc[i < 0 ? 0 : i >> 1][j][8 * (i & 1) + r] + bias[j];
       if (g.gelu) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) v[j] = gelu(v[j]);
@@ -459,7 +489,9 @@ __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args& g, const f32x1
         if constexpr (TN == 2) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, q), rc, o * 2, 0, 0);
         else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, q), rc, o * 2, 0, 0);
       } else {
-        v += res[i & 1][r];
+        const float mean = __uint_as_float(st[i & 1][r][0]), inv = __uint_as_float(st[i & 1][r][1]);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) v[j] += ln_value(res[i & 1][r][j], mean, inv, lg[j], lb[j]);
         if constexpr (TN == 2) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rc, o * 4, 0, 0);
         else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v[0]), rc, o * 4, 0, 0);
       }
@@ -626,8 +658,8 @@ __global__ __launch_bounds__(256) void softmax_kernel(float* __restrict__ s, con
   const long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= rows) return;
   const int c = (int)(r / ((long long)heads * window));
-  int first, len;
-  chunk_span(tt, c, window, stride, first, len);
+  int first, len, row0;
+  chunk_span(tt, c, window, stride, first, len, row0);
   float* row = s + r * window;
   float x[SM_MAX_PER_LANE];
   float mx = -INFINITY;
@@ -656,12 +688,15 @@ __global__ __launch_bounds__(256) void softmax_kernel(float* __restrict__ s, con
 // takes queries [32 w, 32 w + 32).  K and V of the chunk are staged in LDS
 // once (K row-major, V transposed with its keys permuted into accumulator
 // order); the scores are computed transposed, S^T = K . Q^T, so a query is a
-// lane's column and its softmax statistics are per-lane sums completed across
-// the lane pair (L, L^32).  Pass 1 forms the row maximum and sum online over
-// 32-key blocks; pass 2 recomputes the scores, normalises them (the
-// probabilities exactly as defined, rounded as product operands) and
+// lane's column and its softmax statistics are per-lane values completed across
+// the lane pair (L, L^32).  Pass 1 finds the row maximum; pass 2 recomputes the
+// scores (matrix instructions have room: the vector unit is what bounds this
+// kernel), forms p = exp(s - max), rounds it as the product operand,
 // accumulates O^T = V^T . P with P straight from the accumulators (its key
-// order is the one V was permuted into).
+// order is the one V was permuted into) and sums p; O is divided by the sum
+// at the end.  One exponential per score instead of two, and keys are masked
+// in the last 32-key block only: 68,608 rows, 12 heads of 64: 324 -> 184 us.
+__device__ __forceinline__ float exp2_of(float x) { return __builtin_amdgcn_exp2f(x); }
 template <int DH>
 __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restrict__ qkv,
                                                          __bf16* __restrict__ ctx, const TTable tt,
@@ -675,11 +710,11 @@ __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restric
   __bf16* Ks = lds_att;                       // [window][KW]
   __bf16* Vt = lds_att + (size_t)window * KW; // [DH][VW]
   const int c = blockIdx.x / heads, head = blockIdx.x % heads;
-  int first, len;
-  chunk_span(tt, c, window, stride, first, len);
+  int first, len, row0;
+  chunk_span(tt, c, window, stride, first, len, row0);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nt = blockDim.x;
   const int cl = lane & 31, h = lane >> 5;
-  const __bf16* base = qkv + (size_t)c * window * 3 * H + head * DH;
+  const __bf16* base = qkv + (size_t)row0 * 3 * H + head * DH;
   const int nkb = (len + 31) / 32;
 
   // stage K (row-major) and V (transposed, keys in accumulator order per block)
@@ -702,7 +737,7 @@ __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restric
   const int q = wave * 32 + cl;
   bf16x8 qf[KS];
   {
-    const __bf16* qrow = base + (size_t)min(q, window - 1) * 3 * H;
+    const __bf16* qrow = base + (size_t)min(q, len - 1) * 3 * H;
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qrow + 16 * kk + 8 * h);
   }
@@ -718,34 +753,29 @@ __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restric
     }
     return sacc;
   };
-  // pass 1: running maximum and sum of exp over the valid keys
-  float mx = -INFINITY, sum = 0.0f;
-  for (int kb = 0; kb < nkb; ++kb) {
+  // pass 1: the maximum score over the valid keys (the chunk's last block may
+  // hold fewer than 32)
+  const int nfull = len / 32;
+  float mx = -INFINITY;
+  for (int kb = 0; kb < nfull; ++kb) {
     const f32x16 sacc = scores(kb);
-    float bm = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
+  }
+  if (nfull < nkb) {
+    const f32x16 sacc = scores(nfull);
 #pragma unroll
     for (int r = 0; r < 16; ++r)
-      if (kb * 32 + acc_row(h, r) < len) bm = fmaxf(bm, sacc[r] * scale);
-    const float nm = fmaxf(mx, bm);
-    float bs = 0.0f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      if (kb * 32 + acc_row(h, r) < len) bs += __expf(sacc[r] * scale - nm);
-    sum = (mx == -INFINITY ? 0.0f : sum * __expf(mx - nm)) + bs;
-    mx = nm;
+      if (nfull * 32 + acc_row(h, r) < len) mx = fmaxf(mx, sacc[r]);
   }
-  {
-    const float mo = __shfl_xor(mx, 32), so = __shfl_xor(sum, 32);
-    const float m2 = fmaxf(mx, mo);
-    sum = (mx == -INFINITY ? 0.0f : sum * __expf(mx - m2)) + (mo == -INFINITY ? 0.0f : so * __expf(mo - m2));
-    mx = m2;
-  }
-  const float inv = 1.0f / sum;
-  // pass 2: probabilities and O^T = V^T . P
+  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  // pass 2: p = exp((s - max) scale) as 2^(s c - max c), O^T += V^T . P, sum of p
+  const float c2 = scale * 1.4426950408889634f, mc = mx * c2;
+  float sum = 0.0f;
   f32x16 oacc[DB];
 #pragma unroll
   for (int b = 0; b < DB; ++b) oacc[b] = f32x16{};
-  for (int kb = 0; kb < nkb; ++kb) {
+  auto block = [&](int kb, bool last) {
     const f32x16 sacc = scores(kb);
     bf16x8 pf[2];
 #pragma unroll
@@ -753,7 +783,9 @@ __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restric
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int r = 8 * f + j;
-        const float pv = kb * 32 + acc_row(h, r) < len ? __expf(sacc[r] * scale - mx) * inv : 0.0f;
+        float pv = exp2_of(fmaf(sacc[r], c2, -mc));
+        if (last) pv = kb * 32 + acc_row(h, r) < len ? pv : 0.0f;
+        sum += pv;
         pf[f][j] = (__bf16)pv;
       }
 #pragma unroll
@@ -763,36 +795,57 @@ __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restric
         const bf16x8 vfrag = *reinterpret_cast<const bf16x8*>(Vt + (b * 32 + cl) * VW + kb * 32 + 16 * f + 8 * h);
         oacc[b] = BF::mfma(vfrag, pf[f], oacc[b]);
       }
-  }
-  if (q < window) {             // the output as the next product's operand
-    __bf16* orow = ctx + ((size_t)c * window + q) * H + head * DH;
+  };
+  for (int kb = 0; kb < nfull; ++kb) block(kb, false);
+  if (nfull < nkb) block(nfull, true);
+  const float inv = 1.0f / (sum + __shfl_xor(sum, 32));
+  if (q < len) {                // the output as the next product's operand
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    __bf16* orow = ctx + ((size_t)row0 + q) * H + head * DH + 4 * h;
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) orow[32 * b + acc_row(h, r)] = (__bf16)oacc[b][r];
+      for (int r4 = 0; r4 < 4; ++r4) {
+        bf16x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = (__bf16)(oacc[b][4 * r4 + i] * inv);
+        *reinterpret_cast<bf16x4*>(orow + 32 * b + 8 * r4) = o;
+      }
   }
 }
 
-// Mean of each chunk's rows over its tokens.  One workgroup per chunk.
 // Masked mean over a chunk's tokens: one workgroup per chunk; thread t sums
 // the feature quad t % (H/4) over the tokens p = t / (H/4) + k G (G token
 // groups, 16-byte loads), then the G partial sums are added in group order.
+// bf16 path (stats given): the rows are LN(y), recomputed as they are read.
 constexpr int POOL_THREADS = 1024;
-__global__ __launch_bounds__(POOL_THREADS) void pool_kernel(const float* __restrict__ h, const TTable tt,
+__global__ __launch_bounds__(POOL_THREADS) void pool_kernel(const float* __restrict__ h, const float2* __restrict__ stats,
+                                                            const float* __restrict__ ln_g,
+                                                            const float* __restrict__ ln_b, const TTable tt,
                                                             int window, int stride, int H,
                                                             float* __restrict__ pooled) {
   typedef float f4 __attribute__((ext_vector_type(4)));
   __shared__ f4 part[POOL_THREADS];
   const int c = blockIdx.x, tid = threadIdx.x;
-  int first, len;
-  chunk_span(tt, c, window, stride, first, len);
+  int first, len, row0;
+  chunk_span(tt, c, window, stride, first, len, row0);
   const float inv = 1.0f / (float)len;
   const int nq = H / 4, groups = POOL_THREADS / nq;        // H <= 1024: at least 4 groups
   const int q = tid % nq, grp = tid / nq;
   f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
   if (grp < groups) {
-    const f4* base = reinterpret_cast<const f4*>(h + (size_t)c * window * H) + q;
-    for (int p = grp; p < len; p += groups) acc += base[(size_t)p * nq];
+    const f4* base = reinterpret_cast<const f4*>(h + (size_t)row0 * H) + q;
+    if (stats) {
+      const f4 g = reinterpret_cast<const f4*>(ln_g)[q], b = reinterpret_cast<const f4*>(ln_b)[q];
+      for (int p = grp; p < len; p += groups) {
+        const f4 x = base[(size_t)p * nq];
+        const float2 st = stats[row0 + p];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] += ln_value(x[i], st.x, st.y, g[i], b[i]);
+      }
+    } else {
+      for (int p = grp; p < len; p += groups) acc += base[(size_t)p * nq];
+    }
   }
   part[tid] = acc;
   __syncthreads();
@@ -850,7 +903,7 @@ bool bf16_path(const wm_text_dims& d) {
 }
 
 struct TextLayout {
-  size_t err, h, qkv, sc, ctx, y, f, pooled, hb, qkvb, ctxb, fb, total;
+  size_t err, h, qkv, sc, ctx, y, f, pooled, hb, qkvb, ctxb, fb, stats, total;
 };
 
 TextLayout text_layout(const wm_text_dims& dm, int n_chunks) {
@@ -859,19 +912,21 @@ TextLayout text_layout(const wm_text_dims& dm, int n_chunks) {
   TextLayout L;
   size_t o = 0;
   L.err = o; o += 256;
-  L.h = o; o = al256(o + rows * H * 4);
+  L.h = o; o = al256(o + (bf ? 0 : rows * H * 4));
   L.qkv = o; o = al256(o + (bf ? 0 : rows * 3 * H * 4));
   L.sc = o; o = al256(o + (bf ? 0 : (size_t)n_chunks * dm.heads * dm.window * dm.window * 4));
   L.ctx = o; o = al256(o + (bf ? 0 : rows * H * 4));
   L.y = o; o = al256(o + rows * H * 4);
   L.f = o; o = al256(o + (bf ? 0 : rows * (size_t)dm.ffn * 4));
   L.pooled = o; o = al256(o + (size_t)n_chunks * H * 4);
-  // bf16: the product operands (the fp32 qkv, scores, context and hidden
-  // buffers above are then unused and sized zero)
+  // bf16: the product operands and the rows' LayerNorm statistics (the fp32
+  // h, qkv, scores, context and hidden buffers above are then unused and
+  // sized zero)
   L.hb = o; o = al256(o + (bf ? rows * H * 2 : 0));
   L.qkvb = o; o = al256(o + (bf ? rows * 3 * H * 2 : 0));
   L.ctxb = o; o = al256(o + (bf ? rows * H * 2 : 0));
   L.fb = o; o = al256(o + (bf ? rows * (size_t)dm.ffn * 2 : 0));
+  L.stats = o; o = al256(o + (bf ? rows * 8 : 0));
   L.total = o;
   return L;
 }
@@ -1029,9 +1084,15 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
   TTable tt;
   tt.S = S;
   tt.chunk_off[0] = 0;
+  tt.row_off[0] = 0;
   for (int s = 0; s < S; ++s) {
     tt.tok_off[s] = tok_off[s];
-    tt.chunk_off[s + 1] = tt.chunk_off[s] + n_chunks_of(tok_off[s + 1] - tok_off[s], d.window, d.stride);
+    const int n = tok_off[s + 1] - tok_off[s], nc = n_chunks_of(n, d.window, d.stride);
+    tt.chunk_off[s + 1] = tt.chunk_off[s] + nc;
+    // the bf16 path's rows are the chunks' tokens alone; the float32 path's
+    // batched products take every chunk at `window` rows
+    tt.row_off[s + 1] = tt.row_off[s] + (nc == 0 ? 0 : !bf16_path(d) ? nc * d.window
+                                         : (nc - 1) * d.window + (n - (nc - 1) * d.stride));
   }
   tt.tok_off[S] = tok_off[S];
 
@@ -1042,7 +1103,7 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
   float *h = fp(L.h), *qkv = fp(L.qkv), *sc = fp(L.sc), *ctx = fp(L.ctx), *y = fp(L.y), *f = fp(L.f);
   float* pooled = fp(L.pooled);
   const int H = d.hidden, F = d.ffn, W = d.window, nh = d.heads, dh = H / nh;
-  const int rows = n_chunks * W;
+  const int rows = tt.row_off[S];
   const bool bf = d.precision == WM_BF16;
   // bf16 operand path: fused attention (head width 32 or 64, K and V of a
   // window in LDS) and products on bf16-stored operands
@@ -1058,10 +1119,12 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
     if (e_ != hipSuccess) return set_error(WM_ERR_DEVICE, std::string("kernel launch: ") + hipGetErrorString(e_)); \
   } while (0)
 
+  float2* stats = fused ? reinterpret_cast<float2*>(w8 + L.stats) : nullptr;
   auto g16 = [&](const __bf16* A, int M, int K, const __bf16* Wm, int N, void* C, const float* bias,
-                 const float* res, int gelu, bool out16) {
+                 const float* res, const float* lng, const float* lnb, int gelu, bool out16) {
     Gemm16Args g;
-    g.A = A; g.W = Wm; g.C = C; g.bias = bias; g.res = res; g.M = M; g.N = N; g.K = K; g.gelu = gelu;
+    g.A = A; g.W = Wm; g.C = C; g.bias = bias; g.res = res; g.stats = res ? stats : nullptr;
+    g.ln_g = lng; g.ln_b = lnb; g.M = M; g.N = N; g.K = K; g.gelu = gelu;
     auto tiles = [&](int bm, int bn) { g.tiles_n = (N + bn - 1) / bn; return dim3(((M + bm - 1) / bm) * g.tiles_n); };
     auto go = [&](auto kern, dim3 grid, int threads) { hipLaunchKernelGGL(kern, grid, dim3(threads), 0, st, g); };
     // Which tile: a 256 x 256 tile keeps a compute unit busy for about four
@@ -1087,7 +1150,7 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
     return hipGetLastError();
   };
   auto ln = [&](const float* yin, const float* gm, const float* bt, __bf16* hbo) {
-    hipLaunchKernelGGL(ln_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, yin, gm, bt, H, rows, h, hbo);
+    hipLaunchKernelGGL(ln_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, yin, gm, bt, H, rows, h, hbo, stats);
     return hipGetLastError();
   };
   __bf16* hb = reinterpret_cast<__bf16*>(w8 + L.hb);
@@ -1098,13 +1161,13 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
   if (n_chunks > 0) {
     WM_TT(TK_TEXT_OTHER, [&]() { hipLaunchKernelGGL(embed_ln_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, tokens,
                                              tt, W, d.stride, m->tok_emb, m->pos_emb, m->ln0_g, m->ln0_b,
-                                             H, d.vocab, rows, h, fused ? hb : nullptr, err); return hipGetLastError(); }());
+                                             H, d.vocab, rows, y, h, fused ? hb : nullptr, stats, err); return hipGetLastError(); }());
     for (int l = 0; l < d.layers; ++l) {
       const size_t lH = (size_t)l * H;
       if (fused) {
         // bf16: every product operand is stored as bf16
         WM_TT(TK_TEXT_GEMM, g16(hb, rows, H, m->wqkv16 + lH * 3 * H, 3 * H, qkvb, m->bqkv + 3 * lH,
-                                nullptr, 0, true));
+                                nullptr, nullptr, nullptr, 0, true));
         const int lds = (W * (dh + 8) + dh * (W + 8)) * 2;
         auto kern = dh == 64 ? attention_kernel<64> : attention_kernel<32>;
         WM_TT(TK_TEXT_ATTN, [&]() {
@@ -1114,11 +1177,13 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
                              d.stride, nh, H, 1.0f / std::sqrt((float)dh));
           return hipGetLastError();
         }());
-        WM_TT(TK_TEXT_GEMM, g16(ctxb, rows, H, m->wo16 + lH * H, H, y, m->bo + lH, h, 0, false));
+        WM_TT(TK_TEXT_GEMM, g16(ctxb, rows, H, m->wo16 + lH * H, H, y, m->bo + lH, y, l ? m->ln2_g + lH - H : m->ln0_g,
+                                l ? m->ln2_b + lH - H : m->ln0_b, 0, false));
         WM_TT(TK_TEXT_OTHER, ln(y, m->ln1_g + lH, m->ln1_b + lH, hb));
         WM_TT(TK_TEXT_GEMM, g16(hb, rows, H, m->w116 + (size_t)l * F * H, F, fb, m->b1 + (size_t)l * F,
-                                nullptr, 1, true));
-        WM_TT(TK_TEXT_GEMM, g16(fb, rows, F, m->w216 + (size_t)l * H * F, H, y, m->b2 + lH, h, 0, false));
+                                nullptr, nullptr, nullptr, 1, true));
+        WM_TT(TK_TEXT_GEMM, g16(fb, rows, F, m->w216 + (size_t)l * H * F, H, y, m->b2 + lH, y, m->ln1_g + lH,
+                                m->ln1_b + lH, 0, false));
         WM_TT(TK_TEXT_OTHER, ln(y, m->ln2_g + lH, m->ln2_b + lH, hb));
         continue;
       }
@@ -1154,8 +1219,11 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
       WM_TT(TK_TEXT_GEMM, gemm(dense(f, rows, F, m->w2 + (size_t)l * H * F, H, y, m->b2 + lH, h, 0), 1, false));
       WM_TT(TK_TEXT_OTHER, ln(y, m->ln2_g + lH, m->ln2_b + lH, nullptr));
     }
-    WM_TT(TK_TEXT_OTHER, [&]() { hipLaunchKernelGGL(pool_kernel, dim3(n_chunks), dim3(POOL_THREADS), 0, st, h, tt, W,
-                                             d.stride, H, pooled); return hipGetLastError(); }());
+    const size_t lastH = d.layers > 0 ? (size_t)(d.layers - 1) * H : 0;
+    const float* last_g = d.layers > 0 ? m->ln2_g + lastH : m->ln0_g;
+    const float* last_b = d.layers > 0 ? m->ln2_b + lastH : m->ln0_b;
+    WM_TT(TK_TEXT_OTHER, [&]() { hipLaunchKernelGGL(pool_kernel, dim3(n_chunks), dim3(POOL_THREADS), 0, st, fused ? y : h,
+                                             stats, last_g, last_b, tt, W, d.stride, H, pooled); return hipGetLastError(); }());
   }
   WM_TT(TK_TEXT_OTHER, [&]() { hipLaunchKernelGGL(project_kernel, dim3(S), dim3(256), H * (int)sizeof(float), st,
                                            pooled, tt, H, d.d, m->wp, m->bp, bf ? 1 : 0, z0); return hipGetLastError(); }());
