@@ -120,6 +120,10 @@ __device__ __forceinline__ float gelu(float x) {
   return fmaf(-a, __builtin_amdgcn_exp2f(q), __builtin_elementwise_maximum(x, 0.0f));
 }
 
+// log2 of an integer parameter: for the normal floats that integers >= 1 give,
+// log2f is this one instruction (its denormal scaling left out).
+__device__ __forceinline__ float log2_of(int p) { return __builtin_amdgcn_logf((float)p); }
+
 template <class PR>
 __device__ __forceinline__ float op_value(float v) {   // the value a product operand takes
   if constexpr (PR::G == 1) return (float)(__bf16)v;
@@ -231,6 +235,7 @@ struct RollArgs {
   float* scores;
   float bc2;
   int n_hw, HW, C;
+  int lds_resident;         // narrow rollout: LDS byte offset of the resident weight groups
 };
 
 typedef __attribute__((address_space(3))) uint8_t lds_u8;

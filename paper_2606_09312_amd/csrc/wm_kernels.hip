@@ -914,7 +914,7 @@ __global__ __launch_bounds__(64 * SPLIT, 1) void rollout_split_kernel(const Roll
 #pragma unroll
     for (int p = 0; p < PMAX; ++p) {
       bad_par |= act && nx_par[p] < 1;
-      u[p] = act ? log2f((float)nx_par[p]) : 0.0f;
+      u[p] = act ? log2_of(nx_par[p]) : 0.0f;
     }
     errbits |= (bad_type ? ERRBIT_TYPE : 0) | (bad_par ? ERRBIT_PARAM : 0);
     if (s + 1 < len) {
@@ -1265,7 +1265,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
 #pragma unroll
     for (int p = 0; p < PMAX; ++p) {
       bad_par |= act && nx_par[p] < 1;
-      u[p] = act ? log2f((float)nx_par[p]) : 0.0f;
+      u[p] = act ? log2_of(nx_par[p]) : 0.0f;
     }
     errbits |= (bad_type ? ERRBIT_TYPE : 0) | (bad_par ? ERRBIT_PARAM : 0);
     if (s + 1 < len) {
@@ -1704,6 +1704,11 @@ struct NarrowF32 {
   }
 };
 
+// One 1 KiB weight group (16 bytes per lane) of a buffer.
+__device__ __forceinline__ u32x4 buf_group(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, int off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, off, 0);
+}
+
 template <class NP, int D, int E, int NC, int W>
 struct NarrowGeom {
   static constexpr int GPK = NP::GPK;
@@ -1714,16 +1719,66 @@ struct NarrowGeom {
   static constexpr int NI = NA + NC * NBW * GPK;           // groups per step
   static constexpr int W1G = NC * NK * 2 * GPK;            // W1 groups in the blob
   static constexpr int W2G = NC * NB * GPK;
-  static constexpr int ring_depth() {
-    for (int r = 12; r > 1; --r)
-      if (NI % r == 0) return r;
-    return 1;
-  }
-  static constexpr int RD = ring_depth();
   static_assert(NBW == 2 && NZ == W, "wavefront w owns z fragment w");
   static_assert(NC % W == 0 && NE <= W, "even split");
   static constexpr int G_BYTES = NC * GPK * 1024, X_BYTES = NK * GPK * 1024;
 };
+
+// Which of a wavefront's NI weight groups stay on the chip for the whole
+// sequence: R in registers and L in LDS, spread evenly over the stream of
+// groups, the others read from L2 every step.  What bounds a narrow bf16 step
+// at d = 256 is that stream: H = 512 is 576 KiB per workgroup and step, and
+// a compute unit takes 64 bytes per clock from L2 (9.2 k of the 11 k cycles
+// that a step took with every group streamed).
+template <int NI, int R, int L, int RD_MAX>
+struct GroupPlan {
+  enum Place : uint8_t { STREAM, REG, LDS };
+  static constexpr int NS = NI - R - L;                                 // streamed groups
+  static constexpr int NR = R + L > 0 ? R + L : 1;
+  // lookup tables, so that the unrolled stream indexes its registers with constants
+  struct Table {
+    uint8_t place[NI] = {}, slot[NI] = {};                              // of group i
+    uint8_t stream[NS] = {}, reg[R + 1] = {}, lds[L + 1] = {};          // group of a slot
+    constexpr Table() {
+      int ns = 0, nr = 0, nl = 0, k = 0;
+      for (int i = 0; i < NI; ++i) {
+        if ((i + 1) * (R + L) / NI == i * (R + L) / NI) {
+          place[i] = STREAM; slot[i] = ns; stream[ns++] = i;
+        } else if ((k + 1) * L / NR > k * L / NR) {
+          place[i] = LDS; slot[i] = nl; lds[nl++] = i; ++k;
+        } else {
+          place[i] = REG; slot[i] = nr; reg[nr++] = i; ++k;
+        }
+      }
+    }
+  };
+  static constexpr Table T{};
+  // register ring of streamed groups: its depth divides their number, so that
+  // every step finds slot q in ring entry q % RD
+  static constexpr int ring_depth() {
+    for (int r = RD_MAX; r > 1; --r)
+      if (NS % r == 0) return r;
+    return 1;
+  }
+  static constexpr int RD = ring_depth();
+  static_assert(NI < 256 && L % 2 == 0, "byte tables; two LDS groups are read ahead");
+};
+// Residents per kernel.  bf16 at d = 256: the LDS that the exchange buffers
+// leave (14 KiB of 160 / 8 per wavefront at H = 512, 12 KiB at H = 1024), and
+// the registers that a shorter ring (6 groups in flight instead of 12), operand
+// fragments and biases read from LDS and scalar load offsets free; the counts
+// leave a number of streamed groups that 6 divides.  Measured (us): ansor_round
+// rollout and scores 163 -> 113 (36 of 72 groups resident), long_schedule paper
+// form 737 -> 648 (30 of 144).  float32 is bound by its matrix products (36.9 k
+// of 44 k cycles a step) and keeps streaming; d = 64 streams little (all its
+// groups in registers: 1%).
+template <class NP, int D, int NC>
+struct NarrowResidents {
+  static constexpr bool ON = NP::GPK == 1 && D == 256;
+  static constexpr int LDS = ON ? (NC <= 16 ? 14 : 12) : 0;
+};
+template <bool NORM, int NC>
+constexpr int NARROW_REG = NC <= 16 ? (NORM ? 16 : 22) : 18;
 
 // TRAIN: the training forward of the rollout loss; stores, per valid step in
 // compact row off[i] + t, the operands X = [z; e], the pre-activations A,
@@ -1741,7 +1796,16 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
   using NG = NarrowGeom<NP, D, E, NC, W>;
   using XF = typename NP::XF;
   constexpr int GPK = NG::GPK, NK = NG::NK, NZ = NG::NZ, NE = NG::NE, NB = NG::NB, NBW = NG::NBW;
-  constexpr int NCW = NG::NCW, NA = NG::NA, NI = NG::NI, RD = NG::RD, NT = 64 * W;
+  constexpr int NCW = NG::NCW, NA = NG::NA, NI = NG::NI, NT = 64 * W;
+  using RES = NarrowResidents<NP, D, NC>;
+  constexpr int RREG = RES::ON ? NARROW_REG<NORM, NC> : 0;
+  using PL = GroupPlan<NI, RREG, RES::LDS, RES::ON ? 6 : 12>;
+  constexpr int RD = PL::RD;
+  constexpr auto PT = PL::T;
+  // operand fragments of X: read from LDS two ahead while they are used
+  // (RES::ON), or all held in registers through the first products
+  constexpr bool XLDS = RES::ON;
+  constexpr int XQ = 2;
 
   extern __shared__ __attribute__((aligned(16))) float tab[];
   const float* t_emb = tab;
@@ -1750,14 +1814,18 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
   uint8_t* gbuf = reinterpret_cast<uint8_t*>(tab) + a.tab_bytes;     // GELU fragments [NC]
   uint8_t* xbuf = gbuf + NG::G_BYTES;                                 // X fragments [NK]
   float* dots = reinterpret_cast<float*>(xbuf + NG::X_BYTES);         // paper form: [W][3][16]
-  float* phib = dots + (NORM ? W * 3 * 16 : 0);                       // [16][E + 1]
+  float* b1s = dots + (NORM ? W * 3 * 16 : 0);                        // b1 [NC * 32]
+  float* phib = b1s + NC * 32;                                        // [16][E + 1]
   const bool do_phi = !TRAIN && a.phi != nullptr;
+  // resident weight groups [W][RES::LDS] (after everything else, 16-byte aligned)
+  uint8_t* wlds = reinterpret_cast<uint8_t*>(tab) + a.lds_resident;
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int n = lane & 15, g = lane >> 4;
   constexpr int IN = D + E;
   stage_to_lds(reinterpret_cast<const uint8_t*>(a.tab), reinterpret_cast<uint8_t*>(tab),
                a.tab_bytes, tid, NT);
+  stage_to_lds(a.w1 + (size_t)(NG::W1G + NG::W2G) * 1024, reinterpret_cast<uint8_t*>(b1s), NC * 128, tid, NT);
   if (do_phi)
     for (int i = tid; i < 16 * (E + 1); i += NT) phib[i] = 0.0f;
 
@@ -1770,21 +1838,13 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
       clampi(a.lens[a.perm[blockIdx.x * 16].x], 0, a.T_max));
   const size_t row0 = (TRAIN && valid) ? (size_t)a.off[cand] : 0;
 
-  const float* b1n = reinterpret_cast<const float*>(a.w1 + (size_t)(NG::W1G + NG::W2G) * 1024);
-  const float* b2n = b1n + NC * 32;
-  // owned latent blocks 2w + bq, their b2, and the b1 of the own chunks
+  // owned latent blocks 2w + bq; b1 and b2 are read from LDS where they are
+  // added (rows 16 bq + 4 g .. of the 32-row block w in the table's order)
   const float* zs = a.z0 + (size_t)pc.y * D;
-  f32x4n zq[NBW], b2v[NBW], b1v[NCW][2];
+  const float* t_b2 = t_pb + E + (w * 2 + (g & 1)) * 16 + 4 * (g >> 1);
+  f32x4n zq[NBW];
 #pragma unroll
-  for (int bq = 0; bq < NBW; ++bq) {
-    zq[bq] = *reinterpret_cast<const f32x4n*>(zs + 16 * (w * NBW + bq) + 4 * g);
-    b2v[bq] = *reinterpret_cast<const f32x4n*>(b2n + 16 * (w * NBW + bq) + 4 * g);
-  }
-#pragma unroll
-  for (int cw = 0; cw < NCW; ++cw)
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-      b1v[cw][rb] = *reinterpret_cast<const f32x4n*>(b1n + 32 * (w + cw * W) + 16 * rb + 4 * g);
+  for (int bq = 0; bq < NBW; ++bq) zq[bq] = *reinterpret_cast<const f32x4n*>(zs + 16 * (w * NBW + bq) + 4 * g);
 
   const int32_t* ty_row = a.types + (size_t)cand * a.T_max;
   const int32_t* pa_row = a.params + (size_t)cand * a.T_max * a.P;
@@ -1811,7 +1871,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
 #pragma unroll
     for (int p = 0; p < PMAX; ++p) {
       bad_par |= act && nx_par[p] < 1;
-      u[p] = act ? log2f((float)nx_par[p]) : 0.0f;
+      u[p] = act ? log2_of(nx_par[p]) : 0.0f;
     }
     errbits |= (bad_type ? ERRBIT_TYPE : 0) | (bad_par ? ERRBIT_PARAM : 0);
     if (s + 1 < len) {
@@ -1859,8 +1919,18 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
   };
   // publish z fragment w (blocks 2w, 2w+1), read back all of X (paper
   // form: every wavefront holds the embedding fragments itself)
-  XF xf[NK];
+  XF xf[XLDS ? XQ : NK];
   XF xe[NORM ? NE : 1];
+  // fragment kf of X; with XLDS it is read into the queue entry q % XQ
+  auto x_load = [&](int q) {
+    const int kf = q % NK;
+    if (!(NORM && kf >= NZ)) xf[q % XQ] = NP::load(xbuf, kf, lane);
+  };
+  auto x_frag = [&](int q) -> XF {
+    const int kf = q % NK;
+    if (NORM && kf >= NZ) return xe[NORM ? (kf >= NZ ? kf - NZ : 0) : 0];
+    return xf[XLDS ? q % XQ : kf];
+  };
   auto exchange_x = [&]() {
     float v[8];
 #pragma unroll
@@ -1870,10 +1940,13 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
     }
     NP::store(xbuf, w, lane, NP::cvt(v));
     __syncthreads();
+    if constexpr (XLDS) {
 #pragma unroll
-    for (int kf = 0; kf < NK; ++kf) {
-      if (NORM && kf >= NZ) xf[kf] = xe[NORM ? kf - NZ : 0];
-      else xf[kf] = NP::load(xbuf, kf, lane);
+      for (int q = 0; q < XQ; ++q) x_load(q);
+    } else {
+#pragma unroll
+      for (int kf = 0; kf < NK; ++kf)
+        if (!(NORM && kf >= NZ)) xf[XLDS ? 0 : kf] = NP::load(xbuf, kf, lane);
     }
   };
   // Paper form (Sec. 3.4): at a step boundary the finished step's u is
@@ -1980,16 +2053,29 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
     const int c = j / (NBW * GPK), r = j % (NBW * GPK);
     return ((size_t)c * NB * GPK + r) * 1024;
   };
-  gu8* baseA = ((gu8*)(a.w1)) + (size_t)(w * NK * 2 * GPK) * 1024 + lane * 16;
-  gu8* baseB = ((gu8*)(a.w1)) + (size_t)(NG::W1G + w * NBW * GPK) * 1024 + lane * 16;
-  auto item_ptr = [&](gu8* pA, gu8* pB, int i) -> gu32x4* {
-    return reinterpret_cast<gu32x4*>((i < NA ? pA : pB) + item_off(i));
-  };
+  // Groups are buffer loads with the item's offset in a scalar register and
+  // one lane offset per base: a 64-bit address per load would take vector
+  // registers and two vector additions each.
+  const __amdgpu_buffer_rsrc_t wbuf =
+      __builtin_amdgcn_make_buffer_rsrc((void*)a.w1, (short)0, (NG::W1G + NG::W2G) * 1024, 0x00020000);
+  const uint32_t voA = (uint32_t)(w * NK * 2 * GPK) * 1024 + lane * 16;
+  const uint32_t voB = (uint32_t)(NG::W1G + w * NBW * GPK) * 1024 + lane * 16;
+  auto item_load = [&](int i) -> u32x4 { return buf_group(wbuf, i < NA ? voA : voB, (int)item_off(i)); };
+  // resident groups, then the first streamed ones
+  u32x4 wreg[RREG > 0 ? RREG : 1], wl[2];
+  uint8_t* wl_base = wlds + (size_t)w * RES::LDS * 1024;
+#pragma unroll
+  for (int l = 0; l < RES::LDS; ++l)
+    *reinterpret_cast<u32x4*>(wl_base + l * 1024 + lane * 16) = item_load(PT.lds[l]);
+#pragma unroll
+  for (int r = 0; r < RREG; ++r) wreg[r] = item_load(PT.reg[r]);
   u32x4 ring[RD];
 #pragma unroll
-  for (int i = 0; i < RD; ++i) ring[i] = *item_ptr(baseA, baseB, i);
+  for (int i = 0; i < RD; ++i) ring[i] = item_load(PT.stream[i]);
 
   wait_vm_then_barrier();
+#pragma unroll
+  for (int l = 0; l < 2 && l < RES::LDS; ++l) wl[l] = lds_group(wl_base, l, lane);
   if constexpr (NORM) {
     embed_all(0);
     boundary(false, 0 < len, -1);
@@ -2002,9 +2088,6 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
     const bool active = t < len;
     const float actf = active ? 1.0f : 0.0f;
     const uint32_t amask = active ? 0xFFFFFFFFu : 0u;
-    gu8* pA = baseA;
-    gu8* pB = baseB;
-    asm volatile("" : "+v"(pA), "+v"(pB));
     const size_t row = row0 + t;
     if constexpr (TRAIN) {
       if (active) {                  // X = [z; e]: the owned latent blocks (e: embed_share)
@@ -2045,8 +2128,18 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const u32x4 grp = ring[i % RD];
-      ring[i % RD] = *item_ptr(pA, pB, (i + RD) % NI);   // wraps into the next step
+      u32x4 grp;
+      const int q = PT.slot[i];
+      if (PT.place[i] == PL::REG) {
+        grp = wreg[PT.place[i] == PL::REG ? q : 0];
+      } else if (PT.place[i] == PL::LDS) {
+        const int l = q;
+        grp = wl[l & 1];
+        wl[l & 1] = lds_group(wl_base, (l + 2) % (RES::LDS > 0 ? RES::LDS : 1), lane);
+      } else {
+        grp = ring[q % RD];
+        ring[q % RD] = item_load(PT.stream[(q + RD) % PL::NS]);   // wraps into the next step
+      }
       if (i < NA) {
         const int cw = i / (NK * 2 * GPK), kf = (i / (2 * GPK)) % NK;
         const int rb = (i / GPK) % 2, hh = i % GPK;
@@ -2056,11 +2149,17 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
           gvp[r_in] = gelu(pend[r_in]);
           if (r_in == 7) finish_chunk(cw - 1, gvp);
         }
-        acc[rb] = NP::mma(grp, hh, xf[kf], acc[rb]);
+        const int xq = cw * NK + kf;
+        acc[rb] = NP::mma(grp, hh, x_frag(xq), acc[rb]);
+        if (XLDS && rb == 1 && hh == GPK - 1 && xq + XQ < NCW * NK) x_load(xq + XQ);
         if (kf == NK - 1 && rb == 1 && hh == GPK - 1) {
           float av8[8];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) av8[j] = acc[j >> 2][j & 3] + b1v[cw][j >> 2][j & 3];
+          for (int rb2 = 0; rb2 < 2; ++rb2) {
+            const f32x4n b1 = *reinterpret_cast<const f32x4n*>(b1s + 32 * (w + cw * W) + 16 * rb2 + 4 * g);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) av8[4 * rb2 + j] = acc[rb2][j] + b1[j];
+          }
           if constexpr (TRAIN) {
             if (active) {
               const int c = w + cw * W;
@@ -2101,7 +2200,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
 #pragma unroll
     for (int bq = 0; bq < NBW; ++bq) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) zq[bq][r] += dz[bq][r] + b2v[bq][r] * actf;
+      for (int r = 0; r < 4; ++r) zq[bq][r] += dz[bq][r] + t_b2[8 * bq + r] * actf;
       if constexpr (TRAIN && !NORM) {
         if (active) *reinterpret_cast<f32x4n*>(a.Pz + row * D + 16 * (w * NBW + bq) + 4 * g) = zq[bq];
       }
@@ -2128,7 +2227,9 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
     constexpr int NHF = 1;                           // hw fragments (hw_dim <= 32)
     const int NH = a.HW / 32, NCC = a.C / 32, NKC = NZ + NE + NH;
     const float inv = len > 0 ? 1.0f / (float)len : 0.0f;
-    XF pf[NE];
+    XF xs[NZ], pf[NE];
+#pragma unroll
+    for (int kf = 0; kf < NZ; ++kf) xs[kf] = XLDS ? NP::load(xbuf, kf, lane) : xf[XLDS ? 0 : kf];
 #pragma unroll
     for (int q = 0; q < NE; ++q) {
       float v[8];
@@ -2162,7 +2263,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
         for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
           for (int hh = 0; hh < GPK; ++hh)
-            acc2[rb] = NP::mma(grp_at(kf, rb, hh), hh, kf < NZ ? xf[kf < NZ ? kf : 0] : pf[kf < NZ ? 0 : kf - NZ], acc2[rb]);
+            acc2[rb] = NP::mma(grp_at(kf, rb, hh), hh, kf < NZ ? xs[kf < NZ ? kf : 0] : pf[kf < NZ ? 0 : kf - NZ], acc2[rb]);
       f32x4n b4[2], w4[2];
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) {
@@ -2190,7 +2291,8 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
       }
     }
     // the candidate's four lane groups, then the wavefronts in order
-    float* red = dots + (NORM ? W * 3 * 16 : 0) + 16 * (E + 1);          // [W][NARROW_SCORE_HW][16]
+    // (the last step's GELU fragments have been read)
+    float* red = reinterpret_cast<float*>(gbuf);                         // [W][NARROW_SCORE_HW][16]
 #pragma unroll
     for (int jj = 0; jj < NARROW_SCORE_HW; ++jj) {
       float v = part[jj];
@@ -3360,19 +3462,22 @@ struct NarrowBwdGeom {
   static constexpr int NA = NCW * NP1;
   static constexpr int NI = NA + NC * NBW * GPK;
   static constexpr int W2TG = NC * NZ * 2 * GPK;           // W2^T groups in the blob
-  static constexpr int ring_depth() {
-    for (int r = 12; r > 1; --r)
-      if (NI % r == 0) return r;
-    return 1;
-  }
-  static constexpr int RD = ring_depth();
+  static constexpr int W1TG = NC * IB * GPK;               // W1^T groups
   static_assert(NBW == 2 && NZ == W && NC % W == 0 && NBE <= W, "narrow split");
   // LDS: [dA fragments: NC][delta fragments: NZ][dE partials: W x NBE x 64 lanes x 4]
   static constexpr int DA_BYTES = NC * GPK * 1024, DL_BYTES = NZ * GPK * 1024;
   static constexpr int DE_BYTES = W * NBE * 64 * 16;
   static constexpr int LDS = DA_BYTES + DL_BYTES + DE_BYTES;
   static constexpr int DOTS_BYTES = 2 * W * 16 * 4;        // paper form: two dot products
+  // resident weight groups, as in the forward (GroupPlan): the LDS left beside
+  // the buffers (H = 512: 12 KiB of 160 / 8 per wavefront, H = 1024: 10) and
+  // registers; ansor_round backward 254 -> 191 us, long_schedule paper form
+  // 1367 -> 1279 us
+  static constexpr bool RES = GPK == 1 && D == 256;
+  static constexpr int RLDS = RES ? (NC <= 16 ? 12 : 10) : 0;
 };
+template <bool NORM, int NC>
+constexpr int NARROW_BWD_REG = NC <= 16 ? (NORM ? 24 : 30) : (NORM ? 20 : 26);
 
 // NORM (paper form, as the one-wavefront kernel): du through the
 // normalisation at the start of a step, and dz, dv through the projection
@@ -3384,7 +3489,13 @@ __global__ __launch_bounds__(64 * W, 1) void train_bwd_narrow_kernel(const Train
   using BG = NarrowBwdGeom<NP, D, E, NC, W>;
   using XF = typename NP::XF;
   constexpr int GPK = BG::GPK, NZ = BG::NZ, NBE = BG::NBE, IB = BG::IB, NBW = BG::NBW, NB = BG::NB;
-  constexpr int NCW = BG::NCW, N2T = BG::N2T, NP1 = BG::NP1, NA = BG::NA, NI = BG::NI, RD = BG::RD;
+  constexpr int NCW = BG::NCW, N2T = BG::N2T, NP1 = BG::NP1, NA = BG::NA, NI = BG::NI;
+  constexpr int RREG = BG::RES ? NARROW_BWD_REG<NORM, NC> : 0, RLDS = BG::RLDS;
+  using PL = GroupPlan<NI, RREG, RLDS, BG::RES ? 6 : 12>;
+  constexpr int RD = PL::RD;
+  constexpr auto PT = PL::T;
+  constexpr bool XLDS = BG::RES;    // delta fragments read from LDS as they are used
+  constexpr int XQ = 2;
   (void)NB;
 
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -3405,21 +3516,33 @@ __global__ __launch_bounds__(64 * W, 1) void train_bwd_narrow_kernel(const Train
   const size_t row0 = valid ? (size_t)a.off[cand] : 0;
 
   // item i -> weight group (compile-time offsets from three bases)
-  gu8* baseA2 = ((gu8*)(a.w2t)) + (size_t)(w * N2T) * 1024 + lane * 16;
-  gu8* baseA1 = ((gu8*)(a.w2t)) + (size_t)(BG::W2TG + (w * IB + NZ * 2) * GPK) * 1024 + lane * 16;
-  gu8* baseB = ((gu8*)(a.w2t)) + (size_t)(BG::W2TG + w * NBW * GPK) * 1024 + lane * 16;
-  auto item_ptr = [&](gu8* p2, gu8* p1, gu8* pb, int i) -> gu32x4* {
+  const __amdgpu_buffer_rsrc_t wbuf =
+      __builtin_amdgcn_make_buffer_rsrc((void*)a.w2t, (short)0, (BG::W2TG + BG::W1TG) * 1024, 0x00020000);
+  const uint32_t voA2 = (uint32_t)(w * N2T) * 1024 + lane * 16;
+  const uint32_t voA1 = (uint32_t)(BG::W2TG + (w * IB + NZ * 2) * GPK) * 1024 + lane * 16;
+  const uint32_t voB = (uint32_t)(BG::W2TG + w * NBW * GPK) * 1024 + lane * 16;
+  auto item_load = [&](int i) -> u32x4 {
     if (i < NA) {
       const int cw = i / NP1, k = i % NP1;
-      if (k < N2T) return reinterpret_cast<gu32x4*>(p2 + ((size_t)cw * W * N2T + k) * 1024);
-      return reinterpret_cast<gu32x4*>(p1 + ((size_t)cw * W * IB * GPK + (k - N2T)) * 1024);
+      if (k < N2T) return buf_group(wbuf, voA2, (cw * W * N2T + k) * 1024);
+      return buf_group(wbuf, voA1, (cw * W * IB * GPK + (k - N2T)) * 1024);
     }
     const int j = i - NA, c = j / (NBW * GPK), r = j % (NBW * GPK);
-    return reinterpret_cast<gu32x4*>(pb + ((size_t)c * IB * GPK + r) * 1024);
+    return buf_group(wbuf, voB, (c * IB * GPK + r) * 1024);
   };
+  // resident groups, then the first streamed ones
+  u32x4 wreg[RREG > 0 ? RREG : 1], wl[2];
+  uint8_t* wl_base = lds + BG::LDS + (NORM ? BG::DOTS_BYTES : 0) + (size_t)w * RLDS * 1024;
+#pragma unroll
+  for (int l = 0; l < RLDS; ++l) *reinterpret_cast<u32x4*>(wl_base + l * 1024 + lane * 16) = item_load(PT.lds[l]);
+#pragma unroll
+  for (int r = 0; r < RREG; ++r) wreg[r] = item_load(PT.reg[r]);
   u32x4 ring[RD];
 #pragma unroll
-  for (int i = 0; i < RD; ++i) ring[i] = *item_ptr(baseA2, baseA1, baseB, i);
+  for (int i = 0; i < RD; ++i) ring[i] = item_load(PT.stream[i]);
+  // (a wavefront reads only the resident groups that it wrote itself)
+#pragma unroll
+  for (int l = 0; l < 2 && l < RLDS; ++l) wl[l] = lds_group(wl_base, l, lane);
 
   f32x4n dq[NBW];
 #pragma unroll
@@ -3430,10 +3553,6 @@ __global__ __launch_bounds__(64 * W, 1) void train_bwd_narrow_kernel(const Train
     const float actf = active ? 1.0f : 0.0f;
     const uint32_t amask = active ? 0xFFFFFFFFu : 0u;
     const size_t row = row0 + t;
-    gu8* p2 = baseA2;
-    gu8* p1 = baseA1;
-    gu8* pb = baseB;
-    asm volatile("" : "+v"(p2), "+v"(p1), "+v"(pb));
     // ---- owned delta blocks: seed, delta_{t+1} (paper form: du through the
     // normalisation, du = (delta - (delta . z) z) / |u| with z the unit
     // prediction), operand fragment w in LDS
@@ -3483,9 +3602,9 @@ __global__ __launch_bounds__(64 * W, 1) void train_bwd_narrow_kernel(const Train
         av[cw][rb] = active ? *reinterpret_cast<const f32x4n*>(a.A + row * a.H + 32 * (w + cw * W) + 16 * rb + 4 * g)
                             : f32x4n{};
     __syncthreads();
-    XF dop[NZ];
+    XF dop[XLDS ? XQ : NZ];
 #pragma unroll
-    for (int kf = 0; kf < NZ; ++kf) dop[kf] = NP::load(dlbuf, kf, lane);
+    for (int kf = 0; kf < (XLDS ? XQ : NZ); ++kf) dop[kf] = NP::load(dlbuf, kf, lane);
 
     f32x4n acc[2], deacc[NBE];
     acc[0] = f32x4n{}; acc[1] = f32x4n{};
@@ -3496,13 +3615,25 @@ __global__ __launch_bounds__(64 * W, 1) void train_bwd_narrow_kernel(const Train
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const u32x4 grp = ring[i % RD];
-      ring[i % RD] = *item_ptr(p2, p1, pb, (i + RD) % NI);   // wraps into the next step
+      u32x4 grp;
+      const int slot = PT.slot[i];
+      if (PT.place[i] == PL::REG) {
+        grp = wreg[PT.place[i] == PL::REG ? slot : 0];
+      } else if (PT.place[i] == PL::LDS) {
+        grp = wl[slot & 1];
+        wl[slot & 1] = lds_group(wl_base, (slot + 2) % (RLDS > 0 ? RLDS : 1), lane);
+      } else {
+        grp = ring[slot % RD];
+        ring[slot % RD] = item_load(PT.stream[(slot + RD) % PL::NS]);   // wraps into the next step
+      }
       if (i < NA) {
         const int cw = i / NP1, k = i % NP1;
         if (k < N2T) {
           const int kf = k / (2 * GPK), rb = (k / GPK) % 2, hh = k % GPK;
-          acc[rb] = NP::mma(grp, hh, dop[kf], acc[rb]);
+          const int xq = cw * NZ + kf;
+          acc[rb] = NP::mma(grp, hh, dop[XLDS ? xq % XQ : kf], acc[rb]);
+          if (XLDS && rb == 1 && hh == GPK - 1 && xq + XQ < NCW * NZ)
+            dop[xq % XQ] = NP::load(dlbuf, (xq + XQ) % NZ, lane);
           if (k == N2T - 1) {
             const int c = w + cw * W;
             float da[8];
@@ -4487,8 +4618,10 @@ template <class NP, int NC, bool NORM, bool TRAIN = false, bool SCORE = false, i
 hipError_t launch_rollout_narrow(const DevModel& m, RollArgs a, int tiles, hipStream_t st) {
   using NG = NarrowGeom<NP, D, E, NC, W>;
   a.w1 = m.trans_n;
-  const int lds = m.roll_tab_bytes + NG::G_BYTES + NG::X_BYTES + (NORM ? W * 3 * 16 * 4 : 0) +
-                  (a.phi && !TRAIN ? 16 * (E + 1) * 4 : 0) + (SCORE ? W * NARROW_SCORE_HW * 16 * 4 : 0);
+  static_assert(!SCORE || W * NARROW_SCORE_HW * 16 * 4 <= NG::G_BYTES, "partial scores in the GELU buffer");
+  a.lds_resident = (m.roll_tab_bytes + NG::G_BYTES + NG::X_BYTES + (NORM ? W * 3 * 16 * 4 : 0) + NC * 128 +
+                    (a.phi && !TRAIN ? 16 * (E + 1) * 4 : 0) + 15) & ~15;
+  const int lds = a.lds_resident + W * NarrowResidents<NP, D, NC>::LDS * 1024;
   auto kern = rollout_narrow_kernel<NP, D, E, NC, W, NORM, TRAIN, SCORE>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) {
@@ -4811,7 +4944,7 @@ hipError_t launch_train_fwd(const DevModel& m, const TrainIO& io, hipStream_t st
 template <class NP, int NC, bool NORM, int D = 256, int E = 64, int W = 8>
 hipError_t launch_train_bwd_narrow(const DevModel& m, TrainArgs a, int tiles, hipStream_t st) {
   using BG = NarrowBwdGeom<NP, D, E, NC, W>;
-  constexpr int lds = BG::LDS + (NORM ? BG::DOTS_BYTES : 0);
+  constexpr int lds = BG::LDS + (NORM ? BG::DOTS_BYTES : 0) + W * BG::RLDS * 1024;
   static_assert(lds <= 160 * 1024, "LDS");
   a.w2t = m.trans_nt;
   // paper form: the transposed normal map follows W1^T in the blob
