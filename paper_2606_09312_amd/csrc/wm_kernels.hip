@@ -2333,64 +2333,106 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
-__device__ __forceinline__ float group16_sum(float x) {
-  // butterfly over the 16 lanes of a group (xor 1, 2, 4, 8 stays inside it)
+// Per-candidate sums over an action sequence, shared by both kinds of action
+// features: a workgroup of 256 threads takes 256 / NL candidates, NL lanes
+// each, lane q the steps q, q + NL, ...; kinds are counted in LDS (one atomic
+// per step), the log2-parameter sums (and maxima) stay in registers and are
+// completed over the NL lanes.  Row c of `cnt` holds candidate c's K counts.
+// NL = 4 keeps a large batch's loads dense; below FEAT_WIDE_BATCH candidates the
+// kernel is as long as one lane's chain of loads, and NL = 16 shortens it.
+constexpr int FEAT_THREADS = 256, FEAT_CNT = 33;              // row stride of the counts
+constexpr int FEAT_WIDE_BATCH = 16384;
+
+template <int NL, bool CLAMP, bool MAX>
+__device__ __forceinline__ void action_sums(const int32_t* types, const int32_t* params, const int32_t* lens,
+                                            int B, int T_max, int K, int P, int* cnt, float (&us)[PMAX],
+                                            float (&um)[PMAX], int& len) {
+  constexpr int CPB = FEAT_THREADS / NL;
+  const int tid = threadIdx.x, c = tid / NL, q = tid % NL;
+  const int i = blockIdx.x * CPB + c;
+  for (int u = tid; u < CPB * FEAT_CNT; u += FEAT_THREADS) cnt[u] = 0;
+  __syncthreads();
+  len = i < B ? clampi(lens[i], 0, T_max) : 0;
+  const int32_t* ty_row = types + (size_t)(i < B ? i : 0) * T_max;
+  const int32_t* pa_row = params + (size_t)(i < B ? i : 0) * T_max * P;
 #pragma unroll
-  for (int m = 8; m >= 1; m >>= 1) x += __shfl_xor(x, m);
-  return x;
+  for (int p = 0; p < PMAX; ++p) { us[p] = 0.0f; um[p] = -INFINITY; }
+#pragma unroll 2
+  for (int t = q; t < len; t += NL) {
+    const int ty = ty_row[t];
+    float u[PMAX];
+#pragma unroll
+    for (int p = 0; p < PMAX; ++p)
+      if (p < P) u[p] = log2_of(pa_row[(size_t)t * P + p]);
+    // kinds outside [0, K): clamped (mean embedding) or not counted
+    if (CLAMP || (ty >= 0 && ty < K)) atomicAdd(&cnt[c * FEAT_CNT + clampi(ty, 0, K - 1)], 1);
+#pragma unroll
+    for (int p = 0; p < PMAX; ++p)
+      if (p < P) {
+        us[p] += u[p];
+        if (MAX) um[p] = fmaxf(um[p], u[p]);
+      }
+  }
+#pragma unroll
+  for (int p = 0; p < PMAX; ++p)
+    if (p < P) {
+#pragma unroll
+      for (int m = 1; m < NL; m <<= 1) {
+        us[p] += __shfl_xor(us[p], m);
+        if (MAX) um[p] = fmaxf(um[p], __shfl_xor(um[p], m));
+      }
+    }
+  __syncthreads();
 }
 
-// a4 where the rollout kernel does not sum phi itself: 16 lanes per candidate
-// (four candidates per wavefront), lane s taking steps s, s + 16, ...; the
-// kind counts and log2-parameter sums are reduced over the candidate's 16
-// lanes, then lane s forms features s, s + 16, ... of the regrouped mean
-// (0 for an empty sequence).
-__global__ __launch_bounds__(256) void phi_kernel(const float* __restrict__ emb,
+// a4 where the rollout kernel does not sum phi itself.  After the sums, each
+// thread holds one feature's column of the embedding tables (K + P weights) in
+// registers and forms it for every fourth, second, ... of the workgroup's
+// candidates (the counts and log2 sums are LDS broadcasts), instead of loading
+// the tables again per candidate: 65,536 candidates of 8 to 48 steps, E = 128:
+// 95 -> 60 us.
+template <int E, int NL>
+__global__ __launch_bounds__(FEAT_THREADS) void phi_kernel(const float* __restrict__ emb,
                                                    const int32_t* __restrict__ types,
                                                    const int32_t* __restrict__ params,
                                                    const int32_t* __restrict__ lens, int B,
-                                                   int T_max, int E, int P, int K,
+                                                   int T_max, int P, int K,
                                                    float* __restrict__ phi) {
-  const int lane = threadIdx.x & 63, s = lane & 15;
-  const int i = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 4 + (lane >> 4);
-  const bool valid = i < B;
-  const float* t_emb = emb;
+  constexpr int NT = FEAT_THREADS, CPB = NT / NL;
+  static_assert(NT % E == 0, "one feature per thread");
+  __shared__ int cnt[CPB * FEAT_CNT];
+  __shared__ __attribute__((aligned(16))) float sums[CPB * PMAX];
+  __shared__ int lens_s[CPB];
   const float* t_pw = emb + K * temb_stride(E);        // [PMAX][E], zero rows past P
   const float* t_pb = t_pw + PMAX * E;
-  const int len = valid ? clampi(lens[i], 0, T_max) : 0;
-  float cnt[32];                                       // n_k, K <= 32 (exact in float)
+  const int tid = threadIdx.x;
+  float us[PMAX], um[PMAX];
+  int len;
+  action_sums<NL, true, false>(types, params, lens, B, T_max, K, P, cnt, us, um, len);
+  if (tid % NL == 0) {
 #pragma unroll
-  for (int k = 0; k < 32; ++k) cnt[k] = 0.0f;
-  float us[PMAX];                                      // sums of log2(params)
-#pragma unroll
-  for (int p = 0; p < PMAX; ++p) us[p] = 0.0f;
-  const int32_t* ty_row = types + (size_t)(valid ? i : 0) * T_max;
-  const int32_t* pa_row = params + (size_t)(valid ? i : 0) * T_max * P;
-  for (int t = s; t < len; t += 16) {
-    const int ty = clampi(ty_row[t], 0, K - 1);
-#pragma unroll
-    for (int k = 0; k < 32; ++k)
-      if (k < K) cnt[k] += ty == k ? 1.0f : 0.0f;
-#pragma unroll
-    for (int p = 0; p < PMAX; ++p)
-      if (p < P) us[p] += log2f((float)pa_row[(size_t)t * P + p]);
+    for (int p = 0; p < PMAX; ++p) sums[(tid / NL) * PMAX + p] = us[p];
+    lens_s[tid / NL] = len;
   }
-  // every lane takes part in the reductions (invalid groups sum zeros)
+  const int f = tid % E;
+  float wt[32], wp[PMAX];
 #pragma unroll
-  for (int k = 0; k < 32; ++k)
-    if (k < K) cnt[k] = group16_sum(cnt[k]);
+  for (int k = 0; k < 32; ++k) wt[k] = k < K ? emb[k * temb_stride(E) + f] : 0.0f;
 #pragma unroll
-  for (int p = 0; p < PMAX; ++p) us[p] = p < P ? group16_sum(us[p]) : 0.0f;
-  if (!valid) return;
-  const float inv = len > 0 ? 1.0f / (float)len : 0.0f;
-  for (int f = s; f < E; f += 16) {
+  for (int p = 0; p < PMAX; ++p) wp[p] = t_pw[p * E + f];
+  const float pb = t_pb[f];
+  __syncthreads();
+  const int i0 = blockIdx.x * CPB, nc = min(CPB, B - i0);
+  for (int c = tid / E; c < nc; c += NT / E) {
+    const int L = lens_s[c];
+    const float inv = L > 0 ? 1.0f / (float)L : 0.0f;
     float acc = 0.0f;
 #pragma unroll
     for (int k = 0; k < 32; ++k)
-      if (k < K) acc = fmaf(cnt[k], t_emb[k * temb_stride(E) + f], acc);
+      if (k < K) acc = fmaf((float)cnt[c * FEAT_CNT + k], wt[k], acc);
 #pragma unroll
-    for (int p = 0; p < PMAX; ++p) acc = fmaf(us[p], t_pw[p * E + f], acc);
-    phi[(size_t)i * E + f] = len > 0 ? fmaf(acc, inv, t_pb[f]) : 0.0f;
+    for (int p = 0; p < PMAX; ++p) acc = fmaf(sums[c * PMAX + p], wp[p], acc);
+    phi[(size_t)(i0 + c) * E + f] = L > 0 ? fmaf(acc, inv, pb) : 0.0f;
   }
 }
 
@@ -2398,64 +2440,40 @@ __global__ __launch_bounds__(256) void phi_kernel(const float* __restrict__ emb,
 // Structured action features (the ranker's phi, Sec. 3.5): per candidate the
 // number of steps of each kind, the length, and per parameter slot the mean
 // and the maximum of log2(param) over the steps (all zero when the sequence
-// is empty).  One wavefront per candidate, lanes over steps; kinds outside
-// [0, K) are not counted.
+// is empty); kinds outside [0, K) are not counted.  The workgroup's rows are
+// one contiguous range of the output and are stored from LDS: 65,536
+// candidates: 69 -> 39 us (one wavefront per candidate, ballots per kind).
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) x = fmaxf(x, __shfl_xor(x, m));
-  return x;
-}
-
-__global__ __launch_bounds__(256) void phi_struct_kernel(const int32_t* __restrict__ types,
+template <int NL>
+__global__ __launch_bounds__(FEAT_THREADS) void phi_struct_kernel(const int32_t* __restrict__ types,
                                                           const int32_t* __restrict__ params,
                                                           const int32_t* __restrict__ lens, int B,
                                                           int T_max, int K, int P,
                                                           float* __restrict__ phi_s) {
-  const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (i >= B) return;                                  // whole wavefront leaves together
-  const int len = clampi(lens[i], 0, T_max);
-  const int32_t* ty_row = types + (size_t)i * T_max;
-  const int32_t* pa_row = params + (size_t)i * T_max * P;
-  int cnt[32];
-#pragma unroll
-  for (int k = 0; k < 32; ++k) cnt[k] = 0;
+  constexpr int CPB = FEAT_THREADS / NL;
+  __shared__ int cnt[CPB * FEAT_CNT];
+  __shared__ float stat[CPB * (2 * PMAX + 1)];    // length, means, maxima
+  const int tid = threadIdx.x, c = tid / NL, q = tid % NL;
   float us[PMAX], um[PMAX];
-#pragma unroll
-  for (int p = 0; p < PMAX; ++p) { us[p] = 0.0f; um[p] = -INFINITY; }
-  for (int t0 = 0; t0 < len; t0 += 64) {
-    const int t = t0 + lane;
-    const bool v = t < len;
-    const int ty = v ? ty_row[t] : -1;
+  int len;
+  action_sums<NL, false, true>(types, params, lens, B, T_max, K, P, cnt, us, um, len);
+  const int W = phi_struct_dim(K, P);
+  if (q == 0) {
+    const float inv = len > 0 ? 1.0f / (float)len : 0.0f;
+    float* st = stat + c * (2 * PMAX + 1);
+    st[0] = (float)len;
 #pragma unroll
     for (int p = 0; p < PMAX; ++p)
-      if (p < P && v) {
-        const float u = log2f((float)pa_row[(size_t)t * P + p]);
-        us[p] += u;
-        um[p] = fmaxf(um[p], u);
+      if (p < P) {
+        st[1 + p] = len > 0 ? us[p] * inv : 0.0f;
+        st[1 + P + p] = len > 0 ? um[p] : 0.0f;
       }
-#pragma unroll
-    for (int k = 0; k < 32; ++k)
-      if (k < K) cnt[k] += __popcll(__ballot(ty == k));
   }
-  float* o = phi_s + (size_t)i * phi_struct_dim(K, P);
-  const float inv = len > 0 ? 1.0f / (float)len : 0.0f;
-#pragma unroll
-  for (int p = 0; p < PMAX; ++p) {
-    if (p >= P) break;
-    const float s = wave_sum(us[p]);
-    const float m = wave_max(um[p]);
-    if (lane == 0) {
-      o[K + 1 + p] = len > 0 ? s * inv : 0.0f;
-      o[K + 1 + P + p] = len > 0 ? m : 0.0f;
-    }
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < 32; ++k)
-      if (k < K) o[k] = (float)cnt[k];
-    o[K] = (float)len;
+  __syncthreads();
+  const int i0 = blockIdx.x * CPB, nc = min(CPB, B - i0);
+  for (int u = tid; u < nc * W; u += FEAT_THREADS) {
+    const int r = u / W, f = u - r * W;
+    phi_s[(size_t)i0 * W + u] = f < K ? (float)cnt[r * FEAT_CNT + f] : stat[r * (2 * PMAX + 1) + f - K];
   }
 }
 
@@ -2522,6 +2540,121 @@ __global__ __launch_bounds__(TREE_THREADS) void score_trees_kernel(
 #pragma unroll
     for (int w = 0; w < TREE_THREADS / 64; ++w) y += red[w * TREE_CPB + tid];
     scores[(size_t)j * B + i0 + tid] = y;
+  }
+}
+
+// The same ensemble with lanes over candidates: a workgroup of 16 wavefronts
+// takes 64 candidates and up to two hardware vectors; x lies in LDS feature by
+// feature (64 candidates each, the hardware vectors as columns of their own),
+// so a lane reads its value from its own bank whatever feature its node asks
+// for.  Wavefront w walks trees w, w + 16, ..., TREEW_TREES at a time for
+// latency: all lanes of a wavefront are in one tree, whose first levels are
+// one or a few cache lines.  With a tree per lane every node read touched 64
+// lines, which bounded the kernel (one line per clock per compute unit):
+// 65,536 candidates, 2 vectors, 256 trees of depth 8, 573 features: 486 ->
+// 162 us.  Leaves are summed in a fixed order, pairwise over four trees
+// and over the wavefronts (8e-8 from float64 at 256 trees).
+constexpr int TREEW_CPB = 64, TREEW_WAVES = 16, TREEW_TREES = 4;
+constexpr int TREEW_COLUMNS = 640;                     // 64 floats each: 160 KiB of LDS
+constexpr int TREEW_MIN_BATCH = 8192;
+
+template <int NHW>
+__global__ __launch_bounds__(64 * TREEW_WAVES) void score_trees_wide_kernel(
+    const int2* __restrict__ nodes, const float* __restrict__ leaves, int NT, int depth, float base,
+    const float* __restrict__ zT, int d, const float* __restrict__ phi_s, int phi_dim,
+    const float* __restrict__ hw, int hw_dim, int B, float* __restrict__ scores) {
+  extern __shared__ __attribute__((aligned(16))) float tsm[];
+  const int Fx = d + phi_dim;                          // features that differ by candidate
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i0 = blockIdx.x * TREEW_CPB, nc = min(TREEW_CPB, B - i0);
+  // rows past the batch repeat the first
+  const float* zrow = zT + (size_t)(i0 + (lane < nc ? lane : 0)) * d;
+  const float* prow = phi_s + (size_t)(i0 + (lane < nc ? lane : 0)) * phi_dim;
+  if ((d & 3) == 0 && ((uintptr_t)zT & 15) == 0) {
+#pragma unroll 4
+    for (int f = 4 * w; f < d; f += 4 * TREEW_WAVES) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(zrow + f);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) tsm[(f + q) * 64 + lane] = v[q];
+    }
+  } else {
+    for (int f = w; f < d; f += TREEW_WAVES) tsm[f * 64 + lane] = zrow[f];
+  }
+  for (int f = w; f < phi_dim; f += TREEW_WAVES) tsm[(d + f) * 64 + lane] = prow[f];
+  for (int f = w; f < NHW * hw_dim; f += TREEW_WAVES) tsm[(Fx + f) * 64 + lane] = hw[f];
+  __syncthreads();
+  const int n_int = (1 << depth) - 1;
+  float acc[NHW];
+#pragma unroll
+  for (int j = 0; j < NHW; ++j) acc[j] = 0.0f;
+  for (int t0 = w; t0 < NT; t0 += TREEW_WAVES * TREEW_TREES) {
+    const int2* tn[TREEW_TREES];
+    int node[TREEW_TREES][NHW];
+#pragma unroll
+    for (int u = 0; u < TREEW_TREES; ++u) {
+      const int t = t0 + u * TREEW_WAVES;
+      tn[u] = nodes + (size_t)(t < NT ? t : t0) * n_int;    // past the last tree: walked, not added
+#pragma unroll
+      for (int j = 0; j < NHW; ++j) node[u][j] = 0;
+    }
+    auto left = [&](int2 nd, int j) -> bool {
+      const int f = nd.x + (j > 0 && nd.x >= Fx ? j * hw_dim : 0);
+      return tsm[f * 64 + lane] < __int_as_float(nd.y);
+    };
+    int l0 = 0;
+    if (depth >= 3) {
+      // the first three levels' seven nodes are scalar loads, chosen per lane
+      l0 = 3;
+#pragma unroll
+      for (int u = 0; u < TREEW_TREES; ++u) {
+        const int2* n7 = tn[u];
+        const int2 a0 = n7[0], a1 = n7[1], a2 = n7[2], a3 = n7[3], a4 = n7[4], a5 = n7[5], a6 = n7[6];
+#pragma unroll
+        for (int j = 0; j < NHW; ++j) {
+          const bool b0 = left(a0, j);
+          const bool b1 = left(make_int2(b0 ? a1.x : a2.x, b0 ? a1.y : a2.y), j);
+          const int x = b0 ? (b1 ? a3.x : a4.x) : (b1 ? a5.x : a6.x), y = b0 ? (b1 ? a3.y : a4.y) : (b1 ? a5.y : a6.y);
+          const bool b2 = left(make_int2(x, y), j);
+          node[u][j] = 7 + (b0 ? 0 : 4) + (b1 ? 0 : 2) + (b2 ? 0 : 1);
+        }
+      }
+    }
+    for (int l = l0; l < depth; ++l) {
+      int2 nd[TREEW_TREES][NHW];
+#pragma unroll
+      for (int u = 0; u < TREEW_TREES; ++u)
+#pragma unroll
+        for (int j = 0; j < NHW; ++j) nd[u][j] = tn[u][node[u][j]];
+#pragma unroll
+      for (int u = 0; u < TREEW_TREES; ++u)
+#pragma unroll
+        for (int j = 0; j < NHW; ++j) node[u][j] = 2 * node[u][j] + (left(nd[u][j], j) ? 1 : 2);
+    }
+    float leaf[TREEW_TREES][NHW];
+#pragma unroll
+    for (int u = 0; u < TREEW_TREES; ++u) {
+      const int t = t0 + u * TREEW_WAVES;
+      const float* tl = leaves + (size_t)(t < NT ? t : t0) * (n_int + 1);
+#pragma unroll
+      for (int j = 0; j < NHW; ++j) leaf[u][j] = t < NT ? tl[node[u][j] - n_int] : 0.0f;
+    }
+#pragma unroll
+    for (int j = 0; j < NHW; ++j) acc[j] += (leaf[0][j] + leaf[1][j]) + (leaf[2][j] + leaf[3][j]);
+  }
+  __syncthreads();                                     // x has been read: the partial sums take its place
+#pragma unroll
+  for (int j = 0; j < NHW; ++j) tsm[(j * TREEW_WAVES + w) * 64 + lane] = acc[j];
+  __syncthreads();
+  if (tid < NHW * 64 && lane < nc) {
+    float y[TREEW_WAVES];
+#pragma unroll
+    for (int k = 0; k < TREEW_WAVES; ++k) y[k] = tsm[(w * TREEW_WAVES + k) * 64 + lane];
+#pragma unroll
+    for (int h = TREEW_WAVES / 2; h >= 1; h >>= 1)
+#pragma unroll
+      for (int k = 0; k < h; ++k) y[k] += y[k + h];
+    scores[(size_t)w * B + i0 + lane] = base + y[0];
   }
 }
 
@@ -4288,11 +4421,21 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_kernel(const float* __rest
 // ==========================================================================
 // Top-k per (hardware vector j, subgraph s): one workgroup of 1024 threads.
 //
-// Scores map to order-preserving unsigned keys (NaN lowest, -0 == +0).  A
-// most-significant-digit radix select finds the k-th largest key K*; a second
-// radix select over the (complemented) local index finds how many candidates
-// tied at K* to keep, lowest index first.  The k selected candidates are then
-// bitonic-sorted in LDS by the 64-bit key (score key, ~index).
+// Scores map to order-preserving unsigned keys (NaN lowest, -0 == +0).  The
+// k-th largest of the threads' own maxima bounds the k-th largest key from
+// below (k <= 1024 threads, at least k of which hold a candidate), so the
+// candidates at or above the first 22 bits of that bound contain the top k;
+// they are collected in LDS (about k of them unless scores tie) and ordered by
+// the 64-bit key (score key, ~index), by counting ranks (up to 512) or a
+// bitonic sort.  Latency bounds this kernel (one workgroup per segment): the
+// scores are read once into registers (twice past 32 Ki scores) and no atomic runs per score.  us,
+// before -> after: 65,536 scores, k = 256: 94 -> 26; 2,048, k = 64: 11.6 -> 5.4;
+// 256, k = 16: 8.1 -> 4.1.
+//
+// Where more than TOPK_CAP candidates reach the bound (many equal scores), a
+// most-significant-digit radix select finds the k-th largest key K*, a second
+// one over the (complemented) local index finds how many candidates tied at
+// K* to keep, lowest index first, and the k selected are sorted.
 
 __device__ __forceinline__ uint32_t score_key(float v) {
   if (v != v) return 0u;                // NaN ranks last
@@ -4303,6 +4446,46 @@ __device__ __forceinline__ uint32_t score_key(float v) {
 
 constexpr int TOPK_THREADS = 1024;
 constexpr int TOPK_WAVES = TOPK_THREADS / 64;
+constexpr int TOPK_CAP = 2048;          // candidates collected at the bound
+constexpr int TOPK_RANK = 512;          // of which are ordered by counting
+
+// One 11-bit digit of the `need`-th largest of the threads' values whose upper
+// bits equal `prefix` (1-based; at least `need` such threads take part): returns
+// the digit and lowers `need` by the values above it.  hist: 2048 bins.
+__device__ __forceinline__ uint32_t digit11_select(uint32_t v, bool in, int shift, uint32_t* hist, int* sh, int& need) {
+  const int tid = threadIdx.x;
+  hist[tid] = 0;
+  hist[tid + 1024] = 0;
+  __syncthreads();
+  if (in) atomicAdd(&hist[(v >> shift) & 2047], 1u);
+  __syncthreads();
+  // thread t sums bins 2047 - 2t and 2046 - 2t; an inclusive scan over the
+  // workgroup (highest bins first) finds where the count reaches `need`
+  const int lane = tid & 63, w = tid >> 6;
+  const int c0 = (int)hist[2047 - 2 * tid], c1 = (int)hist[2046 - 2 * tid];
+  int incl = c0 + c1;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int x = __shfl_up(incl, o);
+    if (lane >= o) incl += x;
+  }
+  if (lane == 63) sh[4 + w] = incl;
+  __syncthreads();
+  int before = 0;
+  for (int k = 0; k < w; ++k) before += sh[4 + k];
+  incl += before;
+  const int above = incl - c0 - c1;
+  if (above < need && incl >= need) {
+    const bool first = above + c0 >= need;
+    sh[0] = first ? 2047 - 2 * tid : 2046 - 2 * tid;
+    sh[1] = need - above - (first ? 0 : c0);
+  }
+  __syncthreads();
+  const uint32_t digit = (uint32_t)sh[0];
+  need = sh[1];
+  __syncthreads();
+  return digit;
+}
 
 // Largest-first radix select over the keys that for_each(f) passes to f
 // (each thread its own elements): returns the `need`-th largest key (1-based)
@@ -4375,8 +4558,8 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const float* __restr
                                                             int P2, int32_t* __restrict__ idx,
                                                             float* __restrict__ val) {
   __shared__ uint32_t hist_w[TOPK_WAVES * 256];
-  __shared__ unsigned long long sel[WM_MAX_K];
-  __shared__ int sh[4];
+  __shared__ unsigned long long sel[TOPK_CAP];
+  __shared__ int sh[4 + TOPK_WAVES];
   const int S = seg.n;
   const int j = blockIdx.x / S, s = blockIdx.x % S;
   const int lo = seg.off[s], hi = seg.off[s + 1], n = hi - lo;
@@ -4400,9 +4583,79 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const float* __restr
         if (i < n) f(keys[q], i);
       }
     } else {
-      for (int i = tid; i < n; i += TOPK_THREADS) f(score_key(y[i]), i);
+      // sixteen loads in flight per thread
+      for (int i0 = tid; i0 < n; i0 += 16 * TOPK_THREADS) {
+        float v[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v[q] = i0 + q * TOPK_THREADS < n ? y[i0 + q * TOPK_THREADS] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+          if (i0 + q * TOPK_THREADS < n) f(score_key(v[q]), i0 + q * TOPK_THREADS);
+      }
     }
   };
+
+  auto put = [&](int r, unsigned long long e) {
+    const int li = clampi((int)(~(uint32_t)(e & 0xFFFFFFFFull)), 0, n - 1);
+    const size_t o = ((size_t)j * S + s) * k + r;
+    idx[o] = lo + li;
+    if (val) val[o] = y[li];
+  };
+  // descending bitonic sort of sel[0, m2)
+  auto bitonic = [&](int m2) {
+    for (int size = 2; size <= m2; size <<= 1) {
+      for (int stride = size >> 1; stride > 0; stride >>= 1) {
+        for (int i = tid; i < m2; i += TOPK_THREADS) {
+          const int partner = i ^ stride;
+          if (partner > i) {
+            const bool desc = (i & size) == 0;
+            const unsigned long long a0 = sel[i], a1 = sel[partner];
+            if (desc ? (a0 < a1) : (a0 > a1)) { sel[i] = a1; sel[partner] = a0; }
+          }
+        }
+        __syncthreads();
+      }
+    }
+  };
+
+  // bound from the threads' maxima, candidates at or above it
+  {
+    uint32_t mx = 0;
+    each_key([&](uint32_t kk, int) { mx = kk > mx ? kk : mx; });
+    if (tid == 0) sh[3] = 0;
+    int need = k;
+    const uint32_t d0 = digit11_select(mx, tid < n, 21, hist_w, sh, need);
+    const uint32_t d1 = digit11_select(mx, tid < n && (mx >> 21) == d0, 10, hist_w, sh, need);
+    const uint32_t bound = (d0 << 21) | (d1 << 10);
+    each_key([&](uint32_t kk, int i) {
+      if (kk >= bound) {
+        const int slot = atomicAdd(&sh[3], 1);
+        if (slot < TOPK_CAP) sel[slot] = ((unsigned long long)kk << 32) | (unsigned long long)(~(uint32_t)i);
+      }
+    });
+    __syncthreads();
+    const int m = sh[3];
+    if (m <= TOPK_RANK) {
+      if (tid < m) {
+        const unsigned long long e = sel[tid];
+        int r = 0;
+#pragma unroll 8
+        for (int q = 0; q < m; ++q) r += sel[q] > e;
+        if (r < k) put(r, e);
+      }
+      return;
+    }
+    if (m <= TOPK_CAP) {
+      int m2 = TOPK_RANK;
+      while (m2 < m) m2 <<= 1;
+      for (int i = m + tid; i < m2; i += TOPK_THREADS) sel[i] = 0ull;
+      __syncthreads();
+      bitonic(m2);
+      for (int r = tid; r < k; r += TOPK_THREADS) put(r, sel[r]);
+      return;
+    }
+    __syncthreads();
+  }
 
   int need_eq = 0;
   const uint32_t kstar = radix_select(
@@ -4435,27 +4688,8 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const float* __restr
     }
   });
   __syncthreads();
-  // bitonic sort, descending
-  for (int size = 2; size <= P2; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int i = tid; i < P2; i += TOPK_THREADS) {
-        const int partner = i ^ stride;
-        if (partner > i) {
-          const bool desc = (i & size) == 0;
-          const unsigned long long a0 = sel[i], a1 = sel[partner];
-          if (desc ? (a0 < a1) : (a0 > a1)) { sel[i] = a1; sel[partner] = a0; }
-        }
-      }
-      __syncthreads();
-    }
-  }
-  for (int r = tid; r < k; r += TOPK_THREADS) {
-    // (exactly k keys are selected; the clamp only guards the read)
-    const int li = clampi((int)(~(uint32_t)(sel[r] & 0xFFFFFFFFull)), 0, n - 1);
-    const size_t o = ((size_t)j * S + s) * k + r;
-    idx[o] = lo + li;
-    if (val) val[o] = y[li];
-  }
+  bitonic(P2);
+  for (int r = tid; r < k; r += TOPK_THREADS) put(r, sel[r]);
 }
 
 // ==========================================================================
@@ -4700,10 +4934,17 @@ hipError_t launch_phi(const DevModel& m, const int32_t* types, const int32_t* pa
                       const int32_t* lens, int32_t B, int32_t T_max, float* phi, hipStream_t st) {
   const int E = m.dims.embed_dim;
   if (B == 0) return hipSuccess;
-  const int blocks = (B + 15) / 16;               // four wavefronts of four candidates each
-  hipLaunchKernelGGL(phi_kernel, dim3(blocks), dim3(256), 0, st, m.emb_nat, types, params, lens,
-                     B, T_max, E, m.dims.n_params, m.dims.n_kinds, phi);
-  return hipGetLastError();
+  const bool wide = B < FEAT_WIDE_BATCH;
+  auto go = [&](auto kern) {
+    const int cpb = FEAT_THREADS / (wide ? 16 : 4);
+    hipLaunchKernelGGL(kern, dim3((B + cpb - 1) / cpb), dim3(FEAT_THREADS), 0, st, m.emb_nat, types, params, lens, B,
+                       T_max, m.dims.n_params, m.dims.n_kinds, phi);
+    return hipGetLastError();
+  };
+  if (E == 32) return wide ? go(phi_kernel<32, 16>) : go(phi_kernel<32, 4>);
+  if (E == 64) return wide ? go(phi_kernel<64, 16>) : go(phi_kernel<64, 4>);
+  if (E == 128) return wide ? go(phi_kernel<128, 16>) : go(phi_kernel<128, 4>);
+  return hipErrorInvalidValue;            // the embedding widths of have_kernels
 }
 
 hipError_t launch_phi_struct(const int32_t* types, const int32_t* params, const int32_t* lens,
@@ -4711,8 +4952,10 @@ hipError_t launch_phi_struct(const int32_t* types, const int32_t* params, const 
                              hipStream_t st) {
   if (B == 0) return hipSuccess;
   if (K > 32 || P > PMAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(phi_struct_kernel, dim3((B + 3) / 4), dim3(256), 0, st, types, params, lens, B,
-                     T_max, K, P, phi_s);
+  const bool wide = B < FEAT_WIDE_BATCH;
+  const int cpb = FEAT_THREADS / (wide ? 16 : 4);
+  hipLaunchKernelGGL(wide ? phi_struct_kernel<16> : phi_struct_kernel<4>, dim3((B + cpb - 1) / cpb), dim3(FEAT_THREADS),
+                     0, st, types, params, lens, B, T_max, K, P, phi_s);
   return hipGetLastError();
 }
 
@@ -4720,6 +4963,32 @@ hipError_t launch_score_trees(const DevForest& f, const float* zT, int32_t d, co
                               int32_t phi_dim, int32_t B, const float* hw, int32_t n_hw,
                               int32_t hw_dim, float* scores, hipStream_t st) {
   if (B == 0) return hipSuccess;
+  // Lanes over candidates where 64 candidates' features fit the LDS and the
+  // batch fills half of the compute units with such workgroups; a smaller batch
+  // is spread wider by 8 candidates per workgroup (d = 256, us for 1 / 2
+  // hardware vectors, 8 per workgroup against 64: B = 4096 19 / 33 against 24 / 41
+  // (before the scalar levels), 8192 33 / 60 against 19 / 33, 65,536 229 / 447
+  // against 86 / 132).
+  if (d + phi_dim + 2 * hw_dim <= TREEW_COLUMNS && B >= TREEW_MIN_BATCH) {
+    const int cols = d + phi_dim + (n_hw > 1 ? 2 : 1) * hw_dim;
+    const int rows = cols > 2 * TREEW_WAVES ? cols : 2 * TREEW_WAVES;
+    auto go = [&](auto kern, int j) -> hipError_t {
+      const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, rows * 256);
+      if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return e;
+      }
+      hipLaunchKernelGGL(kern, dim3((B + TREEW_CPB - 1) / TREEW_CPB), dim3(64 * TREEW_WAVES), rows * 256, st,
+                         static_cast<const int2*>(f.nodes), f.leaves, f.n_trees, f.depth, f.base, zT, d, phi_s,
+                         phi_dim, hw + (size_t)j * hw_dim, hw_dim, B, scores + (size_t)j * B);
+      return hipGetLastError();
+    };
+    for (int j = 0; j < n_hw; j += 2) {
+      const hipError_t e = j + 1 < n_hw ? go(score_trees_wide_kernel<2>, j) : go(score_trees_wide_kernel<1>, j);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   const int lds = (TREE_CPB * (d + phi_dim + hw_dim) + (TREE_THREADS / 64) * TREE_CPB) * (int)sizeof(float);
   hipError_t e = hipFuncSetAttribute((const void*)score_trees_kernel,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);

@@ -344,6 +344,31 @@ def test_separate_entry_points_match_fused(wm):
     assert np.abs(phi.cpu().numpy() - ref["phi"]).max() <= 1e-4 * max(1.0, np.abs(ref["phi"]).max())
 
 
+@pytest.mark.parametrize("n,k,kind", [
+    (1, 1, "normal"), (1023, 1023, "normal"), (1025, 1024, "normal"), (40000, 600, "normal"),
+    (65537, 1024, "normal"), (3000, 40, "equal"), (40000, 1000, "two"), (5000, 100, "nan"), (33000, 7, "one_bin")])
+def test_topk_bound_paths(wm, n, k, kind):
+    """Each way out of the top-k's candidate collection: up to 512 candidates at
+    the bound (ranks counted), up to 2048 (sorted), more (equal scores: the radix
+    selects), more NaNs than numbers, scores that share their first 22 bits."""
+    rng = np.random.default_rng(n + k)
+    y = rng.standard_normal((2, n)).astype(np.float32)
+    if kind == "equal":
+        y[:] = 1.5
+    elif kind == "two":
+        y = np.where(y > 2.2, np.float32(2.0), np.float32(-1.0))
+    elif kind == "nan":
+        y[:, rng.permutation(n)[: n - 50]] = np.nan
+    elif kind == "one_bin":
+        y = (np.float32(1.0) + rng.integers(0, 1000, size=(2, n)).astype(np.float32) * np.float32(2.0 ** -23))
+    idx = torch.empty((2, 1, k), dtype=torch.int32, device="cuda")
+    val = torch.empty((2, 1, k), device="cuda")
+    wm.topk(torch.from_numpy(y).cuda(), [0, n], k, idx, val)
+    ref_i, ref_v = O.topk(y.astype(np.float64), [0, n], k)
+    np.testing.assert_array_equal(idx.cpu().numpy(), ref_i)
+    np.testing.assert_array_equal(val.cpu().numpy(), ref_v.astype(np.float32))
+
+
 def test_topk_entry_point_edge_scores(wm):
     dev = "cuda"
     y = np.array([[1.0, 3.0, 3.0, np.nan, -0.0, 0.0, 3.0, -np.inf, np.inf, 2.0]], np.float32)

@@ -33,9 +33,11 @@ def _forest(wm, w, seed, **kw):
     return wm.Forest(f["feat"], f["thr"], f["leaf"], float(f["base"]), n_feat), f
 
 
-@pytest.mark.parametrize("T_max,len_lo", [(32, 0), (100, 60)])
-def test_phi_struct_matches_oracle(wm, T_max, len_lo):
-    w = synth.scaled(synth.workload("ansor_round"), B=333, len_lo=len_lo, len_hi=T_max, T_max=T_max)
+@pytest.mark.parametrize("B,T_max,len_lo", [(333, 32, 0), (333, 100, 60), (16384 + 5, 9, 0)])
+def test_phi_struct_matches_oracle(wm, B, T_max, len_lo):
+    """Both lane counts per candidate (16 below 16384 candidates, 4 above), a
+    partial last workgroup."""
+    w = synth.scaled(synth.workload("ansor_round"), B=B, len_lo=len_lo, len_hi=T_max, T_max=T_max)
     I = synth.make_inputs(w, 61, pad="garbage")
     I["lens"][:4] = 0
     t = to_dev(I, "cuda")
@@ -67,6 +69,32 @@ def test_score_trees_exact_decisions(wm, n_trees, depth):
     got = sc.cpu().numpy().astype(np.float64)
     want = TR.score_trees(zT, phi, hw, f["feat"], f["thr"], f["leaf"], float(f["base"]))
     np.testing.assert_allclose(got, want, rtol=0, atol=1e-6 * n_trees)
+
+
+@pytest.mark.parametrize("d,n_hw,n_trees,depth", [(256, 1, 70, 8), (256, 3, 17, 3), (7, 2, 5, 2), (512, 2, 64, 9)])
+def test_score_trees_lanes_over_candidates(wm, d, n_hw, n_trees, depth):
+    """Batches from 8192 candidates walk a tree with a candidate per lane: a
+    partial last workgroup, one, two and an odd number of hardware vectors, tree
+    counts off the wavefront count, depths below, at and above the three levels
+    that are chosen from scalars, latent widths off the 16-byte loads."""
+    base = synth.workload("ansor_round")
+    B, K, P, HW = 8192 + 37, base.n_kinds, base.n_params, base.hw_dim
+    rng = np.random.default_rng(depth * 100 + d)
+    F = d + TR.phi_dim(K, P) + HW
+    n_int = 2 ** depth - 1
+    feat = rng.integers(0, F, size=(n_trees, n_int)).astype(np.int32)
+    thr = rng.standard_normal((n_trees, n_int)).astype(np.float32)
+    leaf = (0.1 * rng.standard_normal((n_trees, n_int + 1))).astype(np.float32)
+    forest = wm.Forest(feat, thr, leaf, 0.25, F)
+    zT = rng.standard_normal((B, d)).astype(np.float32)
+    phi = rng.standard_normal((B, TR.phi_dim(K, P))).astype(np.float32)
+    hw = rng.standard_normal((n_hw, HW)).astype(np.float32)
+    zT[5, :], zT[6, :] = thr[0, 0], np.nan         # on a threshold: right; NaN: right
+    dv = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    sc = torch.empty((n_hw, B), device="cuda")
+    wm.score_trees(forest, dv(zT), dv(phi), dv(hw), sc)
+    want = TR.score_trees(zT, phi, hw, feat, thr, leaf, 0.25)
+    np.testing.assert_allclose(sc.cpu().numpy().astype(np.float64), want, rtol=0, atol=1e-6 * n_trees)
 
 
 def _certain(ref_zT, g_zT, phi, hw_j, f, d):
