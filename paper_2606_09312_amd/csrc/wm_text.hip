@@ -4,13 +4,15 @@
 // mean over a program's chunks, and a linear projection head to the latent.
 //
 // All chunks of all programs are one batch of rows, one row per (chunk,
-// position).  bf16: the rows are the chunks' tokens and nothing else; dense
-// products on bf16-stored operands, attention fused per (chunk, head).
-// float32: every chunk takes `window` rows (positions past its tokens are
-// padding: never pooled, masked as attention keys); the dense products run in
-// an LDS-tiled matrix-core kernel (128 x 128 output tiles, 32-deep stages),
-// and attention is the same kernel batched over (chunk, head) for the scores
-// and for probabilities x values, with a row softmax in between.
+// position).  Head widths 32 and 64 (bf16: windows up to 512) take the packed
+// paths: the rows are the chunks' tokens and nothing else, attention is fused
+// per (chunk, head), and dense products run on bf16 operands, in float32 as
+// six products of three bf16 planes per operand.  Other shapes take the general
+// path: every chunk takes `window` rows (positions past its tokens are
+// padding: never pooled, masked as attention keys), products in an LDS-tiled
+// matrix-core kernel (128 x 128 output tiles, 32-deep stages), attention by the
+// same kernel batched over (chunk, head) for the scores and for probabilities
+// x values, with a row softmax in between.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -32,7 +34,7 @@ struct wm_text_model {
   const float *tok_emb, *pos_emb, *ln0_g, *ln0_b;
   const float *wqkv, *bqkv, *wo, *bo, *ln1_g, *ln1_b, *w1, *b1, *w2, *b2, *ln2_g, *ln2_b;
   const float *wp, *bp;
-  const __bf16 *wqkv16, *wo16, *w116, *w216;   // WM_BF16: the layer matrices as bf16
+  const __bf16 *wqkv16, *wo16, *w116, *w216;   // the layer matrices as bf16 (WM_FP32: three planes)
 };
 
 namespace wm {
@@ -69,6 +71,15 @@ __device__ __forceinline__ float wave_max(float x) {
   return x;
 }
 
+// x as three bf16 planes, x = hi + mid + lo to 2^-24 |x| (each remainder is
+// exact in float32): the operand form of the float32 products below.
+__device__ __forceinline__ void split3(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
+  hi = (__bf16)x;
+  const float r = x - (float)hi;
+  mid = (__bf16)r;
+  lo = (__bf16)(r - (float)mid);
+}
+
 // One LayerNorm output (the same value wherever it is recomputed).
 __device__ __forceinline__ float ln_value(float x, float mean, float rs, float g, float b) {
   return fmaf((x - mean) * rs, g, b);
@@ -92,7 +103,7 @@ __device__ __forceinline__ int program_of(const TTable& tt, int c) {
 }
 // First token, token count and first row of chunk c.  A program's chunks are
 // `window` rows apart; only its last chunk can hold fewer tokens, and on the
-// bf16 path the next program's rows follow them directly.
+// packed paths the next program's rows follow them directly.
 __device__ __forceinline__ void chunk_span(const TTable& tt, int c, int window, int stride,
                                            int& first, int& len, int& row) {
   const int s = program_of(tt, c), k = c - tt.chunk_off[s];
@@ -117,13 +128,14 @@ __device__ __forceinline__ void row_place(const TTable& tt, int r, int window, i
 // zero), then as ln_kernel.  One wavefront per row, lanes over the features.
 constexpr int LN_MAX_PER_LANE = 16;               // hidden <= 1024
 
-// LayerNorm of one row held as x[i] = feature lane + 64 i.  bf16 path: writes
-// the normalised row as the next product's operand (hb) and its mean and
-// 1/deviation (stats); the residual path and the pooling recompute the float32
+// LayerNorm of one row held as x[i] = feature lane + 64 i.  Packed paths: writes
+// the normalised row as the next product's operand (hb; plane > 0: its three
+// planes) and its mean and 1/deviation (stats); the residual path and the pooling recompute the float32
 // values from y and those two, so they are never stored (10 -> 6 bytes per
-// feature; 68,608 rows of 768: 85 -> 60 us).  fp32 path: writes h.
+// feature; 68,608 rows of 768: 85 -> 60 us).  General path: writes h.
 __device__ __forceinline__ void ln_row(const float (&x)[LN_MAX_PER_LANE], float s, int H, const float* g,
-                                       const float* b, size_t r, float* h, __bf16* hb, float2* stats) {
+                                       const float* b, size_t r, float* h, __bf16* hb, size_t plane,
+                                       float2* stats) {
   const int lane = threadIdx.x & 63;
   const float mean = wave_sum(s) / (float)H;
   float v = 0.0f;
@@ -137,7 +149,8 @@ __device__ __forceinline__ void ln_row(const float (&x)[LN_MAX_PER_LANE], float 
     const int f = lane + 64 * i;
     if (f < H) {
       const float o = ln_value(x[i], mean, rs, g[f], b[f]);
-      if (hb) hb[r * H + f] = (__bf16)o;
+      if (plane) split3(o, hb[r * H + f], hb[plane + r * H + f], hb[2 * plane + r * H + f]);
+      else if (hb) hb[r * H + f] = (__bf16)o;
       else h[r * H + f] = o;
     }
   }
@@ -150,15 +163,15 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t* __restrict
                                                        const float* __restrict__ g,
                                                        const float* __restrict__ b, int H, int vocab,
                                                        int rows, float* __restrict__ y, float* __restrict__ h,
-                                                       __bf16* __restrict__ hb, float2* __restrict__ stats,
-                                                       int32_t* err) {
+                                                       __bf16* __restrict__ hb, size_t plane,
+                                                       float2* __restrict__ stats, int32_t* err) {
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= rows) return;
   int c, p, first, len, row;
   row_place(tt, r, window, c, p);
   chunk_span(tt, c, window, stride, first, len, row);
-  if (p >= len) {                                 // fp32 path only: padding
+  if (p >= len) {                                 // general path only: padding
     for (int f = lane; f < H; f += 64) h[(size_t)r * H + f] = 0.0f;
     return;
   }
@@ -176,14 +189,14 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t* __restrict
     if (hb && f < H) y[(size_t)r * H + f] = x[i];
     s += x[i];
   }
-  ln_row(x, s, H, g, b, r, h, hb, stats);
+  ln_row(x, s, H, g, b, r, h, hb, plane, stats);
 }
 
 // LN(y[r]) (the residual sum is formed by the product's epilogue).
 __global__ __launch_bounds__(256) void ln_kernel(const float* __restrict__ y,
                                                  const float* __restrict__ g,
                                                  const float* __restrict__ b, int H, int rows,
-                                                 float* __restrict__ h, __bf16* __restrict__ hb,
+                                                 float* __restrict__ h, __bf16* __restrict__ hb, size_t plane,
                                                  float2* __restrict__ stats) {
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -197,7 +210,7 @@ __global__ __launch_bounds__(256) void ln_kernel(const float* __restrict__ y,
     x[i] = f < H ? in[f] : 0.0f;
     s += x[i];
   }
-  ln_row(x, s, H, g, b, r, h, hb, stats);
+  ln_row(x, s, H, g, b, r, h, hb, plane, stats);
 }
 
 // ---------------------------------------------------------------------------
@@ -814,10 +827,233 @@ __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restric
   }
 }
 
+// float32 dense product on the bf16 matrix cores: both operands as three bf16
+// planes (split3), C = sum of the six plane products that matter
+// (hi hi; hi mid, mid hi, hi lo, mid mid, lo hi: what is left out is below
+// 2^-25 of |a||b|), the five small ones in an accumulator of their own.  Six
+// bf16 products take 96 cycles per 16x16x32 where float32 ones take 256.  Its
+// distance from float64 over the encoder equals that of the float32 products
+// (5e-7).  Tiles of 64 x 64, 4 wavefronts of 32 x 32, slices of 32 (24 KiB with
+// all planes) in a ring of three, one barrier per slice as in
+// gemm16_small_kernel; two workgroups per compute unit.  2400 rows, us per
+// layer's product against 128 x 128 float32 tiles (114 of 256 compute units
+// busy at N = 768): see the table in the repository's design notes.
+struct Gemm3Args {
+  const __bf16 *A, *W;      // planes a_plane, w_plane elements apart
+  void* C;                  // float32, or planes c_plane elements apart
+  const float* bias;
+  const float* res;         // y (then C is y), or null
+  const float2* stats;
+  const float *ln_g, *ln_b;
+  size_t a_plane, w_plane, c_plane;
+  int M, N, K, tiles_n, gelu;
+};
+template <bool SPLIT_OUT>
+__global__ __launch_bounds__(256, 2) void gemm16x3_kernel(const Gemm3Args g) {
+  constexpr int BM = 64, BN = 64, PL = BM * GK, SLICE = 6 * PL;   // planes: A hi, mid, lo, W hi, mid, lo
+  __shared__ __attribute__((aligned(16))) __bf16 S[3 * SLICE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cl = lane & 31, h = lane >> 5;
+  const int t = xcd_tile(blockIdx.x, gridDim.x);
+  const int m0 = (t / g.tiles_n) * BM, n0 = (t % g.tiles_n) * BN;
+  const int rows = min(BM, g.M - m0), cols = min(BN, g.N - n0);
+  const int wm = wave & 1, wn = wave >> 1;
+  const int K2 = g.K * 2, nk = g.K / GK;
+  const uint32_t oa = slice_offset<1>(tid, K2, rows), ob = slice_offset<1>(tid, K2, cols);
+  u32x4 ra[3], rb[3];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    ra[p] = buffer_of(g.A + p * g.a_plane + (size_t)m0 * g.K, (uint32_t)rows * K2);
+    rb[p] = buffer_of(g.W + p * g.w_plane + (size_t)n0 * g.K, (uint32_t)cols * K2);
+  }
+  f32x16 hi = {}, lo = {};
+  const int sw = (cl >> 2) & 3;
+  auto copy = [&](int s, int b) {
+    __bf16* d = S + b * SLICE + wave * 512;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) copy16(ra[p], d + p * PL, oa, s * GK * 2);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) copy16(rb[p], d + (3 + p) * PL, ob, s * GK * 2);
+  };
+  copy(0, 0);
+  if (nk > 1) copy(1, 1);
+  int cur = 0;
+  for (int s = 0; s < nk; ++s) {
+    if (s + 1 < nk) wait_counts<6, true>(); else wait_counts<0, true>();
+    raw_barrier();
+    if (s + 2 < nk) copy(s + 2, cur == 0 ? 2 : cur - 1);
+    const __bf16* base = S + cur * SLICE + cl * GK;
+    bf16x8 fa[2][3], fb[2][3];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const __bf16* a = base + ((2 * ks + h) ^ sw) * 8;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        fa[ks][p] = *reinterpret_cast<const bf16x8*>(a + p * PL + wm * 32 * GK);
+        fb[ks][p] = *reinterpret_cast<const bf16x8*>(a + (3 + p) * PL + wn * 32 * GK);
+      }
+    }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      lo = BF::mfma(fa[ks][2], fb[ks][0], lo);
+      hi = BF::mfma(fa[ks][0], fb[ks][0], hi);
+      lo = BF::mfma(fa[ks][1], fb[ks][1], lo);
+      lo = BF::mfma(fa[ks][0], fb[ks][2], lo);
+      lo = BF::mfma(fa[ks][1], fb[ks][0], lo);
+      lo = BF::mfma(fa[ks][0], fb[ks][1], lo);
+    }
+    cur = cur == 2 ? 0 : cur + 1;
+  }
+  const int n = n0 + wn * 32 + cl;
+  if (n >= g.N) return;
+  const float bias = g.bias[n];
+  const float lg = g.res ? g.ln_g[n] : 0.0f, lb = g.res ? g.ln_b[n] : 0.0f;
+  float y[16];
+  float2 st[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = min(m0 + wm * 32 + acc_row(h, r), g.M - 1);
+    y[r] = g.res ? g.res[(size_t)m * g.N + n] : 0.0f;
+    st[r] = g.res ? g.stats[m] : make_float2(0.0f, 0.0f);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + wm * 32 + acc_row(h, r);
+    if (m >= g.M) continue;
+    float v = (hi[r] + lo[r]) + bias;
+    if (g.gelu) v = gelu(v);
+    if (g.res) v += ln_value(y[r], st[r].x, st[r].y, lg, lb);
+    const size_t o = (size_t)m * g.N + n;
+    if constexpr (SPLIT_OUT) {
+      __bf16* c = static_cast<__bf16*>(g.C) + o;
+      split3(v, c[0], c[g.c_plane], c[2 * g.c_plane]);
+    } else {
+      static_cast<float*>(g.C)[o] = v;
+    }
+  }
+}
+
+// n float32 values as `planes` bf16 planes (1: rounded; 3: split3), n apart.
+__global__ __launch_bounds__(256) void split_planes_kernel(const float* __restrict__ src, size_t n, int planes,
+                                                           __bf16* __restrict__ dst) {
+  for (size_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
+    if (planes == 1) dst[i] = (__bf16)src[i];
+    else split3(src[i], dst[i], dst[n + i], dst[2 * n + i]);
+  }
+}
+
+// Fused float32 attention of one (chunk, head) and 128 queries: wavefront w
+// takes queries 32 w .. of the block; keys in blocks of 64, staged in LDS (K and
+// V row-major), softmax online.  S^T = K . Q^T on the float32 matrix cores with
+// the contraction enumerated half by half (a lane half reads its 32 features
+// in 16-byte pieces), so a query is a lane's column; P stays in the
+// accumulators, whose key order V's rows are read in.  Row strides keep both
+// reads off shared banks.  Replaces score matrices in memory, a softmax pass
+// and two batched products (150 us per layer at 2400 rows).
+template <int DH>
+__global__ __launch_bounds__(256, 2) void attention32_kernel(const float* __restrict__ qkv,
+                                                             __bf16* __restrict__ ctx, size_t plane,
+                                                             const TTable tt, int window, int stride, int heads,
+                                                             int H, float scale) {
+  constexpr int KB = 64, DB = DH / 32, HS = DH / 2;     // keys per block, 32-feature blocks, features per lane half
+  constexpr int KW = DH + 4, VW = DH + 8;
+  __shared__ __attribute__((aligned(16))) float Ks[KB * KW];
+  __shared__ __attribute__((aligned(16))) float Vs[KB * VW];
+  const int c = blockIdx.x / heads, head = blockIdx.x % heads;
+  int first, len, row0;
+  chunk_span(tt, c, window, stride, first, len, row0);
+  const int q0 = blockIdx.y * 128;
+  if (q0 >= len) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cl = lane & 31, h = lane >> 5;
+  const float* base = qkv + (size_t)row0 * 3 * H + head * DH;
+  const int q = q0 + wave * 32 + cl;
+  // scores in units of log2: exp(s scale) = 2^(s scale log2 e)
+  const float c2 = scale * 1.4426950408889634f;
+  float qf[HS];
+  {
+    const float* qrow = base + (size_t)min(q, len - 1) * 3 * H + h * HS;
+#pragma unroll
+    for (int i = 0; i < HS; i += 4) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(qrow + i);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) qf[i + j] = v[j];
+    }
+  }
+  f32x16 oacc[DB];
+#pragma unroll
+  for (int b = 0; b < DB; ++b) oacc[b] = f32x16{};
+  float mx = -INFINITY, sum = 0.0f;
+  for (int k0 = 0; k0 < len; k0 += KB) {
+    __syncthreads();
+    for (int u = tid; u < KB * (DH / 4); u += 256) {
+      const int key = u / (DH / 4), d4 = (u % (DH / 4)) * 4;
+      const float* src = base + (size_t)min(k0 + key, len - 1) * 3 * H + d4;   // keys past the end are masked
+      *reinterpret_cast<f32x4*>(Ks + key * KW + d4) = *reinterpret_cast<const f32x4*>(src + H);
+      *reinterpret_cast<f32x4*>(Vs + key * VW + d4) = *reinterpret_cast<const f32x4*>(src + 2 * H);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kb = 0; kb < KB / 32; ++kb) {
+      const int kbase = k0 + 32 * kb;
+      if (kbase >= len) break;
+      f32x16 s = {};
+#pragma unroll
+      for (int i = 0; i < HS; i += 4) {
+        const f32x4 kf = *reinterpret_cast<const f32x4*>(Ks + (32 * kb + cl) * KW + h * HS + i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float a = kf[j];
+          s = FP::mfma(a, qf[i + j], s);
+        }
+      }
+      float bm = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s[r] = kbase + acc_row(h, r) < len ? s[r] * c2 : -INFINITY;
+        bm = fmaxf(bm, s[r]);
+      }
+      bm = fmaxf(bm, __shfl_xor(bm, 32));
+      const float nm = fmaxf(mx, bm);
+      const float f = exp2_of(mx - nm);        // 0 at the first block
+      float bs = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s[r] = exp2_of(s[r] - nm);
+        bs += s[r];
+      }
+      sum = fmaf(sum, f, bs);
+      mx = nm;
+#pragma unroll
+      for (int b = 0; b < DB; ++b) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[b][r] *= f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float p = s[r];
+          oacc[b] = FP::mfma(Vs[(32 * kb + acc_row(h, r)) * VW + 32 * b + cl], p, oacc[b]);
+        }
+      }
+    }
+  }
+  const float inv = 1.0f / (sum + __shfl_xor(sum, 32));
+  if (q < len) {
+    __bf16* o = ctx + ((size_t)row0 + q) * H + head * DH;
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int d = 32 * b + acc_row(h, r);
+        split3(oacc[b][r] * inv, o[d], o[plane + d], o[2 * plane + d]);
+      }
+  }
+}
+
 // Masked mean over a chunk's tokens: one workgroup per chunk; thread t sums
 // the feature quad t % (H/4) over the tokens p = t / (H/4) + k G (G token
 // groups, 16-byte loads), then the G partial sums are added in group order.
-// bf16 path (stats given): the rows are LN(y), recomputed as they are read.
+// Packed paths (stats given): the rows are LN(y), recomputed as they are read.
 constexpr int POOL_THREADS = 1024;
 __global__ __launch_bounds__(POOL_THREADS) void pool_kernel(const float* __restrict__ h, const float2* __restrict__ stats,
                                                             const float* __restrict__ ln_g,
@@ -896,10 +1132,12 @@ int n_chunks_of(int n_tokens, int window, int stride) {
   return 1 + (n_tokens - window + stride - 1) / stride;
 }
 
-// bf16 with a fused-attention head width and window: operands stored as bf16
-bool bf16_path(const wm_text_dims& d) {
+// Packed paths: rows of tokens only, products on bf16 operands (float32: three
+// planes of them) and fused attention, whose head widths and (bf16) window
+// these are.  Everything else takes the general path.
+bool packed_path(const wm_text_dims& d) {
   const int dh = d.hidden / d.heads;
-  return d.precision == WM_BF16 && (dh == 32 || dh == 64) && d.window <= 512;
+  return (dh == 32 || dh == 64) && (d.precision == WM_FP32 || d.window <= 512);
 }
 
 struct TextLayout {
@@ -908,24 +1146,25 @@ struct TextLayout {
 
 TextLayout text_layout(const wm_text_dims& dm, int n_chunks) {
   const size_t rows = (size_t)n_chunks * dm.window, H = dm.hidden;
-  const bool bf = bf16_path(dm);
+  const bool bf = packed_path(dm), f32 = bf && dm.precision == WM_FP32;
+  const size_t pb = f32 ? 6 : 2;             // bytes of a product operand
   TextLayout L;
   size_t o = 0;
   L.err = o; o += 256;
   L.h = o; o = al256(o + (bf ? 0 : rows * H * 4));
-  L.qkv = o; o = al256(o + (bf ? 0 : rows * 3 * H * 4));
+  L.qkv = o; o = al256(o + (bf && !f32 ? 0 : rows * 3 * H * 4));
   L.sc = o; o = al256(o + (bf ? 0 : (size_t)n_chunks * dm.heads * dm.window * dm.window * 4));
   L.ctx = o; o = al256(o + (bf ? 0 : rows * H * 4));
   L.y = o; o = al256(o + rows * H * 4);
   L.f = o; o = al256(o + (bf ? 0 : rows * (size_t)dm.ffn * 4));
   L.pooled = o; o = al256(o + (size_t)n_chunks * H * 4);
-  // bf16: the product operands and the rows' LayerNorm statistics (the fp32
-  // h, qkv, scores, context and hidden buffers above are then unused and
-  // sized zero)
-  L.hb = o; o = al256(o + (bf ? rows * H * 2 : 0));
-  L.qkvb = o; o = al256(o + (bf ? rows * 3 * H * 2 : 0));
-  L.ctxb = o; o = al256(o + (bf ? rows * H * 2 : 0));
-  L.fb = o; o = al256(o + (bf ? rows * (size_t)dm.ffn * 2 : 0));
+  // packed paths: the product operands and the rows' LayerNorm statistics (the
+  // float32 h, scores, context and hidden buffers above, and in bf16 qkv, are
+  // then unused and sized zero)
+  L.hb = o; o = al256(o + (bf ? rows * H * pb : 0));
+  L.qkvb = o; o = al256(o + (bf && !f32 ? rows * 3 * H * 2 : 0));
+  L.ctxb = o; o = al256(o + (bf ? rows * H * pb : 0));
+  L.fb = o; o = al256(o + (bf ? rows * (size_t)dm.ffn * pb : 0));
   L.stats = o; o = al256(o + (bf ? rows * 8 : 0));
   L.total = o;
   return L;
@@ -995,11 +1234,14 @@ wm_status wm_text_model_create(const wm_text_dims* dims, const wm_text_weights* 
       {w->wp, (size_t)d.d * H, true, 0}, {w->bp, (size_t)d.d, false, 0}};
   size_t total = 0;
   for (auto& p : parts) { p.off = total; total = al256(total + p.n * 4); }
-  // bf16 copies of wqkv, wo, w1, w2 (parts 4, 6, 10, 12)
+  // bf16 copies of wqkv, wo, w1, w2 (parts 4, 6, 10, 12); float32 on the packed
+  // path: their three planes
   const int mats[4] = {4, 6, 10, 12};
+  const bool w16 = bf || packed_path(d);
+  const size_t planes = bf ? 1 : 3;
   size_t off16[4] = {0, 0, 0, 0};
-  if (bf)
-    for (int i = 0; i < 4; ++i) { off16[i] = total; total = al256(total + parts[mats[i]].n * 2); }
+  if (w16)
+    for (int i = 0; i < 4; ++i) { off16[i] = total; total = al256(total + parts[mats[i]].n * 2 * planes); }
   void* dev = nullptr;
   if (hipMalloc(&dev, total) != hipSuccess) {
     (void)hipGetLastError();
@@ -1017,17 +1259,22 @@ wm_status wm_text_model_create(const wm_text_dims* dims, const wm_text_weights* 
       return set_error(WM_ERR_DEVICE, "hipMemcpy of the encoder weights failed");
     }
   }
-  if (bf) {
-    std::vector<__bf16> t16;
-    for (int i = 0; i < 4; ++i) {
+  if (w16) {
+    // the matrices' bf16 values (planes) are formed on the device from the
+    // uploaded float32 ones
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < 4 && e == hipSuccess; ++i) {
       const Part& p = parts[mats[i]];
       if (p.n == 0) continue;
-      t16.resize(p.n);
-      for (size_t j = 0; j < p.n; ++j) t16[j] = (__bf16)p.src[j];
-      if (hipMemcpy(base + off16[i], t16.data(), p.n * 2, hipMemcpyHostToDevice) != hipSuccess) {
-        (void)hipFree(dev);
-        return set_error(WM_ERR_DEVICE, "hipMemcpy of the encoder weights failed");
-      }
+      hipLaunchKernelGGL(split_planes_kernel, dim3(2048), dim3(256), 0, nullptr,
+                         reinterpret_cast<const float*>(base + p.off), p.n, (int)planes,
+                         reinterpret_cast<__bf16*>(base + off16[i]));
+      e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) {
+      (void)hipFree(dev);
+      return set_error(WM_ERR_DEVICE, std::string("rounding the encoder weights: ") + hipGetErrorString(e));
     }
   }
   wm_text_model* m = new (std::nothrow) wm_text_model;
@@ -1042,7 +1289,7 @@ wm_status wm_text_model_create(const wm_text_dims* dims, const wm_text_weights* 
                          &m->ln2_b, &m->wp, &m->bp};
   for (size_t i = 0; i < parts.size(); ++i) *dst[i] = reinterpret_cast<const float*>(base + parts[i].off);
   const __bf16** dst16[] = {&m->wqkv16, &m->wo16, &m->w116, &m->w216};
-  for (int i = 0; i < 4; ++i) *dst16[i] = bf ? reinterpret_cast<const __bf16*>(base + off16[i]) : nullptr;
+  for (int i = 0; i < 4; ++i) *dst16[i] = w16 ? reinterpret_cast<const __bf16*>(base + off16[i]) : nullptr;
   *out = m;
   return clear_error();
 }
@@ -1089,9 +1336,9 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
     tt.tok_off[s] = tok_off[s];
     const int n = tok_off[s + 1] - tok_off[s], nc = n_chunks_of(n, d.window, d.stride);
     tt.chunk_off[s + 1] = tt.chunk_off[s] + nc;
-    // the bf16 path's rows are the chunks' tokens alone; the float32 path's
+    // the packed paths' rows are the chunks' tokens alone; the general path's
     // batched products take every chunk at `window` rows
-    tt.row_off[s + 1] = tt.row_off[s] + (nc == 0 ? 0 : !bf16_path(d) ? nc * d.window
+    tt.row_off[s + 1] = tt.row_off[s] + (nc == 0 ? 0 : !packed_path(d) ? nc * d.window
                                          : (nc - 1) * d.window + (n - (nc - 1) * d.stride));
   }
   tt.tok_off[S] = tok_off[S];
@@ -1105,9 +1352,7 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
   const int H = d.hidden, F = d.ffn, W = d.window, nh = d.heads, dh = H / nh;
   const int rows = tt.row_off[S];
   const bool bf = d.precision == WM_BF16;
-  // bf16 operand path: fused attention (head width 32 or 64, K and V of a
-  // window in LDS) and products on bf16-stored operands
-  const bool fused = bf16_path(d);
+  const bool fused = packed_path(d), f32 = fused && !bf;
   auto gemm = [&](const GemmArgs& g, int batch, bool bt) {
     return bf ? launch_gemm<BF>(g, batch, bt, st) : launch_gemm<FP>(g, batch, bt, st);
   };
@@ -1149,8 +1394,20 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
     }
     return hipGetLastError();
   };
+  auto g3 = [&](const __bf16* A, int K, const __bf16* Wm, size_t w_plane, int N, void* C, const float* bias,
+                const float* res, const float* lng, const float* lnb, int gelu, bool split) {
+    Gemm3Args g;
+    g.A = A; g.W = Wm; g.C = C; g.bias = bias; g.res = res; g.stats = stats; g.ln_g = lng; g.ln_b = lnb;
+    g.a_plane = (size_t)rows * K; g.w_plane = w_plane; g.c_plane = (size_t)rows * N;
+    g.M = rows; g.N = N; g.K = K; g.gelu = gelu;
+    g.tiles_n = (N + 63) / 64;
+    const dim3 grid(((rows + 63) / 64) * g.tiles_n);
+    if (split) hipLaunchKernelGGL(gemm16x3_kernel<true>, grid, dim3(256), 0, st, g);
+    else hipLaunchKernelGGL(gemm16x3_kernel<false>, grid, dim3(256), 0, st, g);
+    return hipGetLastError();
+  };
   auto ln = [&](const float* yin, const float* gm, const float* bt, __bf16* hbo) {
-    hipLaunchKernelGGL(ln_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, yin, gm, bt, H, rows, h, hbo, stats);
+    hipLaunchKernelGGL(ln_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, yin, gm, bt, H, rows, h, hbo, f32 ? (size_t)rows * H : 0, stats);
     return hipGetLastError();
   };
   __bf16* hb = reinterpret_cast<__bf16*>(w8 + L.hb);
@@ -1161,9 +1418,30 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
   if (n_chunks > 0) {
     WM_TT(TK_TEXT_OTHER, [&]() { hipLaunchKernelGGL(embed_ln_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, tokens,
                                              tt, W, d.stride, m->tok_emb, m->pos_emb, m->ln0_g, m->ln0_b,
-                                             H, d.vocab, rows, y, h, fused ? hb : nullptr, stats, err); return hipGetLastError(); }());
+                                             H, d.vocab, rows, y, h, fused ? hb : nullptr, f32 ? (size_t)rows * H : 0, stats, err); return hipGetLastError(); }());
     for (int l = 0; l < d.layers; ++l) {
       const size_t lH = (size_t)l * H;
+      const float* g0 = l ? m->ln2_g + lH - H : m->ln0_g;       // the LayerNorm before this layer
+      const float* b0 = l ? m->ln2_b + lH - H : m->ln0_b;
+      if (f32) {
+        const size_t Lw = (size_t)d.layers * H;
+        WM_TT(TK_TEXT_GEMM, g3(hb, H, m->wqkv16 + lH * 3 * H, Lw * 3 * H, 3 * H, qkv, m->bqkv + 3 * lH, nullptr,
+                               nullptr, nullptr, 0, false));
+        WM_TT(TK_TEXT_ATTN, [&]() {
+          hipLaunchKernelGGL(dh == 64 ? attention32_kernel<64> : attention32_kernel<32>,
+                             dim3(n_chunks * nh, (W + 127) / 128), dim3(256), 0, st, qkv, ctxb, (size_t)rows * H, tt, W,
+                             d.stride, nh, H, 1.0f / std::sqrt((float)dh));
+          return hipGetLastError();
+        }());
+        WM_TT(TK_TEXT_GEMM, g3(ctxb, H, m->wo16 + lH * H, Lw * H, H, y, m->bo + lH, y, g0, b0, 0, false));
+        WM_TT(TK_TEXT_OTHER, ln(y, m->ln1_g + lH, m->ln1_b + lH, hb));
+        WM_TT(TK_TEXT_GEMM, g3(hb, H, m->w116 + lH * F, Lw * F, F, fb, m->b1 + (size_t)l * F, nullptr, nullptr,
+                               nullptr, 1, true));
+        WM_TT(TK_TEXT_GEMM, g3(fb, F, m->w216 + lH * F, Lw * F, H, y, m->b2 + lH, y, m->ln1_g + lH, m->ln1_b + lH, 0,
+                               false));
+        WM_TT(TK_TEXT_OTHER, ln(y, m->ln2_g + lH, m->ln2_b + lH, hb));
+        continue;
+      }
       if (fused) {
         // bf16: every product operand is stored as bf16
         WM_TT(TK_TEXT_GEMM, g16(hb, rows, H, m->wqkv16 + lH * 3 * H, 3 * H, qkvb, m->bqkv + 3 * lH,
@@ -1177,8 +1455,7 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
                              d.stride, nh, H, 1.0f / std::sqrt((float)dh));
           return hipGetLastError();
         }());
-        WM_TT(TK_TEXT_GEMM, g16(ctxb, rows, H, m->wo16 + lH * H, H, y, m->bo + lH, y, l ? m->ln2_g + lH - H : m->ln0_g,
-                                l ? m->ln2_b + lH - H : m->ln0_b, 0, false));
+        WM_TT(TK_TEXT_GEMM, g16(ctxb, rows, H, m->wo16 + lH * H, H, y, m->bo + lH, y, g0, b0, 0, false));
         WM_TT(TK_TEXT_OTHER, ln(y, m->ln1_g + lH, m->ln1_b + lH, hb));
         WM_TT(TK_TEXT_GEMM, g16(hb, rows, H, m->w116 + (size_t)l * F * H, F, fb, m->b1 + (size_t)l * F,
                                 nullptr, nullptr, nullptr, 1, true));

@@ -86,6 +86,26 @@ def test_codebert_backbone(wm):
     print(f"  max rel {rel.max():.2e}", flush=True)
 
 
+@pytest.mark.parametrize("prec,hidden,heads,window", [
+    ("fp32", 96, 1, 64), ("bf16", 96, 1, 64), ("bf16", 64, 2, 544), ("fp32", 64, 2, 544), ("fp32", 192, 3, 160)])
+def test_other_shapes(wm, prec, hidden, heads, window):
+    """Head widths without fused attention (96) and windows past the fused bf16
+    one (general path), and the float32 fused attention over several key and
+    query blocks with a ragged last one."""
+    w = synth.TextWorkload(name="other", S=5, vocab=300, hidden=hidden, heads=heads, ffn=160, layers=2,
+                           window=window, stride=window // 2, d=32, len_lo=0, len_hi=3 * window)
+    W = synth.make_text_weights(w, 81)
+    model = wm.TextModel(w, W, precision=prec)
+    tokens, off = synth.make_programs(w, 83)
+    print(f"[text] other {prec} {hidden}/{heads} window {window} lens={np.diff(off)}", flush=True)
+    g = run(wm, model, tokens, off)
+    ref = TE.encode(W, programs_of(tokens, off), w.window, w.stride, w.heads, prec)
+    rel = latent_rel(g, ref)
+    assert rel.max() <= TOL[prec], f"z0 rel err {rel.max():.3e}"
+    if prec == "fp32":          # six plane products: float32 accuracy, far inside the tolerance
+        assert rel.max() <= 5e-6, f"z0 rel err {rel.max():.3e}"
+
+
 @pytest.mark.parametrize("S,n", [(3, 70), (40, 190), (200, 190)])
 def test_product_tiles(wm, S, n):
     """Each tile size of the bf16 products (64 x 64, 128 x 64 and 256 x 256 tiles
