@@ -648,7 +648,7 @@ wm_status wm_rollout_loss(const wm_model* model, const float* z0, const int32_t*
   } else {
     WM_TIMED(TK_BUCKET, st, launch_row_offsets(lens, 0, T_max, io.off, st));
   }
-  WM_TIMED(TK_LOSS, st, launch_step_loss(io.P, targets, negatives, n_neg, lens, io.off, B, T_max,
+  WM_TIMED(TK_LOSS, st, launch_step_loss(io.P, targets, negatives, n_neg, io.row_src, io.off, B, T_max,
                                           m.dims.d, lam, gamma, io.SD, fptr(L.lrow), loss, total, st));
   if (!grads) return ok();
   if (B > 0) WM_TIMED(TK_TRAIN_BWD, st, launch_train_bwd(m, io, st));

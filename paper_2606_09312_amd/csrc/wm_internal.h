@@ -76,7 +76,7 @@ bool have_train_kernels(int prec, int d, int e);
 hipError_t launch_row_offsets(const int32_t* lens, int B, int T_max, int32_t* off, hipStream_t st);
 hipError_t launch_train_fwd(const DevModel& m, const TrainIO& io, hipStream_t st);
 hipError_t launch_step_loss(const float* P, const float* targets, const float* negatives, int NN,
-                            const int32_t* lens, const int32_t* off, int B, int T_max, int D,
+                            const int32_t* row_src, const int32_t* off, int B, int T_max, int D,
                             float lam, float gamma, float* SD, float* lrow, float* loss,
                             float* total, hipStream_t st);
 hipError_t launch_train_bwd(const DevModel& m, const TrainIO& io, hipStream_t st);

@@ -2969,77 +2969,90 @@ __global__ __launch_bounds__(64 * WAVES, 1) void train_fwd_kernel(const TrainArg
 }
 
 // Per-step loss and its gradient with respect to the prediction: one
-// wavefront per (candidate, step) slot; lane L holds features 4L..4L+3 (and
-// +256, ...), so the prediction, the target and up to LOSS_NEG negatives
-// are read in one pass of independent 16-byte loads.  The hardest negative
+// wavefront per valid step, walking the compact rows (a fixed grid strides
+// over them, so padding slots cost nothing); lane L holds features 4L..4L+3
+// (d <= 256).  The prediction, the target and up to LOSS_NEG negatives are one
+// batch of independent 16-byte loads and stay in registers until the gradient
+// is formed; the distances' lane sums run side by side.  The hardest negative
 // is the nearest (first one on ties); a zero distance contributes a zero
 // gradient.  targets / negatives are indexed by slot, P / SD / lrow by
-// compact row.
+// compact row.  HBM bounds it: 8192 long schedules with 4 negatives (1.3 GB)
+// 650 -> 335 us (one wavefront per slot, padding included, negatives read
+// again for the gradient).
 constexpr int LOSS_NEG = 8;          // negatives per pass
+constexpr int LOSS_BLOCKS = 2048;    // 8 workgroups of 4 wavefronts per compute unit
+
+// N lane sums side by side.
+template <int N>
+__device__ __forceinline__ void wave_sums(float (&x)[N]) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1)
+#pragma unroll
+    for (int q = 0; q < N; ++q) x[q] += __shfl_xor(x[q], m);
+}
+
+// NNC > 0: exactly NNC <= LOSS_NEG negatives; 0: any number, LOSS_NEG a pass.
+template <int NNC>
 __global__ __launch_bounds__(256) void loss_kernel(const float* __restrict__ P,
                                                    const float* __restrict__ targets,
                                                    const float* __restrict__ negatives, int NN,
-                                                   const int32_t* __restrict__ lens,
-                                                   const int32_t* __restrict__ off, int B,
-                                                   int T_max, int D, float lam, float gamma,
+                                                   const int32_t* __restrict__ row_src,
+                                                   const int32_t* __restrict__ off, int B, int D,
+                                                   float lam, float gamma,
                                                    float* __restrict__ SD, float* __restrict__ lrow) {
+  constexpr int NQ = NNC > 0 ? NNC : LOSS_NEG;
   const int lane = threadIdx.x & 63;
-  const long long slot = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (slot >= (long long)B * T_max) return;            // whole wavefront leaves together
-  const int i = (int)(slot / T_max), t = (int)(slot - (long long)i * T_max);
-  if (t >= clampi(lens[i], 0, T_max)) return;
-  const size_t row = (size_t)off[i] + t;
-  const f32x4* p4 = reinterpret_cast<const f32x4*>(P + row * D);
-  const f32x4* y4 = reinterpret_cast<const f32x4*>(targets + slot * D);
-  const int D4 = D / 4;
-  float m = 0.0f;
-  for (int c = lane; c < D4; c += 64) {
-    const f32x4 v = p4[c] - y4[c];
-    m += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-  }
-  const float match = wave_sum(m);
-  const float dpos = sqrtf(match);
-  float dmin = INFINITY;
-  int hard = 0;
-  for (int q0 = 0; q0 < NN; q0 += LOSS_NEG) {
-    float sq[LOSS_NEG];
+  const int rows = off[B], D4 = D / 4;
+  const bool on = lane < D4;
+  const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int row = blockIdx.x * 4 + (threadIdx.x >> 6); row < rows; row += 4 * LOSS_BLOCKS) {
+    const size_t slot = (size_t)__builtin_amdgcn_readfirstlane(row_src[row]);
+    const f32x4* n4 = reinterpret_cast<const f32x4*>(negatives + slot * NN * D);
+    f32x4 pv = zero, yv = zero;
+    if (on) {
+      pv = reinterpret_cast<const f32x4*>(P + (size_t)row * D)[lane];
+      yv = reinterpret_cast<const f32x4*>(targets + slot * D)[lane];
+    }
+    const f32x4 diff = pv - yv;
+    f32x4 best = zero;                       // prediction minus the hardest negative
+    float dmin = INFINITY, match = 0.0f;
+    for (int q0 = 0; q0 < (NNC > 0 ? 1 : NN); q0 += LOSS_NEG) {
+      f32x4 dn[NQ];
+      float sq[NQ + 1];
 #pragma unroll
-    for (int q = 0; q < LOSS_NEG; ++q) sq[q] = 0.0f;
-    for (int c = lane; c < D4; c += 64) {
-      const f32x4 pv = p4[c];
+      for (int q = 0; q < NQ; ++q) {
+        dn[q] = zero;
+        if (on && (NNC > 0 || q0 + q < NN)) dn[q] = pv - n4[(size_t)(q0 + q) * D4 + lane];
+      }
 #pragma unroll
-      for (int q = 0; q < LOSS_NEG; ++q) {
-        if (q0 + q < NN) {
-          const f32x4 v = pv - reinterpret_cast<const f32x4*>(negatives + (slot * NN + q0 + q) * D)[c];
-          sq[q] += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+      for (int q = 0; q < NQ; ++q)
+        sq[q] = dn[q][0] * dn[q][0] + dn[q][1] * dn[q][1] + dn[q][2] * dn[q][2] + dn[q][3] * dn[q][3];
+      sq[NQ] = diff[0] * diff[0] + diff[1] * diff[1] + diff[2] * diff[2] + diff[3] * diff[3];
+      wave_sums(sq);
+      match = sq[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const float dq = sqrtf(sq[q]);
+        if ((NNC > 0 || q0 + q < NN) && dq < dmin) {
+          dmin = dq;
+          best = dn[q];
         }
       }
     }
-#pragma unroll
-    for (int q = 0; q < LOSS_NEG; ++q) {
-      if (q0 + q < NN) {
-        const float dq = sqrtf(wave_sum(sq[q]));
-        if (dq < dmin) { dmin = dq; hard = q0 + q; }
-      }
-    }
-  }
-  const float hinge = dpos - dmin + gamma;
-  const bool act = hinge > 0.0f;
-  if (lane == 0) lrow[row] = lam * match + (1.0f - lam) * (act ? hinge : 0.0f);
-  const float ip = dpos > 0.0f ? 1.0f / dpos : 0.0f;
-  const float in = dmin > 0.0f ? 1.0f / dmin : 0.0f;
-  const f32x4* n4 = reinterpret_cast<const f32x4*>(negatives + (slot * NN + hard) * D);
-  f32x4* g4 = reinterpret_cast<f32x4*>(SD + row * D);
-  const float wr = act ? (1.0f - lam) : 0.0f;
-  for (int c = lane; c < D4; c += 64) {
-    const f32x4 pv = p4[c], diff = pv - y4[c], dn = pv - n4[c];
+    const float dpos = sqrtf(match);
+    const float hinge = dpos - dmin + gamma;
+    const bool act = hinge > 0.0f;
+    if (lane == 0) lrow[row] = lam * match + (1.0f - lam) * (act ? hinge : 0.0f);
+    const float ip = dpos > 0.0f ? 1.0f / dpos : 0.0f;
+    const float in = dmin > 0.0f ? 1.0f / dmin : 0.0f;
+    const float wr = act ? (1.0f - lam) : 0.0f;
     f32x4 g;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       g[k] = lam * 2.0f * diff[k];
-      if (act) g[k] += wr * (diff[k] * ip - dn[k] * in);
+      if (act) g[k] += wr * (diff[k] * ip - best[k] * in);
     }
-    g4[c] = g;
+    if (on) reinterpret_cast<f32x4*>(SD + (size_t)row * D)[lane] = g;
   }
 }
 
@@ -4840,13 +4853,33 @@ hipError_t launch_rollout_de(const DevModel& m, const RollArgs& a, int tiles, in
   return launch_rollout_t<PR, D, E, 1, NORM>(m, a, blocks, st);
 }
 
-// Narrow tiles (16 candidates) for batches of at most two such tiles per
-// compute unit: d = 256, e = 64 (8 wavefronts; bf16 with hidden widths 512
-// and 1024, fp32 with 512) and d = 64, e = 32 (2 wavefronts, hidden width
-// 128), both transition forms.  Up to 512 tiles they beat one 32-candidate
-// tile per compute unit: candidates are sorted longest first, so the
-// second tiles a compute unit takes are the short ones.
-constexpr int NARROW_MAX_TILES = 512;
+// Batches that run in narrow tiles (16 candidates): d = 256, e = 64 (8
+// wavefronts; bf16 with hidden widths 512 and 1024, fp32 with 512) and d = 64,
+// e = 32 (2 wavefronts, hidden width 128), both transition forms.  A compute
+// unit takes the tiles one after another, longest first, so their time grows
+// with the batch (the steps of all candidates), while a 32-candidate tile per
+// SIMD takes as long as its longest sequence from one tile to 1024 of them (B =
+// 32,768), then twice that.  Lengths uniform in 1..48, narrow / other, us:
+//   bf16 H = 512          B = 12,000 346 / 1237, 32,768 893 / 1200, 49,152 1280 / 1257
+//        paper form       24,000 991 / 1272, 32,768 1307 / 1285
+//   bf16 H = 1024         32,768 1919 / 2099, 49,152 2762 / 2233
+//        paper form       24,000 1737 / 2114, 32,768 2295 / 2167
+//   fp32 H = 512          12,000 1647 / 7714, 65,536 7427 / 8207 (paper form 8433 / 9192)
+//   d = 64 bf16           12,000 110 / 250, 65,536 274 / 312 (paper form 335 / 341)
+//   d = 64 fp32           12,000 278 / 839, 65,536 716 / 1077
+// (score included).  The training kernels store every step's activations and
+// meet earlier (T = 32, forward, loss, backward and gradients): bf16 residual
+// H = 512 12,000 1703 / 1820, 16,384 2248 / 2239, H = 1024 2872 / 2900, 3692 / 3560;
+// paper form 16,384 2663 / 2641, H = 1024 4243 / 4359; fp32 16,384 5244 / 5553.
+int narrow_max_candidates(const DevModel& m, bool train) {
+  constexpr int NO_LIMIT = 0x7FFFFFFF;
+  if (m.prec == WM_FP32) return NO_LIMIT;
+  const bool l2 = m.dims.norm == WM_NORM_L2;
+  if (train) return l2 ? 16000 : 12288;
+  if (m.dims.d == 64) return 65536;
+  if (m.dims.trans_hidden <= 512) return l2 ? 30720 : 45056;
+  return l2 ? 28672 : 34816;
+}
 template <class NP, int NC, bool NORM, bool TRAIN = false, bool SCORE = false, int D = 256, int E = 64,
           int W = 8>
 hipError_t launch_rollout_narrow(const DevModel& m, RollArgs a, int tiles, hipStream_t st) {
@@ -4885,7 +4918,8 @@ hipError_t launch_rollout(const DevModel& m, const float* z0, const int2* perm,
   const bool norm = m.dims.norm == WM_NORM_L2;
   *phi_done = false;
   const int ntiles = (B + 15) / 16;
-  if (d == 256 && e == 64 && m.trans_n && B > 0 && ntiles <= NARROW_MAX_TILES) {
+  const bool narrow_ok = m.trans_n && B > 0 && B <= narrow_max_candidates(m, false);
+  if (d == 256 && e == 64 && narrow_ok) {
     const int NC = m.dims.trans_hidden / 32;
     // scores fused: phi sums present, the narrow cost blob, at most two
     // hardware vectors of at most 32 features
@@ -4914,7 +4948,7 @@ hipError_t launch_rollout(const DevModel& m, const float* z0, const int2* perm,
     if (prec == WM_BF16 && NC == 32) return norm ? narrow(NarrowBF16{}, I32{}, BT{}) : narrow(NarrowBF16{}, I32{}, BF{});
     if (prec == WM_FP32 && NC == 16) return norm ? narrow(NarrowF32{}, I16{}, BT{}) : narrow(NarrowF32{}, I16{}, BF{});
   }
-  if (d == 64 && e == 32 && m.trans_n && B > 0 && ntiles <= NARROW_MAX_TILES && m.dims.trans_hidden == 128) {
+  if (d == 64 && e == 32 && narrow_ok && m.dims.trans_hidden == 128) {
     *phi_done = phi != nullptr;
     if (prec == WM_BF16)
       return norm ? launch_rollout_narrow<NarrowBF16, 4, true, false, false, 64, 32, 2>(m, a, ntiles, st)
@@ -5161,10 +5195,9 @@ hipError_t launch_train_fwd(const DevModel& m, const TrainIO& io, hipStream_t st
   const TrainArgs a = train_args(m, io);
   const int tiles = (io.B + 31) / 32;
   const bool norm = m.dims.norm == WM_NORM_L2;
-  // both transition forms, up to NARROW_MAX_TILES = 512 tiles of 16 candidates
-  // (two per compute unit): narrow tiles
   const int ntiles = (io.B + 15) / 16;
-  if (m.dims.d == 256 && m.dims.embed_dim == 64 && m.trans_n && m.trans_nt && ntiles <= NARROW_MAX_TILES) {
+  const bool narrow_ok = m.trans_n && m.trans_nt && io.B <= narrow_max_candidates(m, true);
+  if (m.dims.d == 256 && m.dims.embed_dim == 64 && narrow_ok) {
     const int NC = m.dims.trans_hidden / 32;
     const RollArgs r = train_roll_args(m, io, norm);
     if (norm) {
@@ -5177,8 +5210,7 @@ hipError_t launch_train_fwd(const DevModel& m, const TrainIO& io, hipStream_t st
       if (m.prec == WM_FP32 && NC == 16) return launch_rollout_narrow<NarrowF32, 16, false, true>(m, r, ntiles, st);
     }
   }
-  if (m.dims.d == 64 && m.dims.embed_dim == 32 && m.dims.trans_hidden == 128 && m.trans_n && m.trans_nt &&
-      ntiles <= NARROW_MAX_TILES) {
+  if (m.dims.d == 64 && m.dims.embed_dim == 32 && m.dims.trans_hidden == 128 && narrow_ok) {
     const RollArgs r = train_roll_args(m, io, norm);
     if (m.prec == WM_BF16)
       return norm ? launch_rollout_narrow<NarrowBF16, 4, true, true, false, 64, 32, 2>(m, r, ntiles, st)
@@ -5233,10 +5265,9 @@ hipError_t launch_train_bwd(const DevModel& m, const TrainIO& io, hipStream_t st
   const TrainArgs a = train_args(m, io);
   const int tiles = (io.B + 31) / 32;
   const bool norm = m.dims.norm == WM_NORM_L2;
-  // both transition forms, up to NARROW_MAX_TILES = 512 tiles of 16 candidates
-  // (two per compute unit): narrow tiles
   const int ntiles = (io.B + 15) / 16;
-  if (m.dims.d == 256 && m.dims.embed_dim == 64 && m.trans_nt && ntiles <= NARROW_MAX_TILES) {
+  const bool narrow_ok = m.trans_n && m.trans_nt && io.B <= narrow_max_candidates(m, true);
+  if (m.dims.d == 256 && m.dims.embed_dim == 64 && narrow_ok) {
     const int NC = m.dims.trans_hidden / 32;
     if (norm) {
       if (m.prec == WM_BF16 && NC == 16) return launch_train_bwd_narrow<NarrowBF16, 16, true>(m, a, ntiles, st);
@@ -5248,8 +5279,7 @@ hipError_t launch_train_bwd(const DevModel& m, const TrainIO& io, hipStream_t st
       if (m.prec == WM_FP32 && NC == 16) return launch_train_bwd_narrow<NarrowF32, 16, false>(m, a, ntiles, st);
     }
   }
-  if (m.dims.d == 64 && m.dims.embed_dim == 32 && m.dims.trans_hidden == 128 && m.trans_nt &&
-      ntiles <= NARROW_MAX_TILES) {
+  if (m.dims.d == 64 && m.dims.embed_dim == 32 && m.dims.trans_hidden == 128 && narrow_ok) {
     if (m.prec == WM_BF16)
       return norm ? launch_train_bwd_narrow<NarrowBF16, 4, true, 64, 32, 2>(m, a, ntiles, st)
                   : launch_train_bwd_narrow<NarrowBF16, 4, false, 64, 32, 2>(m, a, ntiles, st);
@@ -5279,13 +5309,24 @@ hipError_t launch_row_offsets(const int32_t* lens, int B, int T_max, int32_t* of
 }
 
 hipError_t launch_step_loss(const float* P, const float* targets, const float* negatives, int NN,
-                            const int32_t* lens, const int32_t* off, int B, int T_max, int D,
+                            const int32_t* row_src, const int32_t* off, int B, int T_max, int D,
                             float lam, float gamma, float* SD, float* lrow, float* loss,
                             float* total, hipStream_t st) {
+  if (D > 256) return hipErrorInvalidValue;
   const long long slots = (long long)B * T_max;
-  if (slots > 0)
-    hipLaunchKernelGGL(loss_kernel, dim3((unsigned)((slots + 3) / 4)), dim3(256), 0, st, P, targets,
-                       negatives, NN, lens, off, B, T_max, D, lam, gamma, SD, lrow);
+  if (slots > 0) {
+    auto go = [&](auto kern) {
+      const long long blocks = (slots + 3) / 4;
+      hipLaunchKernelGGL(kern, dim3((unsigned)(blocks < LOSS_BLOCKS ? blocks : LOSS_BLOCKS)), dim3(256), 0, st, P,
+                         targets, negatives, NN, row_src, off, B, D, lam, gamma, SD, lrow);
+    };
+    // the usual counts with their loads unrolled exactly
+    if (NN == 1) go(loss_kernel<1>);
+    else if (NN == 2) go(loss_kernel<2>);
+    else if (NN == 4) go(loss_kernel<4>);
+    else if (NN == 8) go(loss_kernel<8>);
+    else go(loss_kernel<0>);
+  }
   if (B > 0)
     hipLaunchKernelGGL(loss_sum_kernel, dim3((B + 255) / 256), dim3(256), 0, st, lrow, off, B, loss);
   if (total) hipLaunchKernelGGL(loss_total_kernel, dim3(1), dim3(1024), 0, st, loss, B, total);

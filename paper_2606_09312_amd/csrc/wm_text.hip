@@ -985,15 +985,28 @@ __global__ __launch_bounds__(256, 2) void attention32_kernel(const float* __rest
 #pragma unroll
   for (int b = 0; b < DB; ++b) oacc[b] = f32x16{};
   float mx = -INFINITY, sum = 0.0f;
+  constexpr int NU = KB * (DH / 4) / 256;              // 16-byte units per thread and matrix
+  f32x4 kn[NU], vn[NU];                                // the next block, loaded under this one's products
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+      const int u = tid + 256 * i, key = u / (DH / 4), d4 = (u % (DH / 4)) * 4;
+      const float* src = base + (size_t)min(k0 + key, len - 1) * 3 * H + d4;   // keys past the end are masked
+      kn[i] = *reinterpret_cast<const f32x4*>(src + H);
+      vn[i] = *reinterpret_cast<const f32x4*>(src + 2 * H);
+    }
+  };
+  load(0);
   for (int k0 = 0; k0 < len; k0 += KB) {
     __syncthreads();
-    for (int u = tid; u < KB * (DH / 4); u += 256) {
-      const int key = u / (DH / 4), d4 = (u % (DH / 4)) * 4;
-      const float* src = base + (size_t)min(k0 + key, len - 1) * 3 * H + d4;   // keys past the end are masked
-      *reinterpret_cast<f32x4*>(Ks + key * KW + d4) = *reinterpret_cast<const f32x4*>(src + H);
-      *reinterpret_cast<f32x4*>(Vs + key * VW + d4) = *reinterpret_cast<const f32x4*>(src + 2 * H);
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+      const int u = tid + 256 * i, key = u / (DH / 4), d4 = (u % (DH / 4)) * 4;
+      *reinterpret_cast<f32x4*>(Ks + key * KW + d4) = kn[i];
+      *reinterpret_cast<f32x4*>(Vs + key * VW + d4) = vn[i];
     }
     __syncthreads();
+    if (k0 + KB < len) load(k0 + KB);
 #pragma unroll
     for (int kb = 0; kb < KB / 32; ++kb) {
       const int kbase = k0 + 32 * kb;
@@ -1026,14 +1039,15 @@ __global__ __launch_bounds__(256, 2) void attention32_kernel(const float* __rest
       sum = fmaf(sum, f, bs);
       mx = nm;
 #pragma unroll
-      for (int b = 0; b < DB; ++b) {
+      for (int b = 0; b < DB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[b][r] *= f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float p = s[r];
+      for (int r = 0; r < 16; ++r) {
+        const float p = s[r];
+#pragma unroll
+        for (int b = 0; b < DB; ++b)
           oacc[b] = FP::mfma(Vs[(32 * kb + acc_row(h, r)) * VW + 32 * b + cl], p, oacc[b]);
-        }
       }
     }
   }

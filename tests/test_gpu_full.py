@@ -161,3 +161,31 @@ def test_short_sequences_tight(wm, name, norm, B):
     assert srel.max() <= tol_s, f"score rel err {srel.max():.3e}"
     check_topk_self_consistent(g["idx"], g["val"], g["scores"], I["seg_off"], k)
     check_topk_vs_oracle(g["idx"], ref["scores"], I["seg_off"], k, tol_s)
+
+
+@pytest.mark.parametrize("prec,norm,H,B", [
+    ("bf16", "none", 512, 12000 + 5), ("bf16", "l2", 512, 20000 + 1), ("bf16", "none", 1024, 16384 + 3),
+    ("fp32", "none", 512, 9000 + 7),
+    # hidden widths without narrow tiles: one, two and four wavefronts per workgroup
+    ("bf16", "none", 320, 9000), ("bf16", "l2", 320, 16384 + 40), ("bf16", "none", 320, 33000),
+    ("fp32", "none", 320, 16384 + 40)])
+def test_batches_between_one_round_and_one_tile_per_simd(wm, prec, norm, H, B):
+    """Batches past 8192 candidates in narrow tiles, and the persistent kernel at
+    the hidden widths that have none, on one- and two-step sequences: batch-mean
+    errors against the oracle (float32: the stated tolerance)."""
+    import dataclasses
+    base = dataclasses.replace(synth.workload("ansor_round"), H=H)
+    w = synth.scaled(base, B=B, len_lo=0, len_hi=2, T_max=2)
+    print(f"[mid] {prec} {norm} H={H} B={B}", flush=True)
+    W = synth.make_weights(w, 1000)
+    model = wm.Model(wm.model_dims(w), W, precision=prec, norm=norm)
+    I = synth.make_inputs(w, 4300 + H, pad="garbage")
+    g = run_evaluate(model, w, I, base.k)
+    assert g["status"] == 0
+    ref = oracle_full(W, I, prec, base.k, norm=norm)
+    tol_z, tol_s = bounds(prec, (0.0, 0.0))
+    rel = latent_rel(g["zT"], ref["zT"])
+    srel = score_rel(g["scores"], ref["scores"], I["seg_off"])
+    assert rel.max() <= tol_z and srel.max() <= tol_s, (rel.max(), srel.max())
+    assert rel.mean() <= SHORT_MEAN and srel.mean() <= SHORT_MEAN, (rel.mean(), srel.mean())
+    check_topk_self_consistent(g["idx"], g["val"], g["scores"], I["seg_off"], base.k)
