@@ -150,6 +150,29 @@ __device__ __forceinline__ f32x16 load_acc(const float* row, int h) {
   return v;
 }
 
+// The weight gradients' product operands X and G of element i.. in the compact
+// rows, stored as the products take them: bf16 kernels (BF) as bf16 (the
+// same values in half the bytes), float32 kernels as float32.
+template <bool BF>
+__device__ __forceinline__ void store_op(float* base, size_t i, float v) {
+  if constexpr (BF) reinterpret_cast<__bf16*>(base)[i] = (__bf16)v;
+  else base[i] = v;
+}
+template <bool BF>
+__device__ __forceinline__ void store_op4(float* base, size_t i, float a, float b, float c, float d) {
+  if constexpr (BF) {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(base) + i) = bf16x4{(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
+  } else {
+    *reinterpret_cast<f32x4*>(base + i) = f32x4{a, b, c, d};
+  }
+}
+template <bool BF>
+__device__ __forceinline__ void store_op_acc(float* base, size_t i, const f32x16& v, int h) {   // as store_acc
+#pragma unroll
+  for (int q = 0; q < 4; ++q) store_op4<BF>(base, i + acc_row(h, 4 * q), v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+}
+
 __device__ __forceinline__ u32x4 lds_group(const uint8_t* base, int group, int lane) {
   return *reinterpret_cast<const u32x4*>(base + group * 1024 + lane * 16);
 }

@@ -1309,9 +1309,9 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
       if (do_phi && (q / G) % W == w) phi_add(q, ev);
       if constexpr (TRAIN) {
         if ((q / G) % W == w && s < len) {
-          float* xo = a.X + (row0 + s) * IN + D + KF * q + SL * h;
+          const size_t xo = (row0 + s) * IN + D + KF * q + SL * h;
 #pragma unroll
-          for (int j = 0; j < SL; ++j) xo[j] = op_value<PR>(ev[j]);
+          for (int j = 0; j < SL; ++j) store_op<PR::G == 1>(a.X, xo + j, ev[j]);
         }
       }
     }
@@ -1333,9 +1333,9 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
         if (do_phi) phi_add(q, ev);
         if constexpr (TRAIN) {
           if (s < len) {
-            float* xo = a.X + (row0 + s) * IN + D + KF * q + SL * h;
+            const size_t xo = (row0 + s) * IN + D + KF * q + SL * h;
 #pragma unroll
-            for (int j = 0; j < SL; ++j) xo[j] = op_value<PR>(ev[j]);
+            for (int j = 0; j < SL; ++j) store_op<PR::G == 1>(a.X, xo + j, ev[j]);
           }
         }
       }
@@ -1477,12 +1477,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
     if constexpr (TRAIN) {
       if (active) {            // X = [z; e]: the owned latent blocks (e: embed_share)
 #pragma unroll
-        for (int bq = 0; bq < NBW; ++bq) {
-          f32x16 v;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) v[r] = op_value<PR>(zq[bq][r]);
-          store_acc(a.X + row * IN + 32 * (w * NBW + bq), v, h);
-        }
+        for (int bq = 0; bq < NBW; ++bq) store_op_acc<PR::G == 1>(a.X, row * IN + 32 * (w * NBW + bq), zq[bq], h);
         if (w == 0 && h == 0) a.row_src[row] = cand * a.T_max + t;
       }
     }
@@ -1528,7 +1523,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
             for (int q = 0; q < 8; ++q) gp[q] = PR::pack2(gv[2 * q], gv[2 * q + 1], amask);
             if (active) {
               store_acc(a.A + row * a.H + 32 * c, acc, h);
-              store_acc(a.G + row * a.H + 32 * c, gv, h);
+              store_op_acc<PR::G == 1>(a.G, row * a.H + 32 * c, gv, h);
             }
           } else {
 #pragma unroll
@@ -1894,11 +1889,9 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
     for (int j = 0; j < 8; ++j) ev[j] = (ev[j] + t_pb[f0 + j]) * af;
     if constexpr (TRAIN) {
       if (q == w && af != 0.0f) {     // the owner stores e of an active step
-        float* xo = a.X + (row0 + s_cur) * IN + D + f0;
-        const f32x4n lo = {NP::op(ev[0]), NP::op(ev[1]), NP::op(ev[2]), NP::op(ev[3])};
-        const f32x4n hi = {NP::op(ev[4]), NP::op(ev[5]), NP::op(ev[6]), NP::op(ev[7])};
-        *reinterpret_cast<f32x4n*>(xo) = lo;
-        *reinterpret_cast<f32x4n*>(xo + 4) = hi;
+        const size_t xo = (row0 + s_cur) * IN + D + f0;
+        store_op4<GPK == 1>(a.X, xo, ev[0], ev[1], ev[2], ev[3]);
+        store_op4<GPK == 1>(a.X, xo + 4, ev[4], ev[5], ev[6], ev[7]);
       }
     }
     if (do_phi && q == w) {
@@ -2092,10 +2085,8 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
     if constexpr (TRAIN) {
       if (active) {                  // X = [z; e]: the owned latent blocks (e: embed_share)
 #pragma unroll
-        for (int bq = 0; bq < NBW; ++bq) {
-          const f32x4n v = {NP::op(zq[bq][0]), NP::op(zq[bq][1]), NP::op(zq[bq][2]), NP::op(zq[bq][3])};
-          *reinterpret_cast<f32x4n*>(a.X + row * IN + 16 * (w * NBW + bq) + 4 * g) = v;
-        }
+        for (int bq = 0; bq < NBW; ++bq)
+          store_op4<GPK == 1>(a.X, row * IN + 16 * (w * NBW + bq) + 4 * g, zq[bq][0], zq[bq][1], zq[bq][2], zq[bq][3]);
         if (w == 0 && g == 0) a.row_src[row] = cand * a.T_max + t;
       }
     }
@@ -2116,11 +2107,9 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
       if constexpr (TRAIN) {
         if (active) {
 #pragma unroll
-          for (int rb2 = 0; rb2 < 2; ++rb2) {
-            const f32x4n gq = {NP::op(gv[4 * rb2]), NP::op(gv[4 * rb2 + 1]), NP::op(gv[4 * rb2 + 2]),
-                               NP::op(gv[4 * rb2 + 3])};
-            *reinterpret_cast<f32x4n*>(a.G + row * a.H + 32 * c + 16 * rb2 + 4 * g) = gq;
-          }
+          for (int rb2 = 0; rb2 < 2; ++rb2)
+            store_op4<GPK == 1>(a.G, row * a.H + 32 * c + 16 * rb2 + 4 * g, gv[4 * rb2], gv[4 * rb2 + 1],
+                                gv[4 * rb2 + 2], gv[4 * rb2 + 3]);
         }
       }
       NP::store(gbuf, c, lane, NP::gfrag(gv, amask));
@@ -2684,9 +2673,9 @@ struct TrainArgs {
   const int32_t* lens;
   const int32_t* off;       // [B+1] row offsets
   int32_t* row_src;         // [R]  i * T_max + t of each row
-  float* X;                 // [R][D+E]
+  float* X;                 // [R][D+E] (bf16: bf16 elements)
   float* A;                 // [R][H]   pre-activations; the backward overwrites them with dA
-  float* G;                 // [R][H]
+  float* G;                 // [R][H]   (bf16: bf16 elements)
   float* P;                 // [R][D]   predicted states
   float* SD;                // [R][D]   dL/dp seeds; the backward overwrites them with delta_{t+1}
   float* DE;                // [R][E]   gradient reaching the step's embedding
@@ -2821,7 +2810,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void train_fwd_kernel(const TrainArg
           u[p] = log2f((float)pv);
         }
     }
-    float* xrow = a.X + row * IN;
+    const size_t xrow = row * IN;
     Frag xe[NE];
 #pragma unroll
     for (int q = 0; q < NE; ++q) {
@@ -2840,7 +2829,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void train_fwd_kernel(const TrainArg
       xe[q] = PR::cvt(ev);
       if (active) {
 #pragma unroll
-        for (int j = 0; j < SL; ++j) xrow[D + f0 + j] = op_value<PR>(ev[j]);
+        for (int j = 0; j < SL; ++j) store_op<PR::G == 1>(a.X, xrow + D + f0 + j, ev[j]);
       }
     }
     // paper form: z' = z - (v.z / v.v) v with v = Wh e (two passes of V^T =
@@ -2890,12 +2879,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void train_fwd_kernel(const TrainArg
     }
     if (active) {
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        f32x16 v;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) v[r] = op_value<PR>(zacc[b][r]);
-        store_acc(xrow + 32 * b, v, h);
-      }
+      for (int b = 0; b < NB; ++b) store_op_acc<PR::G == 1>(a.X, xrow + 32 * b, zacc[b], h);
     }
     for (int c = 0; c < NC; ++c) {
       const int cn = c + 1 < NC ? c + 1 : 0;
@@ -2926,7 +2910,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void train_fwd_kernel(const TrainArg
             for (int q = 0; q < 8; ++q) gp[q] = PR::pack2(gv[2 * q], gv[2 * q + 1], amask);
             if (active) {
               store_acc(a.A + row * a.H + 32 * c, acc, h);
-              store_acc(a.G + row * a.H + 32 * c, gv, h);
+              store_op_acc<PR::G == 1>(a.G, row * a.H + 32 * c, gv, h);
             }
           }
         } else {
@@ -3899,19 +3883,21 @@ __global__ __launch_bounds__(64 * W, 1) void train_bwd_narrow_kernel(const Train
   }
 }
 
-// Weight gradients as split-K products over the compact rows, two problems
-// per launch (dW2 = sum R(delta) (x) g, dW1 = sum R(dA) (x) x):
-//   part[split][m][n] = sum over the split's rows r of op(A[r][m]) * op(B[r][n])
+// Weight gradients as split-K products over the compact rows, two or three
+// problems per launch (dW2 = sum R(delta) (x) g, dW1 = sum R(dA) (x) x, paper
+// form dWh = sum R(dv) (x) R(e)):
+//   part[split][m][n] = sum over the split's rows r of op(A[r][m]) * B[r][n]
 // with the column sums of A (unrounded: db2, db1) on the side.  Workgroup =
 // 4 wavefronts on a 128 x 128 output tile, each wavefront 64 x 64 (2 x 2
-// matrix-core tiles); 32 rows per stage: every thread loads 8 consecutive
-// rows of one column (coalesced across the wavefront), rounds them as
-// product operands and writes them to LDS transposed (column-major, rows
-// contiguous), so each lane's operand fragment is one 16-byte LDS read.  The
-// next stage's loads are in flight during the current stage's products.
+// matrix-core tiles); 32 rows per stage, written to LDS transposed
+// (column-major, rows contiguous), so each lane's operand fragment is one
+// 16-byte LDS read.  The next stage's loads are in flight during the current
+// stage's products.  Workgroups are dealt to the 8 XCDs in turn: every tile of
+// split s runs on XCD s mod 8, so the split's rows come from HBM once per XCD
+// and the other tiles' re-reads hit that XCD's L2.
 struct WgradProblem {
   const float* A;           // [rows][lda], columns [0, M)
-  const float* Bm;          // [rows][ldb], columns [0, N)
+  const float* Bm;          // [rows][ldb], columns [0, N) (bf16 kernel: bf16 elements)
   float* part;              // [splits][M][N]
   float* colsum;            // [splits][M] (may be null)
   int M, N, lda, ldb, tiles_n, tiles;
@@ -3923,39 +3909,156 @@ struct WgradArgs {
 };
 constexpr int WG_T = 128, WG_KC = 32;
 
-template <class PR>
-__global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
-  constexpr int KF = PR::KF, SL = PR::SL;
-  constexpr bool BF = PR::G == 1;
-  using Elem = typename std::conditional<BF, __bf16, float>::type;
-  constexpr int LDW = WG_KC + (BF ? 8 : 4);               // padded LDS row (elements)
-  __shared__ __attribute__((aligned(16))) Elem As[WG_T * LDW];
-  __shared__ __attribute__((aligned(16))) Elem Bs[WG_T * LDW];
-  __shared__ float csum[WG_T];
-  // Workgroups are dealt to the 8 XCDs in turn: every tile of split s runs
-  // on XCD s mod 8, so the split's rows come from HBM once per XCD and the
-  // other tiles' re-reads hit that XCD's L2.
+// Problem, output tile and rows of a workgroup (false: no split left for it).
+__device__ __forceinline__ bool wgrad_place(const WgradArgs& a, WgradProblem& pr, int& m0, int& n0, int& split, int& r0,
+                                            int& r1) {
   const int tiles_all = a.p0.tiles + a.p1.tiles + a.p2.tiles;
   const int xcd = blockIdx.x % 8, k8 = blockIdx.x / 8;
   const int tile_id = k8 % tiles_all;
-  const int split = (k8 / tiles_all) * 8 + xcd;
-  if (split >= a.splits) return;
+  split = (k8 / tiles_all) * 8 + xcd;
+  if (split >= a.splits) return false;
   const int which = tile_id < a.p0.tiles ? 0 : (tile_id < a.p0.tiles + a.p1.tiles ? 1 : 2);
-  const WgradProblem& pr = which == 0 ? a.p0 : (which == 1 ? a.p1 : a.p2);
-  const float* A = pr.A;
-  const float* Bm = pr.Bm;
-  float* part = pr.part;
-  float* colsum = pr.colsum;
-  const int M = pr.M, N = pr.N, lda = pr.lda, ldb = pr.ldb;
-  const int tiles_n = pr.tiles_n;
+  pr = which == 0 ? a.p0 : (which == 1 ? a.p1 : a.p2);
   const int tile = tile_id - (which == 0 ? 0 : (which == 1 ? a.p0.tiles : a.p0.tiles + a.p1.tiles));
-  const int m0 = (tile / tiles_n) * WG_T, n0 = (tile % tiles_n) * WG_T;
-  int r0, r1;
+  m0 = (tile / pr.tiles_n) * WG_T;
+  n0 = (tile % pr.tiles_n) * WG_T;
   split_rows(a.off, a.B, a.splits, split, r0, r1);
+  return true;
+}
+__device__ __forceinline__ void wgrad_store(const WgradProblem& pr, int split, int m0, int n0, int wm, int wn, int cl,
+                                            int h, const f32x16 (&acc)[2][2]) {
+  float* o = pr.part + (size_t)split * pr.M * pr.N;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int n = n0 + wn * 64 + j * 32 + cl;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = m0 + wm * 64 + i * 32 + acc_row(h, r);
+        if (m < pr.M && n < pr.N) o[(size_t)m * pr.N + n] = acc[i][j][r];
+      }
+    }
+}
 
+// bf16: A float32 (rounded as it is staged; its sums are of the unrounded
+// values), B stored as bf16.  A thread loads a column pair of 8 rows of each
+// operand (8- and 4-byte loads): 16 loads and 24 KiB per stage, where float32 B
+// and a column per thread took 32 and 32.  LDS is double-buffered with one
+// barrier per stage, and two stages' loads are in flight (one stage: 650 us
+// below).  Reads bound it: 183 k rows of the paper form at H = 1024 are 1.6 GB
+// (0.31 ms at the copy rate) and 42 tiles read 5.9 GB through L2; 820 -> 620
+// us there, 83 -> 64 us for 34 k rows at H = 512.
+__global__ __launch_bounds__(256, 2) void wgrad16_kernel(const WgradArgs a) {
+  constexpr int LDW = WG_KC + 8;                          // padded LDS row (elements)
+  __shared__ __attribute__((aligned(16))) __bf16 As[2][WG_T * LDW];
+  __shared__ __attribute__((aligned(16))) __bf16 Bs[2][WG_T * LDW];
+  __shared__ float csum[4][WG_T];
+  WgradProblem pr;
+  int m0, n0, split, r0, r1;
+  if (!wgrad_place(a, pr, m0, n0, split, r0, r1)) return;
+  const float* A = pr.A;
+  const __bf16* Bm = reinterpret_cast<const __bf16*>(pr.Bm);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = 2 * (tid & 63), rg = tid >> 6;            // loader: column pair, group of 8 rows
+  const bool okA = m0 + c < pr.M, okB = n0 + c < pr.N;    // M, N even
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  f32x2 va0[8], va1[8];
+  uint32_t vb0[8], vb1[8];
+  float cs0 = 0.0f, cs1 = 0.0f;
+  auto load = [&](int rb, f32x2 (&va)[8], uint32_t (&vb)[8]) {
+    const float* ap = A + (size_t)(rb + 8 * rg) * pr.lda + m0 + c;
+    const __bf16* bp = Bm + (size_t)(rb + 8 * rg) * pr.ldb + n0 + c;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const bool rv = rb + 8 * rg + j < r1;
+      va[j] = rv && okA ? *reinterpret_cast<const f32x2*>(ap + (size_t)j * pr.lda) : f32x2{0.0f, 0.0f};
+      vb[j] = rv && okB ? *reinterpret_cast<const uint32_t*>(bp + (size_t)j * pr.ldb) : 0u;
+    }
+  };
+  auto store = [&](int buf, const f32x2 (&va)[8], const uint32_t (&vb)[8]) {
+    bf16x8 e0, e1;
+    u32x4 b0, b1;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      cs0 += va[j][0];
+      cs1 += va[j][1];
+      e0[j] = (__bf16)va[j][0];
+      e1[j] = (__bf16)va[j][1];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      b0[j] = (vb[2 * j] & 0xFFFFu) | (vb[2 * j + 1] << 16);
+      b1[j] = (vb[2 * j] >> 16) | (vb[2 * j + 1] & 0xFFFF0000u);
+    }
+    __bf16* da = As[buf] + c * LDW + 8 * rg;
+    __bf16* db = Bs[buf] + c * LDW + 8 * rg;
+    *reinterpret_cast<bf16x8*>(da) = e0;
+    *reinterpret_cast<bf16x8*>(da + LDW) = e1;
+    *reinterpret_cast<u32x4*>(db) = b0;
+    *reinterpret_cast<u32x4*>(db + LDW) = b1;
+  };
+  const int wm = wave & 1, wn = wave >> 1;
+  const int cl = lane & 31, h = lane >> 5;
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
+  auto products = [&](int buf) {
+#pragma unroll
+    for (int ks = 0; ks < WG_KC / 16; ++ks) {
+      bf16x8 fa[2], fb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        fa[i] = *reinterpret_cast<const bf16x8*>(As[buf] + (wm * 64 + i * 32 + cl) * LDW + ks * 16 + h * 8);
+        fb[i] = *reinterpret_cast<const bf16x8*>(Bs[buf] + (wn * 64 + i * 32 + cl) * LDW + ks * 16 + h * 8);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = PBF16::mfma(fa[i], fb[j], acc[i][j]);
+    }
+  };
+  // rows past r1 load as zeros, so the loop runs over pairs of stages
+  if (r0 < r1) {
+    load(r0, va0, vb0);
+    load(r0 + WG_KC, va1, vb1);
+    store(0, va0, vb0);
+    for (int rb = r0; rb < r1; rb += 2 * WG_KC) {
+      load(rb + 2 * WG_KC, va0, vb0);
+      __syncthreads();                    // buffer 0 is written, buffer 1 has been read
+      products(0);
+      store(1, va1, vb1);
+      load(rb + 3 * WG_KC, va1, vb1);
+      __syncthreads();
+      products(1);
+      store(0, va0, vb0);
+    }
+  }
+  wgrad_store(pr, split, m0, n0, wm, wn, cl, h, acc);
+  // column sums of A: the four row groups, in order (first column tile only)
+  if (n0 == 0 && pr.colsum) {
+    csum[rg][c] = cs0;
+    csum[rg][c + 1] = cs1;
+    __syncthreads();
+    if (tid < WG_T && m0 + tid < pr.M)
+      pr.colsum[(size_t)split * pr.M + m0 + tid] = (csum[0][tid] + csum[1][tid]) + (csum[2][tid] + csum[3][tid]);
+  }
+}
+
+// float32: every thread loads 8 consecutive rows of one column.
+__global__ __launch_bounds__(256) void wgrad32_kernel(const WgradArgs a) {
+  constexpr int LDW = WG_KC + 4;                          // padded LDS row (elements)
+  __shared__ __attribute__((aligned(16))) float As[WG_T * LDW];
+  __shared__ __attribute__((aligned(16))) float Bs[WG_T * LDW];
+  __shared__ float csum[WG_T];
+  WgradProblem pr;
+  int m0, n0, split, r0, r1;
+  if (!wgrad_place(a, pr, m0, n0, split, r0, r1)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = tid & (WG_T - 1), rg = tid >> 7;          // loader: column, row group (0, 1)
-  const bool okA = m0 + c < M, okB = n0 + c < N;
+  const bool okA = m0 + c < pr.M, okB = n0 + c < pr.N;
   float va[2][8], vb[2][8];
   float cs = 0.0f;
   auto load = [&](int rb) {
@@ -3965,8 +4068,8 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
       for (int j = 0; j < 8; ++j) {
         const int r = rb + (rg + 2 * q) * 8 + j;
         const bool rv = r < r1;
-        va[q][j] = (rv && okA) ? A[(size_t)r * lda + m0 + c] : 0.0f;
-        vb[q][j] = (rv && okB) ? Bm[(size_t)r * ldb + n0 + c] : 0.0f;
+        va[q][j] = (rv && okA) ? pr.A[(size_t)r * pr.lda + m0 + c] : 0.0f;
+        vb[q][j] = (rv && okB) ? pr.Bm[(size_t)r * pr.ldb + n0 + c] : 0.0f;
       }
   };
   auto store = [&]() {
@@ -3974,29 +4077,15 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
     for (int q = 0; q < 2; ++q) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) cs += va[q][j];
-      Elem* da = As + c * LDW + (rg + 2 * q) * 8;
-      Elem* db = Bs + c * LDW + (rg + 2 * q) * 8;
-      if constexpr (BF) {
-        bf16x8 ea, eb;
+      float* da = As + c * LDW + (rg + 2 * q) * 8;
+      float* db = Bs + c * LDW + (rg + 2 * q) * 8;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          ea[j] = (__bf16)va[q][j];
-          eb[j] = (__bf16)vb[q][j];
-        }
-        *reinterpret_cast<bf16x8*>(da) = ea;
-        *reinterpret_cast<bf16x8*>(db) = eb;
-      } else {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const f32x4 xa = {va[q][4 * k], va[q][4 * k + 1], va[q][4 * k + 2], va[q][4 * k + 3]};
-          const f32x4 xb = {vb[q][4 * k], vb[q][4 * k + 1], vb[q][4 * k + 2], vb[q][4 * k + 3]};
-          *reinterpret_cast<f32x4*>(da + 4 * k) = xa;
-          *reinterpret_cast<f32x4*>(db + 4 * k) = xb;
-        }
+      for (int k = 0; k < 2; ++k) {
+        *reinterpret_cast<f32x4*>(da + 4 * k) = f32x4{va[q][4 * k], va[q][4 * k + 1], va[q][4 * k + 2], va[q][4 * k + 3]};
+        *reinterpret_cast<f32x4*>(db + 4 * k) = f32x4{vb[q][4 * k], vb[q][4 * k + 1], vb[q][4 * k + 2], vb[q][4 * k + 3]};
       }
     }
   };
-
   const int wm = wave & 1, wn = wave >> 1;
   const int cl = lane & 31, h = lane >> 5;
   f32x16 acc[2][2];
@@ -4011,44 +4100,26 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
     __syncthreads();
     if (rb + WG_KC < r1) load(rb + WG_KC);
 #pragma unroll
-    for (int ks = 0; ks < WG_KC / KF; ++ks) {
-      typename PR::Frag fa[2], fb[2];
+    for (int ks = 0; ks < WG_KC / 2; ++ks) {
+      float fa[2], fb[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const Elem* pa = As + (wm * 64 + i * 32 + cl) * LDW + ks * KF + h * SL;
-        const Elem* pb = Bs + (wn * 64 + i * 32 + cl) * LDW + ks * KF + h * SL;
-        if constexpr (BF) {
-          fa[i] = *reinterpret_cast<const typename PR::Frag*>(pa);
-          fb[i] = *reinterpret_cast<const typename PR::Frag*>(pb);
-        } else {
-          fa[i] = *pa;
-          fb[i] = *pb;
-        }
+        fa[i] = As[(wm * 64 + i * 32 + cl) * LDW + ks * 2 + h];
+        fb[i] = Bs[(wn * 64 + i * 32 + cl) * LDW + ks * 2 + h];
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = PR::mfma(fa[i], fb[j], acc[i][j]);
+        for (int j = 0; j < 2; ++j) acc[i][j] = PF32::mfma(fa[i], fb[j], acc[i][j]);
     }
   }
-  float* o = part + (size_t)split * M * N;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int n = n0 + wn * 64 + j * 32 + cl;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * 64 + i * 32 + acc_row(h, r);
-        if (m < M && n < N) o[(size_t)m * N + n] = acc[i][j][r];
-      }
-    }
+  wgrad_store(pr, split, m0, n0, wm, wn, cl, h, acc);
   // column sums of A: the two row groups, in order (first column tile only)
-  if (n0 == 0 && colsum) {
+  if (n0 == 0 && pr.colsum) {
     __syncthreads();
     if (rg == 1) csum[c] = cs;
     __syncthreads();
-    if (rg == 0 && okA) colsum[(size_t)split * M + m0 + c] = cs + csum[c];
+    if (rg == 0 && okA) pr.colsum[(size_t)split * pr.M + m0 + c] = cs + csum[c];
   }
 }
 
@@ -5222,8 +5293,7 @@ hipError_t launch_train_fwd(const DevModel& m, const TrainIO& io, hipStream_t st
     const int NC = m.dims.trans_hidden / 32;
 #define WM_TFWD_ROWS(N)                                                                              \
     if (m.prec == WM_BF16 && NC == 16) return launch_train_fwd_rows<PBF16, 16, 8, N>(m, io, tiles, st); \
-    if (m.prec == WM_BF16 && NC == 32) return launch_train_fwd_rows<PBF16, 32, 8, N>(m, io, tiles, st); \
-    if (m.prec == WM_FP32 && NC == 16) return launch_train_fwd_rows<PF32, 16, 4, N>(m, io, tiles, st);
+    if (m.prec == WM_BF16 && NC == 32) return launch_train_fwd_rows<PBF16, 32, 8, N>(m, io, tiles, st);
     if (norm) { WM_TFWD_ROWS(true) } else { WM_TFWD_ROWS(false) }
 #undef WM_TFWD_ROWS
   }
@@ -5290,8 +5360,7 @@ hipError_t launch_train_bwd(const DevModel& m, const TrainIO& io, hipStream_t st
     const int NC = m.dims.trans_hidden / 32;
 #define WM_TBWD_ROWS(N)                                                                         \
     if (m.prec == WM_BF16 && NC == 16) return launch_train_bwd_rows<PBF16, 16, 8, N>(a, tiles, st); \
-    if (m.prec == WM_BF16 && NC == 32) return launch_train_bwd_rows<PBF16, 32, 8, N>(a, tiles, st); \
-    if (m.prec == WM_FP32 && NC == 16) return launch_train_bwd_rows<PF32, 16, 4, N>(a, tiles, st);
+    if (m.prec == WM_BF16 && NC == 32) return launch_train_bwd_rows<PBF16, 32, 8, N>(a, tiles, st);
     if (norm) { WM_TBWD_ROWS(true) } else { WM_TBWD_ROWS(false) }
 #undef WM_TBWD_ROWS
   }
@@ -5350,12 +5419,14 @@ hipError_t launch_weight_grads(const DevModel& m, const TrainIO& io, const GradP
   };
   a.p0 = prob(io.SD, D, D, io.G, H, H, g.w2, g.b2);         // dW2 [D][H], db2
   a.p1 = prob(io.A, H, H, io.X, IN, IN, g.w1, g.b1);        // dW1 [H][IN], db1
-  a.p2 = gwh ? prob(io.DV, D, D, io.X + D, E, IN, g.wh, nullptr)   // dWh [D][E] = sum R(dv) R(e)^T
-             : WgradProblem{};
+  // dWh [D][E] = sum R(dv) R(e)^T: the embedding columns of X (bf16 elements in bf16)
+  const float* Xe = m.prec == WM_BF16 ? reinterpret_cast<const float*>(reinterpret_cast<const __bf16*>(io.X) + D)
+                                      : io.X + D;
+  a.p2 = gwh ? prob(io.DV, D, D, Xe, E, IN, g.wh, nullptr) : WgradProblem{};
   a.off = io.off; a.B = io.B; a.splits = S;
   const dim3 grid((a.p0.tiles + a.p1.tiles + a.p2.tiles) * ((S + 7) / 8) * 8);
-  if (m.prec == WM_BF16) hipLaunchKernelGGL(wgrad_kernel<PBF16>, grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL(wgrad_kernel<PF32>, grid, dim3(256), 0, st, a);
+  if (m.prec == WM_BF16) hipLaunchKernelGGL(wgrad16_kernel, grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(wgrad32_kernel, grid, dim3(256), 0, st, a);
   if (E > EMB_THREADS || EMB_THREADS % E) return hipErrorInvalidValue;
   const int lds = (EMB_THREADS / E) * (K + P + 1) * E * (int)sizeof(float);
   hipError_t e = hipFuncSetAttribute((const void*)emb_grad_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);

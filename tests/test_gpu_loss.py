@@ -250,6 +250,33 @@ def test_loss_short_sequences_rowwise(wm, name, prec, B):
     print("  " + ", ".join(f"{k} {v:.1e}" for k, v in rep.items()), flush=True)
 
 
+@pytest.mark.parametrize("name,norm,B", [("ansor_round", "none", 12288 + 21), ("long_schedule", "none", 12288 + 21),
+                                         ("ansor_round", "l2", 16000 + 21)])
+def test_loss_past_the_narrow_tiles(wm, name, norm, B):
+    """bf16 batches past the narrow-tile limit (12288 candidates, paper form
+    16000): the 32-candidate row-owned kernels, a partial last tile, sequences of
+    at most two steps, per tensor against the oracle."""
+    w = synth.scaled(synth.workload(name), B=B, lengths="uniform", len_lo=0, len_hi=2, T_max=2)
+    print(f"[loss past narrow] {name} {norm} B={B}", flush=True)
+    model, W = model_for(wm, name, "bf16", norm)
+    I = synth.make_inputs(w, 7600 + B, pad="garbage")
+    tgt, neg = margin_targets(W, I, "bf16", 3, 87, 0.3, norm=norm)
+    g = run_loss(wm, model, I, tgt, neg, 0.5, 0.3)
+    check_against_oracle(g, W, I, tgt, neg, 0.5, 0.3, "bf16", rows=False, norm=norm)
+
+
+@pytest.mark.parametrize("n_neg", [1, 2, 4, 5, 8, 9, 17])
+def test_loss_negative_counts(wm, n_neg):
+    """The step losses for each unrolled count of negatives, counts between them
+    and more than one pass of eight."""
+    w = synth.scaled(synth.workload("ansor_round"), B=70, lengths="uniform", len_lo=0, len_hi=3, T_max=3)
+    model, W = model_for(wm, "ansor_round", "fp32")
+    I = synth.make_inputs(w, 7700 + n_neg, pad="garbage")
+    tgt, neg = margin_targets(W, I, "fp32", n_neg, 89, 0.3)
+    g = run_loss(wm, model, I, tgt, neg, 0.5, 0.3)
+    check_against_oracle(g, W, I, tgt, neg, 0.5, 0.3, "fp32", rows=True)
+
+
 def test_loss_narrow_limit(wm):
     """8192 candidates of at most two steps, bf16: the largest batch of
     narrow tiles (two per compute unit).  Per-candidate losses and the
