@@ -182,7 +182,7 @@ wm_status wm_model_create(const wm_dims* dims, const wm_weights* w, wm_model** o
   if (D % 32 == 0 && E % 32 == 0) {
     tn = pack_transition_narrow(dm, *w);
     tnt = pack_transposed_narrow(dm, *w);
-    if (HW % 32 == 0 && dm.cost_hidden % 32 == 0) cn = pack_cost_narrow(dm, *w);
+    if (dm.cost_hidden % 32 == 0) cn = pack_cost_narrow(dm, *w);
   }
   // rollout table: type_emb [K][E + 4], param_w^T [PMAX][E], param_b [E], b2 (accumulator order)
   std::vector<float> tab;

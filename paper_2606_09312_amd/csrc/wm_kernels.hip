@@ -2214,7 +2214,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
     // x = [z_T; phi; h]: z_T fragments from the last exchange, phi from the
     // sums (complete after that exchange's barrier), h per hardware vector
     constexpr int NHF = 1;                           // hw fragments (hw_dim <= 32)
-    const int NH = a.HW / 32, NCC = a.C / 32, NKC = NZ + NE + NH;
+    const int NH = (a.HW + 31) / 32, NCC = a.C / 32, NKC = NZ + NE + NH;
     const float inv = len > 0 ? 1.0f / (float)len : 0.0f;
     XF xs[NZ], pf[NE];
 #pragma unroll
@@ -2234,7 +2234,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
         float v[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          v[j] = (jj < a.n_hw && q < NH) ? a.hw[(size_t)jj * a.HW + 32 * q + 8 * g + j] : 0.0f;
+          v[j] = (jj < a.n_hw && 32 * q + 8 * g + j < a.HW) ? a.hw[(size_t)jj * a.HW + 32 * q + 8 * g + j] : 0.0f;
         hf[jj][q] = NP::cvt(v);
       }
     const float* bc1n = reinterpret_cast<const float*>(a.costn + (size_t)NCC * NKC * 2 * GPK * 1024);
@@ -4990,42 +4990,53 @@ hipError_t launch_rollout(const DevModel& m, const float* z0, const int2* perm,
   *phi_done = false;
   const int ntiles = (B + 15) / 16;
   const bool narrow_ok = m.trans_n && B > 0 && B <= narrow_max_candidates(m, false);
-  if (d == 256 && e == 64 && narrow_ok) {
-    const int NC = m.dims.trans_hidden / 32;
-    // scores fused: phi sums present, the narrow cost blob, at most two
-    // hardware vectors of at most 32 features
-    const bool fuse = sf && phi && m.cost_n && sf->n_hw >= 1 && sf->n_hw <= NARROW_SCORE_HW &&
-                      m.dims.hw_dim <= SCORE_MAX_HW;
+  // Scores fused into the narrow kernel: phi sums present, the narrow cost blob,
+  // at most two hardware vectors of at most 32 features.  At d = 64 the launch
+  // that it saves is what counts (sequences of up to 16 steps, separate / fused,
+  // us: float32 B = 256 78 / 72, 16,384 127 / 117, bf16 38 / 36 and 59 / 53); at
+  // 60,000 candidates the separate kernel's larger tiles make up for it (bf16
+  // 117 / 117).
+  const bool fuse = sf && phi && m.cost_n && sf->n_hw >= 1 && sf->n_hw <= NARROW_SCORE_HW &&
+                    m.dims.hw_dim <= SCORE_MAX_HW && (d > 64 || B <= 32768);
+  auto narrow = [&](auto np, auto nc_tag, auto norm_tag, auto d_tag, auto e_tag, auto w_tag) -> hipError_t {
+    using NPT = decltype(np);
+    constexpr int NCT = decltype(nc_tag)::value, DT = decltype(d_tag)::value, ET = decltype(e_tag)::value;
+    constexpr int WT = decltype(w_tag)::value;
+    constexpr bool NT = decltype(norm_tag)::value;
+    *phi_done = phi != nullptr;
     if (fuse) {
       a.costn = m.cost_n; a.hw = sf->hw; a.scores = sf->scores; a.bc2 = m.bc2;
       a.n_hw = sf->n_hw; a.HW = m.dims.hw_dim; a.C = m.dims.cost_hidden;
+      sf->done = true;
+      return launch_rollout_narrow<NPT, NCT, NT, false, true, DT, ET, WT>(m, a, ntiles, st);
     }
-    auto narrow = [&](auto np, auto nc_tag, auto norm_tag) -> hipError_t {
-      using NPT = decltype(np);
-      constexpr int NCT = decltype(nc_tag)::value;
-      constexpr bool NT = decltype(norm_tag)::value;
-      *phi_done = phi != nullptr;
-      if (fuse) {
-        sf->done = true;
-        return launch_rollout_narrow<NPT, NCT, NT, false, true>(m, a, ntiles, st);
-      }
-      return launch_rollout_narrow<NPT, NCT, NT, false, false>(m, a, ntiles, st);
+    return launch_rollout_narrow<NPT, NCT, NT, false, false, DT, ET, WT>(m, a, ntiles, st);
+  };
+  using BT = std::true_type;
+  using BF = std::false_type;
+  if (d == 256 && e == 64 && narrow_ok) {
+    const int NC = m.dims.trans_hidden / 32;
+    auto go = [&](auto np, auto nc_tag) {
+      using D256 = std::integral_constant<int, 256>;
+      using E64 = std::integral_constant<int, 64>;
+      using W8 = std::integral_constant<int, 8>;
+      return norm ? narrow(np, nc_tag, BT{}, D256{}, E64{}, W8{}) : narrow(np, nc_tag, BF{}, D256{}, E64{}, W8{});
     };
     using I16 = std::integral_constant<int, 16>;
     using I32 = std::integral_constant<int, 32>;
-    using BT = std::true_type;
-    using BF = std::false_type;
-    if (prec == WM_BF16 && NC == 16) return norm ? narrow(NarrowBF16{}, I16{}, BT{}) : narrow(NarrowBF16{}, I16{}, BF{});
-    if (prec == WM_BF16 && NC == 32) return norm ? narrow(NarrowBF16{}, I32{}, BT{}) : narrow(NarrowBF16{}, I32{}, BF{});
-    if (prec == WM_FP32 && NC == 16) return norm ? narrow(NarrowF32{}, I16{}, BT{}) : narrow(NarrowF32{}, I16{}, BF{});
+    if (prec == WM_BF16 && NC == 16) return go(NarrowBF16{}, I16{});
+    if (prec == WM_BF16 && NC == 32) return go(NarrowBF16{}, I32{});
+    if (prec == WM_FP32 && NC == 16) return go(NarrowF32{}, I16{});
   }
   if (d == 64 && e == 32 && narrow_ok && m.dims.trans_hidden == 128) {
-    *phi_done = phi != nullptr;
-    if (prec == WM_BF16)
-      return norm ? launch_rollout_narrow<NarrowBF16, 4, true, false, false, 64, 32, 2>(m, a, ntiles, st)
-                  : launch_rollout_narrow<NarrowBF16, 4, false, false, false, 64, 32, 2>(m, a, ntiles, st);
-    return norm ? launch_rollout_narrow<NarrowF32, 4, true, false, false, 64, 32, 2>(m, a, ntiles, st)
-                : launch_rollout_narrow<NarrowF32, 4, false, false, false, 64, 32, 2>(m, a, ntiles, st);
+    auto go = [&](auto np) {
+      using I4 = std::integral_constant<int, 4>;
+      using D64 = std::integral_constant<int, 64>;
+      using E32 = std::integral_constant<int, 32>;
+      using W2 = std::integral_constant<int, 2>;
+      return norm ? narrow(np, I4{}, BT{}, D64{}, E32{}, W2{}) : narrow(np, I4{}, BF{}, D64{}, E32{}, W2{});
+    };
+    return prec == WM_BF16 ? go(NarrowBF16{}) : go(NarrowF32{});
   }
 #define WM_ROLL(PR, D, E)                                                                          \
   return norm ? launch_rollout_de<PR, D, E, true>(m, a, tiles, blocks, waves, split, phi_done, st)  \

@@ -263,7 +263,7 @@ struct DevModel {
   const uint8_t* trans_wht; // Wh^T fragments (paper-form rollout-loss backward)
   const uint8_t* trans_n;   // narrow-tile transition blob (d and e multiples of 32), or null
   const uint8_t* trans_nt;  // its transposed blob (rollout-loss backward), or null
-  const uint8_t* cost_n;    // narrow cost-model blob (hw_dim a multiple of 32), or null
+  const uint8_t* cost_n;    // narrow cost-model blob (hw_dim padded to a multiple of 32), or null
   const float* roll_tab;    // type_emb [K][E + 4] (padded rows), param_w^T [PMAX][E] (zero rows past P), param_b [E], b2 (acc order) [D]
   const float* emb_nat;     // the first three parts of roll_tab
   const float* enc_w1t;     // We1^T [F][Fh] (bf16-rounded values in bf16 mode)

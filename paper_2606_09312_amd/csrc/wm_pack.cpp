@@ -127,10 +127,11 @@ std::vector<uint8_t> pack_transition_narrow(const wm_dims& dm, const wm_weights&
 }
 
 // Narrow cost-model blob (Narrow::c_bytes): Wc1 with the operand orders of
-// the narrow rollout ([z_T] as z fragments, [phi; h] natural), bc1, wc2.
+// the narrow rollout ([z_T] as z fragments, [phi; h] natural), bc1, wc2.  h is
+// padded to a multiple of 32 with zero columns.
 std::vector<uint8_t> pack_cost_narrow(const wm_dims& dm, const wm_weights& w) {
-  const int D = dm.d, E = dm.embed_dim, HW = dm.hw_dim, C = dm.cost_hidden, IN = D + E + HW;
-  const int NKC = IN / 32;
+  const int D = dm.d, E = dm.embed_dim, HW = (dm.hw_dim + 31) / 32 * 32, C = dm.cost_hidden, IN = D + E + dm.hw_dim;
+  const int NKC = (D + E + HW) / 32;
   const bool bf = dm.precision == WM_BF16;
   const int gpk = bf ? 1 : 2, per = 8 / gpk;
   std::vector<uint8_t> blk(Narrow::c_bytes(D, E, HW, C, gpk), 0);
@@ -149,8 +150,8 @@ std::vector<uint8_t> pack_cost_narrow(const wm_dims& dm, const wm_weights& w) {
         for (int L = 0; L < 64; ++L)
           for (int j = 0; j < 8; ++j) {
             const int row = 32 * cc + 16 * rb + (L & 15);
-            put((((size_t)cc * NKC + kf) * 2 + rb) * gpk, L, j,
-                w.wc1[(size_t)row * IN + narrow_x_feature(D, kf, L >> 4, j)]);
+            const int x = narrow_x_feature(D, kf, L >> 4, j);
+            put((((size_t)cc * NKC + kf) * 2 + rb) * gpk, L, j, x < IN ? w.wc1[(size_t)row * IN + x] : 0.0f);
           }
   const size_t tail = (size_t)(C / 32) * NKC * 2 * gpk * 1024;
   std::memcpy(&blk[tail], w.bc1, (size_t)C * 4);

@@ -259,6 +259,28 @@ def test_hardware_vector_counts(wm, prec, n_hw):
     check_topk_vs_oracle(g["idx"], ref["scores"], I["seg_off"], k, tol)
 
 
+@pytest.mark.parametrize("name,prec,norm,hw_dim,n_hw", [
+    ("tiny", "fp32", "none", 16, 2), ("tiny", "bf16", "none", 16, 1), ("tiny", "fp32", "l2", 32, 1),
+    ("tiny", "bf16", "l2", 32, 2), ("tiny", "fp32", "none", 16, 3), ("ansor_round", "fp32", "none", 16, 2)])
+def test_scores_in_the_rollout_hardware_widths(wm, name, prec, norm, hw_dim, n_hw):
+    """Scores inside the rollout launch at d = 64 (two wavefronts per tile, more
+    cost-hidden chunks than wavefronts), and hardware vectors narrower than an
+    operand fragment (padded with zero columns), 77 candidates: a ragged last tile."""
+    w = synth.scaled(synth.workload(name), B=77, n_hw=n_hw, hw_dim=hw_dim)
+    print(f"[hw] {name} {prec} {norm} hw_dim={hw_dim} n_hw={n_hw}", flush=True)
+    W = synth.make_weights(w, 1700)
+    model = wm.Model(wm.model_dims(w), W, precision=prec, norm=norm)
+    I = synth.make_inputs(w, 3200 + n_hw)
+    k = 16
+    g = run_evaluate(model, w, I, k)
+    ref = O.evaluate(W, I, k, prec, norm=norm)
+    tol = TOL[prec]
+    assert latent_rel(g["zT"], ref["zT"]).max() <= tol
+    assert score_rel(g["scores"], ref["scores"], I["seg_off"]).max() <= tol
+    check_topk_self_consistent(g["idx"], g["val"], g["scores"], I["seg_off"], k)
+    check_topk_vs_oracle(g["idx"], ref["scores"], I["seg_off"], k, tol)
+
+
 @pytest.mark.parametrize("what", ["len_high", "len_negative", "type", "param"])
 def test_device_error_word(wm, what):
     w = synth.scaled(synth.workload("tiny"), B=64)
