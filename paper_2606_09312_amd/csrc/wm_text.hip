@@ -80,6 +80,16 @@ __device__ __forceinline__ void split3(float x, __bf16& hi, __bf16& mid, __bf16&
   lo = (__bf16)(r - (float)mid);
 }
 
+// Where element (r, k) of a product operand of `rows` rows lies: slices of 32
+// columns, each [rows][32], so that the 32-deep slice of a tile is one
+// contiguous range.  In row-major order a slice took 64 bytes from every row:
+// half of each cache line, and rows whose pitch is a multiple of 2 KiB (3072
+// columns) all in one L2 channel.  Whole batches, ms: float32, 3 programs 5.22 ->
+// 4.76, bf16, 32 programs 16.19 -> 15.98.
+__device__ __forceinline__ size_t op_at(size_t r, int k, size_t rows) {
+  return ((size_t)(k >> 5) * rows + r) * 32 + (k & 31);
+}
+
 // One LayerNorm output (the same value wherever it is recomputed).
 __device__ __forceinline__ float ln_value(float x, float mean, float rs, float g, float b) {
   return fmaf((x - mean) * rs, g, b);
@@ -134,7 +144,7 @@ constexpr int LN_MAX_PER_LANE = 16;               // hidden <= 1024
 // values from y and those two, so they are never stored (10 -> 6 bytes per
 // feature; 68,608 rows of 768: 85 -> 60 us).  General path: writes h.
 __device__ __forceinline__ void ln_row(const float (&x)[LN_MAX_PER_LANE], float s, int H, const float* g,
-                                       const float* b, size_t r, float* h, __bf16* hb, size_t plane,
+                                       const float* b, size_t r, int rows, float* h, __bf16* hb, size_t plane,
                                        float2* stats) {
   const int lane = threadIdx.x & 63;
   const float mean = wave_sum(s) / (float)H;
@@ -149,8 +159,9 @@ __device__ __forceinline__ void ln_row(const float (&x)[LN_MAX_PER_LANE], float 
     const int f = lane + 64 * i;
     if (f < H) {
       const float o = ln_value(x[i], mean, rs, g[f], b[f]);
-      if (plane) split3(o, hb[r * H + f], hb[plane + r * H + f], hb[2 * plane + r * H + f]);
-      else if (hb) hb[r * H + f] = (__bf16)o;
+      const size_t at = op_at(r, f, rows);
+      if (plane) split3(o, hb[at], hb[plane + at], hb[2 * plane + at]);
+      else if (hb) hb[at] = (__bf16)o;
       else h[r * H + f] = o;
     }
   }
@@ -189,7 +200,7 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t* __restrict
     if (hb && f < H) y[(size_t)r * H + f] = x[i];
     s += x[i];
   }
-  ln_row(x, s, H, g, b, r, h, hb, plane, stats);
+  ln_row(x, s, H, g, b, r, rows, h, hb, plane, stats);
 }
 
 // LN(y[r]) (the residual sum is formed by the product's epilogue).
@@ -210,7 +221,7 @@ __global__ __launch_bounds__(256) void ln_kernel(const float* __restrict__ y,
     x[i] = f < H ? in[f] : 0.0f;
     s += x[i];
   }
-  ln_row(x, s, H, g, b, r, h, hb, plane, stats);
+  ln_row(x, s, H, g, b, r, rows, h, hb, plane, stats);
 }
 
 // ---------------------------------------------------------------------------
@@ -358,9 +369,10 @@ __global__ __launch_bounds__(256) void gemm_kernel(const GemmArgs g) {
 }
 
 // bf16 dense product with operands stored as bf16 (the product-operand
-// values themselves):  C = epi(A . W^T), A [M][K] and W [N][K] row-major,
-// epilogue + bias[n], GELU, + LN(y)[m][n] (the residual, recomputed from the
-// previous row sums y, their mean and 1/deviation), C fp32 or bf16.  With a
+// values themselves):  C = epi(A . W^T), A [M][K] and W [N][K] in slices
+// (op_at), epilogue + bias[n], GELU, + LN(y)[m][n] (the residual, recomputed
+// from the previous row sums y, their mean and 1/deviation), C fp32 or bf16
+// row-major, or (slices) the bf16 operand of the next product.  With a
 // residual C is y itself: each element is read and then written by one lane.
 //
 // Both kernels stage 32-deep slices of A and W in a ring of four LDS buffers
@@ -378,7 +390,7 @@ struct Gemm16Args {
   const float* res;        // y, or null
   const float2* stats;     // [M] mean, 1/deviation of y
   const float *ln_g, *ln_b;
-  int M, N, K, tiles_n, gelu;
+  int M, N, K, tiles_n, gelu, slices;
 };
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void lds_void;
@@ -390,19 +402,21 @@ __device__ __forceinline__ u32x4 buffer_of(const void* p, uint32_t bytes) {
                (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)),
                (uint32_t)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u};
 }
-// 16 bytes per lane from byte vo (per lane) + so (uniform) of a buffer into
-// LDS at d + lane * 16.  Inline assembly, because the compiler otherwise waits
+// 16 bytes per lane from byte vo (per lane) of a buffer into LDS at d + lane *
+// 16.  Inline assembly, because the compiler otherwise waits
 // for every outstanding copy before an LDS read of another slice of the ring;
 // the kernels wait for the copies themselves (the instruction has no register
-// output, so nothing can be overwritten while it is in flight).  m0 is listed
+// output, so nothing can be overwritten while it is in flight).  s_nop 4 covers the
+// wait of a load on a scalar register that a vector instruction wrote, which the
+// compiler does not see here.  m0 is listed
 // as clobbered for the compiler's own uses of it; the warning that it is a
 // reserved register does not apply to a value nobody keeps there.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void copy16(u32x4 r, __bf16* d, uint32_t vo, int so) {
+__device__ __forceinline__ void copy16(u32x4 r, __bf16* d, uint32_t vo) {
   const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void*)d);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(l), "v"(vo), "s"(r), "s"(so) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :: "s"(l), "v"(vo), "s"(r) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 // Wait until at most VM vector-memory operations are outstanding, and (LGKM)
@@ -430,13 +444,17 @@ __device__ __forceinline__ int xcd_tile(int bid, int total) {
   return x * per + min(x, rem) + i;
 }
 
+// Slice s of a tile's `rows` rows from row r0 of an operand of M rows.
+__device__ __forceinline__ u32x4 slice_of(const __bf16* p, int r0, int rows, int M, int s) {
+  return buffer_of(p + ((size_t)s * M + r0) * GK, (uint32_t)rows * (GK * 2));
+}
 // Where thread t's 16-byte unit i of a slice comes from (bytes from the tile's
 // first row), rows past the last one clamped to it (their results are dropped).
 template <int TN>
-__device__ __forceinline__ uint32_t slice_offset(int u, int row_bytes, int rows) {
+__device__ __forceinline__ uint32_t slice_offset(int u, int rows) {
   const int r = u >> 2, s = (u ^ (r >> 2)) & 3;
   const int c = r % (32 * TN), row = TN > 1 ? r - c + TN * (c & 31) + (c >> 5) : r;
-  return (uint32_t)min(row, rows - 1) * row_bytes + s * 16;
+  return (uint32_t)min(row, rows - 1) * (GK * 2) + s * 16;
 }
 
 // Epilogue of one wavefront: TM x TN tiles at rows m0 + mw, columns n ..
@@ -499,7 +517,10 @@ __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args& g, const f32x1
         bv q;
 #pragma unroll
         for (int j = 0; j < TN; ++j) q[j] = (__bf16)v[j];
-        if constexpr (TN == 2) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, q), rc, o * 2, 0, 0);
+        if (g.slices) {
+          if (mw + 4 * h + (int)row < rows)
+            *reinterpret_cast<bv*>(static_cast<__bf16*>(g.C) + op_at((size_t)m0 + mw + 4 * h + row, n, g.M)) = q;
+        } else if constexpr (TN == 2) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, q), rc, o * 2, 0, 0);
         else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, q), rc, o * 2, 0, 0);
       } else {
         const float mean = __uint_as_float(st[i & 1][r][0]), inv = __uint_as_float(st[i & 1][r][1]);
@@ -538,18 +559,18 @@ __global__ __launch_bounds__(512, 2) void gemm16_large_kernel(const Gemm16Args g
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cl = lane & 31, h = lane >> 5;
   const int t = xcd_tile(blockIdx.x, gridDim.x);
-  const int m0 = (t / g.tiles_n) * BM, n0 = (t % g.tiles_n) * BN;
+  // uniform, so that the slices' buffers are formed by scalar instructions
+  const int m0 = __builtin_amdgcn_readfirstlane((t / g.tiles_n) * BM);
+  const int n0 = __builtin_amdgcn_readfirstlane((t % g.tiles_n) * BN);
   const int rows = min(BM, g.M - m0), cols = min(BN, g.N - n0);
   const int grp = wave >> 2, wn = wave & 3;
-  const int K2 = g.K * 2, nk = g.K / GK;
+  const int nk = g.K / GK;
   uint32_t oa[2], ob[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    oa[i] = slice_offset<1>(i * 512 + tid, K2, rows);
-    ob[i] = slice_offset<TN>(i * 512 + tid, K2, cols);
+    oa[i] = slice_offset<1>(i * 512 + tid, rows);
+    ob[i] = slice_offset<TN>(i * 512 + tid, cols);
   }
-  const u32x4 ra = buffer_of(g.A + (size_t)m0 * g.K, (uint32_t)rows * K2);
-  const u32x4 rb = buffer_of(g.W + (size_t)n0 * g.K, (uint32_t)cols * K2);
   f32x16 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -575,13 +596,15 @@ __global__ __launch_bounds__(512, 2) void gemm16_large_kernel(const Gemm16Args g
   };
   auto copyA = [&](int s) {
     __bf16* d = S + (s & 3) * SLICE + wave * 512;
-    copy16(ra, d, oa[0], s * GK * 2);
-    copy16(ra, d + 4096, oa[1], s * GK * 2);
+    const u32x4 ra = slice_of(g.A, m0, rows, g.M, s);
+    copy16(ra, d, oa[0]);
+    copy16(ra, d + 4096, oa[1]);
   };
   auto copyB = [&](int s) {
     __bf16* d = S + (s & 3) * SLICE + BM * GK + wave * 512;
-    copy16(rb, d, ob[0], s * GK * 2);
-    copy16(rb, d + 4096, ob[1], s * GK * 2);
+    const u32x4 rb = slice_of(g.W, n0, cols, g.N, s);
+    copy16(rb, d, ob[0]);
+    copy16(rb, d + 4096, ob[1]);
   };
   for (int s = 0; s < 3 && s < nk; ++s) { copyA(s); copyB(s); }
   if (nk >= 3) wait_counts<8, false>(); else wait_counts<0, false>();
@@ -619,25 +642,26 @@ __global__ __launch_bounds__(256, 2) void gemm16_small_kernel(const Gemm16Args g
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cl = lane & 31, h = lane >> 5;
   const int t = xcd_tile(blockIdx.x, gridDim.x);
-  const int m0 = (t / g.tiles_n) * BM, n0 = (t % g.tiles_n) * BN;
+  // uniform, so that the slices' buffers are formed by scalar instructions
+  const int m0 = __builtin_amdgcn_readfirstlane((t / g.tiles_n) * BM);
+  const int n0 = __builtin_amdgcn_readfirstlane((t % g.tiles_n) * BN);
   const int rows = min(BM, g.M - m0), cols = min(BN, g.N - n0);
   const int wm = wave & 1, wn = wave >> 1;
-  const int K2 = g.K * 2, nk = g.K / GK;
+  const int nk = g.K / GK;
   uint32_t oa[UA];
 #pragma unroll
-  for (int i = 0; i < UA; ++i) oa[i] = slice_offset<1>(i * 256 + tid, K2, rows);
-  const uint32_t ob = slice_offset<1>(tid, K2, cols);
-  const u32x4 ra = buffer_of(g.A + (size_t)m0 * g.K, (uint32_t)rows * K2);
-  const u32x4 rb = buffer_of(g.W + (size_t)n0 * g.K, (uint32_t)cols * K2);
+  for (int i = 0; i < UA; ++i) oa[i] = slice_offset<1>(i * 256 + tid, rows);
+  const uint32_t ob = slice_offset<1>(tid, cols);
   f32x16 acc[WM][1];
 #pragma unroll
   for (int i = 0; i < WM; ++i) acc[i][0] = f32x16{};
   const int sw = (cl >> 2) & 3;
   auto copy = [&](int s) {
     __bf16* d = S + (s & 3) * SLICE + wave * 512;
+    const u32x4 ra = slice_of(g.A, m0, rows, g.M, s), rb = slice_of(g.W, n0, cols, g.N, s);
 #pragma unroll
-    for (int i = 0; i < UA; ++i) copy16(ra, d + i * 2048, oa[i], s * GK * 2);
-    copy16(rb, d + BM * GK, ob, s * GK * 2);
+    for (int i = 0; i < UA; ++i) copy16(ra, d + i * 2048, oa[i]);
+    copy16(rb, d + BM * GK, ob);
   };
   for (int s = 0; s < 3 && s < nk; ++s) copy(s);
   for (int s = 0; s < nk; ++s) {
@@ -713,7 +737,7 @@ __device__ __forceinline__ float exp2_of(float x) { return __builtin_amdgcn_exp2
 template <int DH>
 __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restrict__ qkv,
                                                          __bf16* __restrict__ ctx, const TTable tt,
-                                                         int window, int stride, int heads, int H,
+                                                         int window, int stride, int heads, int H, int rows,
                                                          float scale) {
   constexpr int KS = DH / 16;                 // 16-deep steps over the head width
   constexpr int DB = DH / 32;                 // 32-row blocks of the head width
@@ -814,7 +838,7 @@ __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restric
   const float inv = 1.0f / (sum + __shfl_xor(sum, 32));
   if (q < len) {                // the output as the next product's operand
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-    __bf16* orow = ctx + ((size_t)row0 + q) * H + head * DH + 4 * h;
+    const size_t orow = (size_t)row0 + q;
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
@@ -822,7 +846,7 @@ __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restric
         bf16x4 o;
 #pragma unroll
         for (int i = 0; i < 4; ++i) o[i] = (__bf16)(oacc[b][4 * r4 + i] * inv);
-        *reinterpret_cast<bf16x4*>(orow + 32 * b + 8 * r4) = o;
+        *reinterpret_cast<bf16x4*>(ctx + op_at(orow, head * DH + 32 * b + 8 * r4 + 4 * h, rows)) = o;
       }
   }
 }
@@ -833,11 +857,20 @@ __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restric
 // 2^-25 of |a||b|), the five small ones in an accumulator of their own.  Six
 // bf16 products take 96 cycles per 16x16x32 where float32 ones take 256.  Its
 // distance from float64 over the encoder equals that of the float32 products
-// (5e-7).  Tiles of 64 x 64, 4 wavefronts of 32 x 32, slices of 32 (24 KiB with
-// all planes) in a ring of three, one barrier per slice as in
-// gemm16_small_kernel; two workgroups per compute unit.  2400 rows, us per
-// layer's product against 128 x 128 float32 tiles (114 of 256 compute units
-// busy at N = 768): see the table in the repository's design notes.
+// (5e-7).
+//
+// Tiles are 64 WM x 64, slices of 32 in a ring of three, and 8 wavefronts in
+// two groups: group kg takes the 16-deep half kg of every slice, so a
+// wavefront's tile is 32 WM x 32 (WM = 2: 9 fragments from LDS for 12 products,
+// where 32 x 32 tiles read a fragment per 32-cycle product, all that the LDS
+// gives the four SIMDs) with two wavefronts per SIMD, and the groups' sums are
+// added through LDS at the end, each group finishing half of the rows.  A
+// slice's fragments are read while the products of the slice before run.
+// Copies from L2 bound it (a third of the cycles are products): with row-major
+// operands this and a kernel of 4 wavefronts on 64 x 64 tiles took the same time,
+// with operands in slices (op_at) 2400 rows of 768 columns, 12 layers, three
+// programs encoded: 5.26 -> 4.76 ms (products 3.74 -> 3.37; N 3072, K 768 110 ->
+// 101 us, N 768, K 3072 99 -> 90).
 struct Gemm3Args {
   const __bf16 *A, *W;      // planes a_plane, w_plane elements apart
   void* C;                  // float32, or planes c_plane elements apart
@@ -848,98 +881,156 @@ struct Gemm3Args {
   size_t a_plane, w_plane, c_plane;
   int M, N, K, tiles_n, gelu;
 };
-template <bool SPLIT_OUT>
-__global__ __launch_bounds__(256, 2) void gemm16x3_kernel(const Gemm3Args g) {
-  constexpr int BM = 64, BN = 64, PL = BM * GK, SLICE = 6 * PL;   // planes: A hi, mid, lo, W hi, mid, lo
+template <int WM, bool SPLIT_OUT>
+__global__ __launch_bounds__(512, WM == 1 ? 4 : 2) void gemm16x3_kernel(const Gemm3Args g) {
+  constexpr int BM = 64 * WM, BN = 64, PA = BM * GK, PB = BN * GK, SLICE = 3 * (PA + PB);
+  constexpr int NR = 8 * WM;                    // rows that a lane finishes
   __shared__ __attribute__((aligned(16))) __bf16 S[3 * SLICE];
-  const int tid = threadIdx.x, lane = tid & 63;
+  static_assert(4 * NR * 256 * 4 <= sizeof(S), "the groups' exchange takes the ring's place");
+  const int tid = threadIdx.x, lane = tid & 63, q = tid & 255;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cl = lane & 31, h = lane >> 5;
   const int t = xcd_tile(blockIdx.x, gridDim.x);
-  const int m0 = (t / g.tiles_n) * BM, n0 = (t % g.tiles_n) * BN;
+  // uniform, so that the slices' buffers are formed by scalar instructions
+  const int m0 = __builtin_amdgcn_readfirstlane((t / g.tiles_n) * BM);
+  const int n0 = __builtin_amdgcn_readfirstlane((t % g.tiles_n) * BN);
   const int rows = min(BM, g.M - m0), cols = min(BN, g.N - n0);
-  const int wm = wave & 1, wn = wave >> 1;
-  const int K2 = g.K * 2, nk = g.K / GK;
-  const uint32_t oa = slice_offset<1>(tid, K2, rows), ob = slice_offset<1>(tid, K2, cols);
-  u32x4 ra[3], rb[3];
-#pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    ra[p] = buffer_of(g.A + p * g.a_plane + (size_t)m0 * g.K, (uint32_t)rows * K2);
-    rb[p] = buffer_of(g.W + p * g.w_plane + (size_t)n0 * g.K, (uint32_t)cols * K2);
-  }
-  f32x16 hi = {}, lo = {};
-  const int sw = (cl >> 2) & 3;
+  const int kg = wave >> 2, wm = wave & 1, wn = (wave >> 1) & 1;
+  const int nk = g.K / GK;
+  const uint32_t oa = slice_offset<1>(WM == 2 ? tid : q, rows), ob = slice_offset<1>(q, cols);
+  // WM = 2: a plane of A is 512 units, one per thread, a plane of W 256: group 0
+  // copies two of them, group 1 one.  WM = 1: group 0 copies A, group 1 W.
   auto copy = [&](int s, int b) {
-    __bf16* d = S + b * SLICE + wave * 512;
+    __bf16* d = S + b * SLICE + (wave & 3) * 512;
+    auto copy_a = [&](int p, __bf16* to) { copy16(slice_of(g.A + p * g.a_plane, m0, rows, g.M, s), to + p * PA, oa); };
+    auto copy_w = [&](int p) { copy16(slice_of(g.W + p * g.w_plane, n0, cols, g.N, s), d + 3 * PA + p * PB, ob); };
+    if constexpr (WM == 2) {
 #pragma unroll
-    for (int p = 0; p < 3; ++p) copy16(ra[p], d + p * PL, oa, s * GK * 2);
+      for (int p = 0; p < 3; ++p) copy_a(p, d + kg * 2048);
+      if (kg == 0) {
+        copy_w(0);
+        copy_w(1);
+      } else {
+        copy_w(2);
+      }
+    } else if (kg == 0) {
 #pragma unroll
-    for (int p = 0; p < 3; ++p) copy16(rb[p], d + (3 + p) * PL, ob, s * GK * 2);
+      for (int p = 0; p < 3; ++p) copy_a(p, d);
+    } else {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) copy_w(p);
+    }
   };
+  // at most `slices` slices' copies of this wavefront outstanding, LDS reads done
+  auto wait = [&](int slices) {
+    if (slices == 0) wait_counts<0, true>();
+    else if (WM == 1) { if (slices == 1) wait_counts<3, true>(); else wait_counts<6, true>(); }
+    else if (kg == 0) { if (slices == 1) wait_counts<5, true>(); else wait_counts<10, true>(); }
+    else { if (slices == 1) wait_counts<4, true>(); else wait_counts<8, true>(); }
+  };
+  const int fo = cl * GK + (((2 * kg + h) ^ (cl >> 2)) & 3) * 8;
+  struct Frags { bf16x8 a[WM][3], b[3]; };
+  auto read = [&](int b, Frags& f) {
+    const __bf16* base = S + b * SLICE + fo;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+#pragma unroll
+      for (int i = 0; i < WM; ++i) f.a[i][p] = *reinterpret_cast<const bf16x8*>(base + p * PA + (wm * WM + i) * 32 * GK);
+      f.b[p] = *reinterpret_cast<const bf16x8*>(base + 3 * PA + p * PB + wn * 32 * GK);
+    }
+  };
+  f32x16 hi[WM], lo[WM];
+#pragma unroll
+  for (int i = 0; i < WM; ++i) hi[i] = lo[i] = f32x16{};
+  auto products = [&](const Frags& f) {
+    constexpr int PI[6] = {0, 2, 1, 0, 1, 0}, PJ[6] = {0, 0, 1, 2, 0, 1};   // largest first, then the small ones
+#pragma unroll
+    for (int u = 0; u < 6; ++u)
+#pragma unroll
+      for (int i = 0; i < WM; ++i) {
+        if (u == 0) hi[i] = BF::mfma(f.a[i][0], f.b[0], hi[i]);
+        else lo[i] = BF::mfma(f.a[i][PI[u]], f.b[PJ[u]], lo[i]);
+      }
+  };
+  // Step s multiplies slice s from registers, reads slice s + 1 and copies slice
+  // s + 3 into slice s's buffer, which every wavefront has read by the barrier;
+  // slice s + 1 has landed by then, slice s + 2 may be in flight.
+  int cur = 0;                                   // buffer of slice s
+  auto step = [&](int s, const Frags& now, Frags& next) {
+    wait(s + 2 < nk ? 1 : 0);
+    raw_barrier();
+    if (s + 3 < nk) copy(s + 3, cur);
+    cur = cur == 2 ? 0 : cur + 1;
+    if (s + 1 < nk) read(cur, next);
+    sched_fence();
+    products(now);
+  };
+  Frags f0, f1;
   copy(0, 0);
   if (nk > 1) copy(1, 1);
-  int cur = 0;
-  for (int s = 0; s < nk; ++s) {
-    if (s + 1 < nk) wait_counts<6, true>(); else wait_counts<0, true>();
-    raw_barrier();
-    if (s + 2 < nk) copy(s + 2, cur == 0 ? 2 : cur - 1);
-    const __bf16* base = S + cur * SLICE + cl * GK;
-    bf16x8 fa[2][3], fb[2][3];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const __bf16* a = base + ((2 * ks + h) ^ sw) * 8;
-#pragma unroll
-      for (int p = 0; p < 3; ++p) {
-        fa[ks][p] = *reinterpret_cast<const bf16x8*>(a + p * PL + wm * 32 * GK);
-        fb[ks][p] = *reinterpret_cast<const bf16x8*>(a + (3 + p) * PL + wn * 32 * GK);
-      }
-    }
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      lo = BF::mfma(fa[ks][2], fb[ks][0], lo);
-      hi = BF::mfma(fa[ks][0], fb[ks][0], hi);
-      lo = BF::mfma(fa[ks][1], fb[ks][1], lo);
-      lo = BF::mfma(fa[ks][0], fb[ks][2], lo);
-      lo = BF::mfma(fa[ks][1], fb[ks][0], lo);
-      lo = BF::mfma(fa[ks][0], fb[ks][1], lo);
-    }
-    cur = cur == 2 ? 0 : cur + 1;
+  if (nk > 2) copy(2, 2);
+  wait(nk > 2 ? 2 : nk > 1 ? 1 : 0);
+  raw_barrier();
+  read(0, f0);
+  for (int s = 0; s < nk; s += 2) {
+    step(s, f0, f1);
+    if (s + 1 < nk) step(s + 1, f1, f0);
   }
+  // the groups' sums: each hands over the rows that the other finishes (WM = 2:
+  // group kg finishes the row tile kg, WM = 1: half kg of the lane's 16 rows)
+  float* x = reinterpret_cast<float*>(S);        // [group][hi, lo][NR][256]
+  __syncthreads();                               // the ring has been read
+  float vh[NR], vl[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const float h0 = hi[0][r], h1 = WM == 2 ? hi[WM - 1][r] : hi[0][8 + r % 8];
+    const float l0 = lo[0][r], l1 = WM == 2 ? lo[WM - 1][r] : lo[0][8 + r % 8];
+    vh[r] = kg ? h1 : h0;
+    vl[r] = kg ? l1 : l0;
+    x[((kg * 2 + 0) * NR + r) * 256 + q] = kg ? h0 : h1;
+    x[((kg * 2 + 1) * NR + r) * 256 + q] = kg ? l0 : l1;
+  }
+  __syncthreads();
   const int n = n0 + wn * 32 + cl;
   if (n >= g.N) return;
   const float bias = g.bias[n];
   const float lg = g.res ? g.ln_g[n] : 0.0f, lb = g.res ? g.ln_b[n] : 0.0f;
-  float y[16];
-  float2 st[16];
+  const int mt = m0 + wm * 32 * WM + (WM == 2 ? kg * 32 : kg * 16) + 4 * h;
+  float y[NR];
+  float2 st[NR];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int m = min(m0 + wm * 32 + acc_row(h, r), g.M - 1);
+  for (int r = 0; r < NR; ++r) {
+    const int m = min(mt + acc_row(0, r), g.M - 1);
     y[r] = g.res ? g.res[(size_t)m * g.N + n] : 0.0f;
     st[r] = g.res ? g.stats[m] : make_float2(0.0f, 0.0f);
   }
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int m = m0 + wm * 32 + acc_row(h, r);
+  for (int r = 0; r < NR; ++r) {
+    const int m = mt + acc_row(0, r);
     if (m >= g.M) continue;
-    float v = (hi[r] + lo[r]) + bias;
+    const float sh = vh[r] + x[(((kg ^ 1) * 2 + 0) * NR + r) * 256 + q];
+    const float sl = vl[r] + x[(((kg ^ 1) * 2 + 1) * NR + r) * 256 + q];
+    float v = (sh + sl) + bias;
     if (g.gelu) v = gelu(v);
     if (g.res) v += ln_value(y[r], st[r].x, st[r].y, lg, lb);
-    const size_t o = (size_t)m * g.N + n;
     if constexpr (SPLIT_OUT) {
-      __bf16* c = static_cast<__bf16*>(g.C) + o;
+      __bf16* c = static_cast<__bf16*>(g.C) + op_at(m, n, g.M);
       split3(v, c[0], c[g.c_plane], c[2 * g.c_plane]);
     } else {
-      static_cast<float*>(g.C)[o] = v;
+      static_cast<float*>(g.C)[(size_t)m * g.N + n] = v;
     }
   }
 }
 
-// n float32 values as `planes` bf16 planes (1: rounded; 3: split3), n apart.
-__global__ __launch_bounds__(256) void split_planes_kernel(const float* __restrict__ src, size_t n, int planes,
-                                                           __bf16* __restrict__ dst) {
+// n float32 values, matrices [N][K] one after another, as `planes` bf16 planes
+// (1: rounded; 3: split3), n apart, every matrix in slices.
+__global__ __launch_bounds__(256) void split_planes_kernel(const float* __restrict__ src, size_t n, int N, int K,
+                                                           int planes, __bf16* __restrict__ dst) {
   for (size_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-    if (planes == 1) dst[i] = (__bf16)src[i];
-    else split3(src[i], dst[i], dst[n + i], dst[2 * n + i]);
+    const size_t row = i / K, l = row / N;
+    const size_t o = l * N * K + op_at(row - l * N, (int)(i - row * K), N);
+    if (planes == 1) dst[o] = (__bf16)src[i];
+    else split3(src[i], dst[o], dst[n + o], dst[2 * n + o]);
   }
 }
 
@@ -955,7 +1046,7 @@ template <int DH>
 __global__ __launch_bounds__(256, 2) void attention32_kernel(const float* __restrict__ qkv,
                                                              __bf16* __restrict__ ctx, size_t plane,
                                                              const TTable tt, int window, int stride, int heads,
-                                                             int H, float scale) {
+                                                             int H, int rows, float scale) {
   constexpr int KB = 64, DB = DH / 32, HS = DH / 2;     // keys per block, 32-feature blocks, features per lane half
   constexpr int KW = DH + 4, VW = DH + 8;
   __shared__ __attribute__((aligned(16))) float Ks[KB * KW];
@@ -1053,12 +1144,12 @@ __global__ __launch_bounds__(256, 2) void attention32_kernel(const float* __rest
   }
   const float inv = 1.0f / (sum + __shfl_xor(sum, 32));
   if (q < len) {
-    __bf16* o = ctx + ((size_t)row0 + q) * H + head * DH;
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int d = 32 * b + acc_row(h, r);
+        __bf16* o = ctx + op_at((size_t)row0 + q, head * DH + 32 * b, rows);
+        const int d = acc_row(h, r);
         split3(oacc[b][r] * inv, o[d], o[plane + d], o[2 * plane + d]);
       }
   }
@@ -1276,12 +1367,13 @@ wm_status wm_text_model_create(const wm_text_dims* dims, const wm_text_weights* 
   if (w16) {
     // the matrices' bf16 values (planes) are formed on the device from the
     // uploaded float32 ones
+    const int mat_n[4] = {3 * d.hidden, d.hidden, d.ffn, d.hidden}, mat_k[4] = {d.hidden, d.hidden, d.hidden, d.ffn};
     hipError_t e = hipSuccess;
     for (int i = 0; i < 4 && e == hipSuccess; ++i) {
       const Part& p = parts[mats[i]];
       if (p.n == 0) continue;
       hipLaunchKernelGGL(split_planes_kernel, dim3(2048), dim3(256), 0, nullptr,
-                         reinterpret_cast<const float*>(base + p.off), p.n, (int)planes,
+                         reinterpret_cast<const float*>(base + p.off), p.n, mat_n[i], mat_k[i], (int)planes,
                          reinterpret_cast<__bf16*>(base + off16[i]));
       e = hipGetLastError();
     }
@@ -1383,7 +1475,7 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
                  const float* res, const float* lng, const float* lnb, int gelu, bool out16) {
     Gemm16Args g;
     g.A = A; g.W = Wm; g.C = C; g.bias = bias; g.res = res; g.stats = res ? stats : nullptr;
-    g.ln_g = lng; g.ln_b = lnb; g.M = M; g.N = N; g.K = K; g.gelu = gelu;
+    g.ln_g = lng; g.ln_b = lnb; g.M = M; g.N = N; g.K = K; g.gelu = gelu; g.slices = gelu;   // the hidden layer: operand of the next product
     auto tiles = [&](int bm, int bn) { g.tiles_n = (N + bn - 1) / bn; return dim3(((M + bm - 1) / bm) * g.tiles_n); };
     auto go = [&](auto kern, dim3 grid, int threads) { hipLaunchKernelGGL(kern, grid, dim3(threads), 0, st, g); };
     // Which tile: a 256 x 256 tile keeps a compute unit busy for about four
@@ -1415,9 +1507,15 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
     g.a_plane = (size_t)rows * K; g.w_plane = w_plane; g.c_plane = (size_t)rows * N;
     g.M = rows; g.N = N; g.K = K; g.gelu = gelu;
     g.tiles_n = (N + 63) / 64;
-    const dim3 grid(((rows + 63) / 64) * g.tiles_n);
-    if (split) hipLaunchKernelGGL(gemm16x3_kernel<true>, grid, dim3(256), 0, st, g);
-    else hipLaunchKernelGGL(gemm16x3_kernel<false>, grid, dim3(256), 0, st, g);
+    auto go = [&](auto kern, int bm) {
+      hipLaunchKernelGGL(kern, dim3(((rows + bm - 1) / bm) * g.tiles_n), dim3(512), 0, st, g);
+    };
+    // 128 x 64 tiles where they fill half of the compute units (one each)
+    if ((long long)((rows + 127) / 128) * g.tiles_n >= 128) {
+      if (split) go(gemm16x3_kernel<2, true>, 128); else go(gemm16x3_kernel<2, false>, 128);
+    } else {
+      if (split) go(gemm16x3_kernel<1, true>, 64); else go(gemm16x3_kernel<1, false>, 64);
+    }
     return hipGetLastError();
   };
   auto ln = [&](const float* yin, const float* gm, const float* bt, __bf16* hbo) {
@@ -1444,7 +1542,7 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
         WM_TT(TK_TEXT_ATTN, [&]() {
           hipLaunchKernelGGL(dh == 64 ? attention32_kernel<64> : attention32_kernel<32>,
                              dim3(n_chunks * nh, (W + 127) / 128), dim3(256), 0, st, qkv, ctxb, (size_t)rows * H, tt, W,
-                             d.stride, nh, H, 1.0f / std::sqrt((float)dh));
+                             d.stride, nh, H, rows, 1.0f / std::sqrt((float)dh));
           return hipGetLastError();
         }());
         WM_TT(TK_TEXT_GEMM, g3(ctxb, H, m->wo16 + lH * H, Lw * H, H, y, m->bo + lH, y, g0, b0, 0, false));
@@ -1466,7 +1564,7 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
           hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
           if (e != hipSuccess) { (void)hipGetLastError(); return e; }
           hipLaunchKernelGGL(kern, dim3(n_chunks * nh), dim3(64 * (W / 32)), lds, st, qkvb, ctxb, tt, W,
-                             d.stride, nh, H, 1.0f / std::sqrt((float)dh));
+                             d.stride, nh, H, rows, 1.0f / std::sqrt((float)dh));
           return hipGetLastError();
         }());
         WM_TT(TK_TEXT_GEMM, g16(ctxb, rows, H, m->wo16 + lH * H, H, y, m->bo + lH, y, g0, b0, 0, false));

@@ -123,6 +123,25 @@ def test_product_tiles(wm, S, n):
     assert rel.max() <= TOL["bf16"], f"z0 rel err {rel.max():.3e}"
 
 
+@pytest.mark.parametrize("S,n,hidden,heads,ffn", [
+    (3, 70, 32, 1, 64), (4, 90, 96, 3, 160), (200, 190, 96, 3, 160), (256, 230, 32, 1, 96)])
+def test_float32_product_tiles(wm, S, n, hidden, heads, ffn):
+    """Both tile heights of the float32 products (64 rows for few rows, 128 for
+    many), contractions of 1 to 5 slices (shorter and longer than the ring of
+    three) and output widths whose last 64-column tile holds 32 columns.  The bound is
+    that of the float32 shapes above."""
+    w = synth.TextWorkload(name="tiles32", S=S, vocab=500, hidden=hidden, heads=heads, ffn=ffn, layers=2, window=64,
+                           stride=32, d=64, len_lo=1, len_hi=n)
+    W = synth.make_text_weights(w, 91)
+    model = wm.TextModel(w, W, precision="fp32")
+    tokens, off = synth.make_programs(w, 93)
+    print(f"[text] fp32 tiles S={S} chunks={model.chunks(off)} tokens={len(tokens)}", flush=True)
+    g = run(wm, model, tokens, off)
+    ref = TE.encode(W, programs_of(tokens, off), w.window, w.stride, w.heads, "fp32")
+    rel = latent_rel(g, ref)
+    assert rel.max() <= 5e-6, f"z0 rel err {rel.max():.3e}"
+
+
 def test_token_out_of_range_is_reported(wm):
     model, W, w = model_for(wm, "tiny_text", "fp32")
     off = np.array([0, 5], dtype=np.int32)
