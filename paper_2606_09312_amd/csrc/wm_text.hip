@@ -85,7 +85,7 @@ __device__ __forceinline__ void split3(float x, __bf16& hi, __bf16& mid, __bf16&
 // contiguous range.  In row-major order a slice took 64 bytes from every row:
 // half of each cache line, and rows whose pitch is a multiple of 2 KiB (3072
 // columns) all in one L2 channel.  Whole batches, ms: float32, 3 programs 5.22 ->
-// 4.76, bf16, 32 programs 16.19 -> 15.98.
+// 4.76 (128 x 64 tiles), bf16, 32 programs 16.19 -> 15.98.
 __device__ __forceinline__ size_t op_at(size_t r, int k, size_t rows) {
   return ((size_t)(k >> 5) * rows + r) * 32 + (k & 31);
 }
@@ -859,18 +859,18 @@ __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restric
 // distance from float64 over the encoder equals that of the float32 products
 // (5e-7).
 //
-// Tiles are 64 WM x 64, slices of 32 in a ring of three, and 8 wavefronts in
-// two groups: group kg takes the 16-deep half kg of every slice, so a
-// wavefront's tile is 32 WM x 32 (WM = 2: 9 fragments from LDS for 12 products,
-// where 32 x 32 tiles read a fragment per 32-cycle product, all that the LDS
-// gives the four SIMDs) with two wavefronts per SIMD, and the groups' sums are
-// added through LDS at the end, each group finishing half of the rows.  A
-// slice's fragments are read while the products of the slice before run.
-// Copies from L2 bound it (a third of the cycles are products): with row-major
-// operands this and a kernel of 4 wavefronts on 64 x 64 tiles took the same time,
-// with operands in slices (op_at) 2400 rows of 768 columns, 12 layers, three
-// programs encoded: 5.26 -> 4.76 ms (products 3.74 -> 3.37; N 3072, K 768 110 ->
-// 101 us, N 768, K 3072 99 -> 90).
+// Tiles are 64 x 64, slices of 32 in a ring of three, and 8 wavefronts in two
+// groups: group kg takes the 16-deep half kg of every slice, and the groups' sums
+// are added through LDS at the end, each group finishing half of the rows.  With
+// two workgroups per compute unit that is four wavefronts per SIMD.  A slice's
+// fragments are read while the products of the slice before run.  Copies from
+// L2 bound it (a third of the cycles are products): operands in slices (op_at)
+// took the products of 2400 rows of 768 columns from 3.74 to 3.37 ms over 12
+// layers.  128 x 64 tiles, which read a quarter fewer bytes from LDS but leave two
+// wavefronts per SIMD, are slower (encoder calls, 64 / 128 rows, ms: 300 rows 1.83
+// / 1.91, 1200 2.69 / 2.76, 1600 3.33 / 3.61, 2000 3.79 / 4.12).  A call of 2400 rows, with
+// 4 wavefronts on 64 x 64 tiles of row-major operands, then this kernel: 5.22, 4.65
+// ms.
 struct Gemm3Args {
   const __bf16 *A, *W;      // planes a_plane, w_plane elements apart
   void* C;                  // float32, or planes c_plane elements apart
@@ -881,10 +881,10 @@ struct Gemm3Args {
   size_t a_plane, w_plane, c_plane;
   int M, N, K, tiles_n, gelu;
 };
-template <int WM, bool SPLIT_OUT>
-__global__ __launch_bounds__(512, WM == 1 ? 4 : 2) void gemm16x3_kernel(const Gemm3Args g) {
-  constexpr int BM = 64 * WM, BN = 64, PA = BM * GK, PB = BN * GK, SLICE = 3 * (PA + PB);
-  constexpr int NR = 8 * WM;                    // rows that a lane finishes
+template <bool SPLIT_OUT>
+__global__ __launch_bounds__(512, 4) void gemm16x3_kernel(const Gemm3Args g) {
+  constexpr int BM = 64, BN = 64, PL = BM * GK, SLICE = 6 * PL;   // planes: A hi, mid, lo, W hi, mid, lo
+  constexpr int NR = 8;                         // rows that a lane finishes
   __shared__ __attribute__((aligned(16))) __bf16 S[3 * SLICE];
   static_assert(4 * NR * 256 * 4 <= sizeof(S), "the groups' exchange takes the ring's place");
   const int tid = threadIdx.x, lane = tid & 63, q = tid & 255;
@@ -897,60 +897,40 @@ __global__ __launch_bounds__(512, WM == 1 ? 4 : 2) void gemm16x3_kernel(const Ge
   const int rows = min(BM, g.M - m0), cols = min(BN, g.N - n0);
   const int kg = wave >> 2, wm = wave & 1, wn = (wave >> 1) & 1;
   const int nk = g.K / GK;
-  const uint32_t oa = slice_offset<1>(WM == 2 ? tid : q, rows), ob = slice_offset<1>(q, cols);
-  // WM = 2: a plane of A is 512 units, one per thread, a plane of W 256: group 0
-  // copies two of them, group 1 one.  WM = 1: group 0 copies A, group 1 W.
+  const uint32_t oa = slice_offset<1>(q, rows), ob = slice_offset<1>(q, cols);
+  // a plane is 256 units: group 0 copies A, group 1 W
   auto copy = [&](int s, int b) {
     __bf16* d = S + b * SLICE + (wave & 3) * 512;
-    auto copy_a = [&](int p, __bf16* to) { copy16(slice_of(g.A + p * g.a_plane, m0, rows, g.M, s), to + p * PA, oa); };
-    auto copy_w = [&](int p) { copy16(slice_of(g.W + p * g.w_plane, n0, cols, g.N, s), d + 3 * PA + p * PB, ob); };
-    if constexpr (WM == 2) {
 #pragma unroll
-      for (int p = 0; p < 3; ++p) copy_a(p, d + kg * 2048);
-      if (kg == 0) {
-        copy_w(0);
-        copy_w(1);
-      } else {
-        copy_w(2);
-      }
-    } else if (kg == 0) {
-#pragma unroll
-      for (int p = 0; p < 3; ++p) copy_a(p, d);
-    } else {
-#pragma unroll
-      for (int p = 0; p < 3; ++p) copy_w(p);
+    for (int p = 0; p < 3; ++p) {
+      if (kg == 0) copy16(slice_of(g.A + p * g.a_plane, m0, rows, g.M, s), d + p * PL, oa);
+      else copy16(slice_of(g.W + p * g.w_plane, n0, cols, g.N, s), d + (3 + p) * PL, ob);
     }
   };
   // at most `slices` slices' copies of this wavefront outstanding, LDS reads done
   auto wait = [&](int slices) {
     if (slices == 0) wait_counts<0, true>();
-    else if (WM == 1) { if (slices == 1) wait_counts<3, true>(); else wait_counts<6, true>(); }
-    else if (kg == 0) { if (slices == 1) wait_counts<5, true>(); else wait_counts<10, true>(); }
-    else { if (slices == 1) wait_counts<4, true>(); else wait_counts<8, true>(); }
+    else if (slices == 1) wait_counts<3, true>();
+    else wait_counts<6, true>();
   };
   const int fo = cl * GK + (((2 * kg + h) ^ (cl >> 2)) & 3) * 8;
-  struct Frags { bf16x8 a[WM][3], b[3]; };
+  struct Frags { bf16x8 a[3], b[3]; };
   auto read = [&](int b, Frags& f) {
     const __bf16* base = S + b * SLICE + fo;
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
-#pragma unroll
-      for (int i = 0; i < WM; ++i) f.a[i][p] = *reinterpret_cast<const bf16x8*>(base + p * PA + (wm * WM + i) * 32 * GK);
-      f.b[p] = *reinterpret_cast<const bf16x8*>(base + 3 * PA + p * PB + wn * 32 * GK);
+      f.a[p] = *reinterpret_cast<const bf16x8*>(base + p * PL + wm * 32 * GK);
+      f.b[p] = *reinterpret_cast<const bf16x8*>(base + (3 + p) * PL + wn * 32 * GK);
     }
   };
-  f32x16 hi[WM], lo[WM];
-#pragma unroll
-  for (int i = 0; i < WM; ++i) hi[i] = lo[i] = f32x16{};
+  f32x16 hi = {}, lo = {};
   auto products = [&](const Frags& f) {
-    constexpr int PI[6] = {0, 2, 1, 0, 1, 0}, PJ[6] = {0, 0, 1, 2, 0, 1};   // largest first, then the small ones
-#pragma unroll
-    for (int u = 0; u < 6; ++u)
-#pragma unroll
-      for (int i = 0; i < WM; ++i) {
-        if (u == 0) hi[i] = BF::mfma(f.a[i][0], f.b[0], hi[i]);
-        else lo[i] = BF::mfma(f.a[i][PI[u]], f.b[PJ[u]], lo[i]);
-      }
+    hi = BF::mfma(f.a[0], f.b[0], hi);
+    lo = BF::mfma(f.a[2], f.b[0], lo);
+    lo = BF::mfma(f.a[1], f.b[1], lo);
+    lo = BF::mfma(f.a[0], f.b[2], lo);
+    lo = BF::mfma(f.a[1], f.b[0], lo);
+    lo = BF::mfma(f.a[0], f.b[1], lo);
   };
   // Step s multiplies slice s from registers, reads slice s + 1 and copies slice
   // s + 3 into slice s's buffer, which every wavefront has read by the barrier;
@@ -976,15 +956,14 @@ __global__ __launch_bounds__(512, WM == 1 ? 4 : 2) void gemm16x3_kernel(const Ge
     step(s, f0, f1);
     if (s + 1 < nk) step(s + 1, f1, f0);
   }
-  // the groups' sums: each hands over the rows that the other finishes (WM = 2:
-  // group kg finishes the row tile kg, WM = 1: half kg of the lane's 16 rows)
+  // the groups' sums: each hands over the half of the lane's 16 rows that the other
+  // finishes (group kg: half kg)
   float* x = reinterpret_cast<float*>(S);        // [group][hi, lo][NR][256]
   __syncthreads();                               // the ring has been read
   float vh[NR], vl[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    const float h0 = hi[0][r], h1 = WM == 2 ? hi[WM - 1][r] : hi[0][8 + r % 8];
-    const float l0 = lo[0][r], l1 = WM == 2 ? lo[WM - 1][r] : lo[0][8 + r % 8];
+    const float h0 = hi[r], h1 = hi[8 + r], l0 = lo[r], l1 = lo[8 + r];
     vh[r] = kg ? h1 : h0;
     vl[r] = kg ? l1 : l0;
     x[((kg * 2 + 0) * NR + r) * 256 + q] = kg ? h0 : h1;
@@ -995,7 +974,7 @@ __global__ __launch_bounds__(512, WM == 1 ? 4 : 2) void gemm16x3_kernel(const Ge
   if (n >= g.N) return;
   const float bias = g.bias[n];
   const float lg = g.res ? g.ln_g[n] : 0.0f, lb = g.res ? g.ln_b[n] : 0.0f;
-  const int mt = m0 + wm * 32 * WM + (WM == 2 ? kg * 32 : kg * 16) + 4 * h;
+  const int mt = m0 + wm * 32 + kg * 16 + 4 * h;
   float y[NR];
   float2 st[NR];
 #pragma unroll
@@ -1507,15 +1486,9 @@ wm_status wm_encode_text(const wm_text_model* m, const int32_t* tokens, const in
     g.a_plane = (size_t)rows * K; g.w_plane = w_plane; g.c_plane = (size_t)rows * N;
     g.M = rows; g.N = N; g.K = K; g.gelu = gelu;
     g.tiles_n = (N + 63) / 64;
-    auto go = [&](auto kern, int bm) {
-      hipLaunchKernelGGL(kern, dim3(((rows + bm - 1) / bm) * g.tiles_n), dim3(512), 0, st, g);
-    };
-    // 128 x 64 tiles where they fill half of the compute units (one each)
-    if ((long long)((rows + 127) / 128) * g.tiles_n >= 128) {
-      if (split) go(gemm16x3_kernel<2, true>, 128); else go(gemm16x3_kernel<2, false>, 128);
-    } else {
-      if (split) go(gemm16x3_kernel<1, true>, 64); else go(gemm16x3_kernel<1, false>, 64);
-    }
+    const dim3 grid(((rows + 63) / 64) * g.tiles_n);
+    if (split) hipLaunchKernelGGL(gemm16x3_kernel<true>, grid, dim3(512), 0, st, g);
+    else hipLaunchKernelGGL(gemm16x3_kernel<false>, grid, dim3(512), 0, st, g);
     return hipGetLastError();
   };
   auto ln = [&](const float* yin, const float* gm, const float* bt, __bf16* hbo) {

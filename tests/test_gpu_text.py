@@ -126,8 +126,7 @@ def test_product_tiles(wm, S, n):
 @pytest.mark.parametrize("S,n,hidden,heads,ffn", [
     (3, 70, 32, 1, 64), (4, 90, 96, 3, 160), (200, 190, 96, 3, 160), (256, 230, 32, 1, 96)])
 def test_float32_product_tiles(wm, S, n, hidden, heads, ffn):
-    """Both tile heights of the float32 products (64 rows for few rows, 128 for
-    many), contractions of 1 to 5 slices (shorter and longer than the ring of
+    """The float32 products with few and many tiles and ragged last ones, contractions of 1 to 5 slices (shorter and longer than the ring of
     three) and output widths whose last 64-column tile holds 32 columns.  The bound is
     that of the float32 shapes above."""
     w = synth.TextWorkload(name="tiles32", S=S, vocab=500, hidden=hidden, heads=heads, ffn=ffn, layers=2, window=64,
