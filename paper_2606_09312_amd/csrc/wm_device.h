@@ -98,27 +98,49 @@ struct PF32 : GeomF32 {
   }
 };
 
-// GELU(x) = x Phi(x) = max(x, 0) - |x| Phi(-|x|), with Phi(-a) = 2^Q(a) and Q
-// the degree-6 polynomial that minimises the largest |a 2^Q(a) - a Phi(-a)|
-// (a Lawson-weighted least-squares fit in float64; that maximum is 5.1e-8).
-// Past a = 10 the argument is clamped: 10 * 2^Q(10) = 3e-22.  What bounds it
-// is the vector unit (the rollout's second unit beside the matrix cores), so
-// instructions count: one exp2 (quarter rate), six multiply-adds, a minimum, a
-// maximum and a last multiply-add, 13 full-rate slots against 19 for the erf of
-// Abramowitz & Stegun 7.1.26 (a reciprocal and an exp2), and closer to float64
-// over [-12, 12]: largest error 2.8e-7 against 3.7e-7, 4.1e-8 rms against
-// 5.5e-8 on N(0, 1).  The minimum and the maximum propagate NaN; -inf gives -3e-22, inf gives
-// inf.
-__device__ __forceinline__ float gelu(float x) {
+// GELU(x) = x Phi(x) = max(x, 0) - |x| Phi(-|x|), with Phi(-a) = 2^Q(a) and Q a
+// polynomial whose constant is pinned at -1, so that GELU(x) -> x / 2 holds to
+// rounding near 0 (a free constant of degree 6 had the smaller largest error, but
+// left GELU(x) / x off by 4.8e-6 there).  What bounds it is the vector unit (the
+// rollout's second unit beside the matrix cores), so instructions count: one exp2
+// (quarter rate), the multiply-adds of Q, a minimum, a maximum and a last
+// multiply-add.  Past a = 10 the argument is clamped: 10 * 2^Q(10) < 1e-16.  The
+// minimum and the maximum propagate NaN; -inf gives that value, inf gives inf.
+//
+// Degree 7 (14 full-rate slots; 19 for x (1 + erf) / 2 with the erf of Abramowitz &
+// Stegun 7.1.26, a reciprocal and an exp2) minimises the largest |a 2^Q - a Phi(-a)|
+// max(1, 1 / a)^0.9 (Lawson-weighted least squares in float64): at most 6.8e-8.  In
+// float32, relative 2-norm error on N(0, s), s = 0.01, 0.03, 0.1, 0.3, 1, 3: 9.1e-8,
+// 1.5e-7, 1.1e-7, 9.7e-8, 5.6e-8, 2.8e-8, where that erf gives 1.6e-7, 1.8e-7, 1.5e-7,
+// 1.2e-7, 8.4e-8, 4.9e-8.
+//
+// Degree 6 (13 slots) is for values that are rounded to bf16 next: at most 1.3e-7,
+// and 6.8e-7 |GELU(x)| up to 0.3; the rounded values' distance from float64 on the
+// same arguments (1.657e-3 to 1.673e-3) is that of the other two forms to seven
+// digits.  Whole bf16 calls, degree 6 / 7, us: 65,536 candidates at d = 256 1290 /
+// 1317, d = 512 8390 / 8485.
+template <bool TO_BF16>
+__device__ __forceinline__ float gelu_as(float x) {
   const float a = __builtin_elementwise_minimum(fabsf(x), 10.0f);
-  float q = fmaf(3.309277963126078e-05f, a, -0.0007692193612456322f);
-  q = fmaf(q, a, 0.00808071531355381f);
-  q = fmaf(q, a, -0.05341210216283798f);
-  q = fmaf(q, a, -0.4587709605693817f);
-  q = fmaf(q, a, -1.1512017250061035f);
-  q = fmaf(q, a, -0.999993085861206f);
+  float q;
+  if constexpr (TO_BF16) {
+    q = fmaf(2.657304867170751e-05f, a, -0.0007110100123099983f);
+    q = fmaf(q, a, 0.00788567028939724f);
+    q = fmaf(q, a, -0.05310521274805069f);
+    q = fmaf(q, a, -0.4590018391609192f);
+    q = fmaf(q, a, -1.1511276960372925f);
+  } else {
+    q = fmaf(6.195338755787816e-06f, a, -3.336321242386475e-05f);
+    q = fmaf(q, a, -0.0004906480899080634f);
+    q = fmaf(q, a, 0.007498874794691801f);
+    q = fmaf(q, a, -0.052773069590330124f);
+    q = fmaf(q, a, -0.4591276943683624f);
+    q = fmaf(q, a, -1.1511129140853882f);
+  }
+  q = fmaf(q, a, -1.0f);
   return fmaf(-a, __builtin_amdgcn_exp2f(q), __builtin_elementwise_maximum(x, 0.0f));
 }
+__device__ __forceinline__ float gelu(float x) { return gelu_as<false>(x); }
 
 // log2 of an integer parameter: for the normal floats that integers >= 1 give,
 // log2f is this one instruction (its denormal scaling left out).

@@ -283,7 +283,8 @@ struct Roll {
     typename PR::Packed gp[PAIRS];
     if constexpr (DO_G2 && N1 == 0) {      // nothing to hide the GELU under
 #pragma unroll
-      for (int q = 0; q < PAIRS; ++q) gp[q] = PR::pack2(gelu(acc1[2 * q]), gelu(acc1[2 * q + 1]), mask);
+      for (int q = 0; q < PAIRS; ++q)
+        gp[q] = PR::pack2(gelu_as<PR::G == 1>(acc1[2 * q]), gelu_as<PR::G == 1>(acc1[2 * q + 1]), mask);
     }
     u32x4 ring[P];
 #pragma unroll
@@ -318,7 +319,8 @@ struct Roll {
           // value pairs spread evenly over the N1 items of the first product
 #pragma unroll
           for (int q = 0; q < PAIRS; ++q)
-            if ((q * N1) / PAIRS == i) gp[q] = PR::pack2(gelu(acc1[2 * q]), gelu(acc1[2 * q + 1]), mask);
+            if ((q * N1) / PAIRS == i)
+              gp[q] = PR::pack2(gelu_as<PR::G == 1>(acc1[2 * q]), gelu_as<PR::G == 1>(acc1[2 * q + 1]), mask);
         }
       } else {
 #pragma unroll
@@ -1066,7 +1068,8 @@ __global__ __launch_bounds__(64 * SPLIT, 1) void rollout_split_kernel(const Roll
 #pragma unroll
               for (int j = 0; j < 4; ++j) acc[4 * r4 + j] += b1v[r4][j];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) gp[q] = PR::pack2(gelu(acc[2 * q]), gelu(acc[2 * q + 1]), amask);
+            for (int q = 0; q < 8; ++q)
+              gp[q] = PR::pack2(gelu_as<PR::G == 1>(acc[2 * q]), gelu_as<PR::G == 1>(acc[2 * q + 1]), amask);
           }
         } else {
 #pragma unroll
@@ -1518,7 +1521,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
           if constexpr (TRAIN) {
             f32x16 gv;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) gv[r] = op_value<PR>(gelu(acc[r]));
+            for (int r = 0; r < 16; ++r) gv[r] = op_value<PR>(gelu_as<PR::G == 1>(acc[r]));
 #pragma unroll
             for (int q = 0; q < 8; ++q) gp[q] = PR::pack2(gv[2 * q], gv[2 * q + 1], amask);
             if (active) {
@@ -1527,7 +1530,8 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
             }
           } else {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) gp[q] = PR::pack2(gelu(acc[2 * q]), gelu(acc[2 * q + 1]), amask);
+            for (int q = 0; q < 8; ++q)
+              gp[q] = PR::pack2(gelu_as<PR::G == 1>(acc[2 * q]), gelu_as<PR::G == 1>(acc[2 * q + 1]), amask);
           }
 #pragma unroll
           for (int f = 0; f < NF2; ++f)
@@ -2135,7 +2139,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
         const int r_in = i % NPC;
         // the previous chunk's GELU number r_in
         if (DEFER && cw > 0 && r_in < 8) {
-          gvp[r_in] = gelu(pend[r_in]);
+          gvp[r_in] = gelu_as<GPK == 1>(pend[r_in]);
           if (r_in == 7) finish_chunk(cw - 1, gvp);
         }
         const int xq = cw * NK + kf;
@@ -2162,7 +2166,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArg
           if (!DEFER || cw == NCW - 1) {   // last chunk: GELU, rounding, mask now
             float gv[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) gv[j] = gelu(av8[j]);
+            for (int j = 0; j < 8; ++j) gv[j] = gelu_as<GPK == 1>(av8[j]);
             finish_chunk(cw, gv);
           } else {
 #pragma unroll
@@ -2689,8 +2693,10 @@ struct TrainArgs {
   int B, T_max, P_, K, H, tab_bytes;
 };
 
-// d/dx [x Phi(x)] = Phi(x) + x phi(x), with erf from the same Abramowitz &
-// Stegun 7.1.26 form as gelu() and phi(x) = exp(-x^2/2) / sqrt(2 pi).
+// d/dx [x Phi(x)] = Phi(x) + x phi(x), with phi(x) = exp(-x^2/2) / sqrt(2 pi) and
+// erf from Abramowitz & Stegun, Handbook of Mathematical Functions, 7.1.26:
+// erf(a) = 1 - (a1 t + ... + a5 t^5) exp(-a^2), t = 1 / (1 + p a), error 1.5e-7
+// (the exponential is phi's too).
 __device__ __forceinline__ float gelu_grad(float x) {
   const float ax = fabsf(x);
   const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, ax, 1.0f));
@@ -2905,7 +2911,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void train_fwd_kernel(const TrainArg
           if (i == N1 - 1) {
             f32x16 gv;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) gv[r] = op_value<PR>(gelu(acc[r]));
+            for (int r = 0; r < 16; ++r) gv[r] = op_value<PR>(gelu_as<PR::G == 1>(acc[r]));
 #pragma unroll
             for (int q = 0; q < 8; ++q) gp[q] = PR::pack2(gv[2 * q], gv[2 * q + 1], amask);
             if (active) {

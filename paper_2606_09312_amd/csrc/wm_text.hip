@@ -510,7 +510,7 @@ __device__ __forceinline__ void gemm16_epilogue(const Gemm16Args& g, const f32x1
       for (int j = 0; j < TN; ++j) v[j] = acc[i < 0 ? 0 : i >> 1][j][8 * (i & 1) + r] + bias[j];
       if (g.gelu) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) v[j] = gelu(v[j]);
+        for (int j = 0; j < TN; ++j) v[j] = gelu_as<OUT16>(v[j]);
       }
       if constexpr (OUT16) {
         typedef __bf16 bv __attribute__((ext_vector_type(TN)));

@@ -281,6 +281,34 @@ def test_scores_in_the_rollout_hardware_widths(wm, name, prec, norm, hw_dim, n_h
     check_topk_vs_oracle(g["idx"], ref["scores"], I["seg_off"], k, tol)
 
 
+def test_gelu_against_float64(wm):
+    """The kernels' GELU, value by value in float32: an encoder with identity
+    matrices and zero biases returns it unchanged.  The bounds hold for its evaluation
+    through an erf with an absolute error of 1.5e-7 (relative 2-norm 1.8e-7 at most
+    on N(0, s); single values 6.2e-7 of GELU(x) up to |x| = 0.5 and 3.8e-7 absolute beyond),
+    so they also say that nothing is lost against that form at any scale of
+    the arguments, the small ones above all."""
+    w = dataclasses.replace(synth.workload("tiny"), feat_dim=64, enc_hidden=64)
+    W = dict(synth.make_weights(w, 1000))
+    W["we1"], W["we2"] = np.eye(64, dtype=np.float32), np.eye(64, dtype=np.float32)
+    W["be1"], W["be2"] = np.zeros(64, np.float32), np.zeros(64, np.float32)
+    model = wm.Model(wm.model_dims(w), W, precision="fp32")
+    rng = np.random.default_rng(3)
+    for s in (0.001, 0.003, 0.01, 0.03, 0.1, 0.3, 1.0, 3.0):
+        x = torch.from_numpy((s * rng.standard_normal((2048, 64))).astype(np.float32)).cuda()
+        z = torch.empty((2048, 64), device="cuda")
+        wm.encode_init(model, x, z)
+        xd, got = x.cpu().double(), z.cpu().double()
+        want = 0.5 * xd * torch.special.erfc(-xd / 2.0 ** 0.5)
+        rel = ((got - want).norm() / want.norm()).item()
+        small = xd.abs() <= 0.5
+        rs = ((got - want).abs() / want.abs().clamp_min(1e-300))[small].max().item()
+        print(f"[gelu] N(0, {s}): rel {rel:.2e}, values up to 0.5 {rs:.2e}", flush=True)
+        assert rel <= 1.8e-7
+        assert rs <= 6.2e-7
+        assert (got - want).abs().max().item() <= 3.8e-7
+
+
 @pytest.mark.parametrize("what", ["len_high", "len_negative", "type", "param"])
 def test_device_error_word(wm, what):
     w = synth.scaled(synth.workload("tiny"), B=64)
