@@ -2331,10 +2331,10 @@ __device__ __forceinline__ float wave_sum(float x) {
 // each, lane q the steps q, q + NL, ...; kinds are counted in LDS (one atomic
 // per step), the log2-parameter sums (and maxima) stay in registers and are
 // completed over the NL lanes.  Row c of `cnt` holds candidate c's K counts.
-// NL = 4 keeps a large batch's loads dense; below FEAT_WIDE_BATCH candidates the
-// kernel is as long as one lane's chain of loads, and NL = 16 shortens it.
+// A lane adds its terms one after another, so NL also sets the rounding of the sums
+// (relative rms error of the mean, 2048 to 4096 steps: 64 lanes 5.9e-8, 16 lanes
+// 2.5e-7, 4 lanes 8.8e-7; 16 lanes equal 64 up to 1024 steps).
 constexpr int FEAT_THREADS = 256, FEAT_CNT = 33;              // row stride of the counts
-constexpr int FEAT_WIDE_BATCH = 16384;
 
 template <int NL, bool CLAMP, bool MAX>
 __device__ __forceinline__ void action_sums(const int32_t* types, const int32_t* params, const int32_t* lens,
@@ -2382,8 +2382,8 @@ __device__ __forceinline__ void action_sums(const int32_t* types, const int32_t*
 // thread holds one feature's column of the embedding tables (K + P weights) in
 // registers and forms it for every fourth, second, ... of the workgroup's
 // candidates (the counts and log2 sums are LDS broadcasts), instead of loading
-// the tables again per candidate: 65,536 candidates of 8 to 48 steps, E = 128:
-// 95 -> 60 us.
+// the tables again per candidate: 65,536 candidates, lengths uniform in 1..48, E = 128,
+// 94 -> 49 us (4 lanes per candidate: 58; 16,384 of up to 2048 steps 296 -> 285, 4 lanes: 714).
 template <int E, int NL>
 __global__ __launch_bounds__(FEAT_THREADS) void phi_kernel(const float* __restrict__ emb,
                                                    const int32_t* __restrict__ types,
@@ -2434,8 +2434,9 @@ __global__ __launch_bounds__(FEAT_THREADS) void phi_kernel(const float* __restri
 // number of steps of each kind, the length, and per parameter slot the mean
 // and the maximum of log2(param) over the steps (all zero when the sequence
 // is empty); kinds outside [0, K) are not counted.  The workgroup's rows are
-// one contiguous range of the output and are stored from LDS: 65,536
-// candidates: 69 -> 39 us (one wavefront per candidate, ballots per kind).
+// one contiguous range of the output and are stored from LDS.  Lengths uniform from 1, us
+// (one wavefront per candidate with ballots per kind / this): 65,536 candidates, T = 48
+// 64 / 26, 128 83 / 56, 512 215 / 194; 2048 candidates, T = 1024 30 / 21.
 
 template <int NL>
 __global__ __launch_bounds__(FEAT_THREADS) void phi_struct_kernel(const int32_t* __restrict__ types,
@@ -5056,16 +5057,15 @@ hipError_t launch_phi(const DevModel& m, const int32_t* types, const int32_t* pa
                       const int32_t* lens, int32_t B, int32_t T_max, float* phi, hipStream_t st) {
   const int E = m.dims.embed_dim;
   if (B == 0) return hipSuccess;
-  const bool wide = B < FEAT_WIDE_BATCH;
+  constexpr int NL = 16, CPB = FEAT_THREADS / NL;
   auto go = [&](auto kern) {
-    const int cpb = FEAT_THREADS / (wide ? 16 : 4);
-    hipLaunchKernelGGL(kern, dim3((B + cpb - 1) / cpb), dim3(FEAT_THREADS), 0, st, m.emb_nat, types, params, lens, B,
+    hipLaunchKernelGGL(kern, dim3((B + CPB - 1) / CPB), dim3(FEAT_THREADS), 0, st, m.emb_nat, types, params, lens, B,
                        T_max, m.dims.n_params, m.dims.n_kinds, phi);
     return hipGetLastError();
   };
-  if (E == 32) return wide ? go(phi_kernel<32, 16>) : go(phi_kernel<32, 4>);
-  if (E == 64) return wide ? go(phi_kernel<64, 16>) : go(phi_kernel<64, 4>);
-  if (E == 128) return wide ? go(phi_kernel<128, 16>) : go(phi_kernel<128, 4>);
+  if (E == 32) return go(phi_kernel<32, NL>);
+  if (E == 64) return go(phi_kernel<64, NL>);
+  if (E == 128) return go(phi_kernel<128, NL>);
   return hipErrorInvalidValue;            // the embedding widths of have_kernels
 }
 
@@ -5074,11 +5074,22 @@ hipError_t launch_phi_struct(const int32_t* types, const int32_t* params, const 
                              hipStream_t st) {
   if (B == 0) return hipSuccess;
   if (K > 32 || P > PMAX) return hipErrorInvalidValue;
-  const bool wide = B < FEAT_WIDE_BATCH;
-  const int cpb = FEAT_THREADS / (wide ? 16 : 4);
-  hipLaunchKernelGGL(wide ? phi_struct_kernel<16> : phi_struct_kernel<4>, dim3((B + cpb - 1) / cpb), dim3(FEAT_THREADS),
-                     0, st, types, params, lens, B, T_max, K, P, phi_s);
-  return hipGetLastError();
+  // Lanes per candidate: a few steps per lane, so that a long sequence is no long
+  // chain of loads in one lane and its sums keep their accuracy; fewer where short
+  // sequences of many candidates would leave lanes idle.  us for 8 / 16 / 32 / 64
+  // lanes, lengths uniform from 1: 65,536 candidates, T = 8 10 / 15 / 28 / 58, 48 28 / 26
+  // / 40 / 60, 128 57 / 51 / 56 / 75, 512 302 / 231 / 208 / 194; 256 candidates, T = 256
+  // 26 / 15 / 10 / 8, 1024 91 / 46 / 25 / 15; 32,768 candidates, T = 32 11 / 12 / 17 / 32.
+  auto go = [&](auto kern, int nl) {
+    const int cpb = FEAT_THREADS / nl;
+    hipLaunchKernelGGL(kern, dim3((B + cpb - 1) / cpb), dim3(FEAT_THREADS), 0, st, types, params, lens, B, T_max, K, P,
+                       phi_s);
+    return hipGetLastError();
+  };
+  if (T_max <= 32 && B >= 32768) return go(phi_struct_kernel<8>, 8);
+  if (T_max <= 64) return go(phi_struct_kernel<16>, 16);
+  if (T_max <= 256) return go(phi_struct_kernel<32>, 32);
+  return go(phi_struct_kernel<64>, 64);
 }
 
 hipError_t launch_score_trees(const DevForest& f, const float* zT, int32_t d, const float* phi_s,

@@ -33,10 +33,12 @@ def _forest(wm, w, seed, **kw):
     return wm.Forest(f["feat"], f["thr"], f["leaf"], float(f["base"]), n_feat), f
 
 
-@pytest.mark.parametrize("B,T_max,len_lo", [(333, 32, 0), (333, 100, 60), (16384 + 5, 9, 0)])
+@pytest.mark.parametrize("B,T_max,len_lo", [(333, 32, 0), (333, 100, 60), (16384 + 5, 9, 0), (32768 + 5, 32, 0),
+                                           (333, 33, 0), (333, 64, 0), (333, 65, 0), (99, 256, 0), (99, 257, 0)])
 def test_phi_struct_matches_oracle(wm, B, T_max, len_lo):
-    """Both lane counts per candidate (16 below 16384 candidates, 4 above), a
-    partial last workgroup."""
+    """Each number of lanes per candidate (8 for many short sequences, 16, 32
+    and 64 with the padded width) on both sides of its limits, a partial last
+    workgroup."""
     w = synth.scaled(synth.workload("ansor_round"), B=B, len_lo=len_lo, len_hi=T_max, T_max=T_max)
     I = synth.make_inputs(w, 61, pad="garbage")
     I["lens"][:4] = 0
@@ -48,6 +50,27 @@ def test_phi_struct_matches_oracle(wm, B, T_max, len_lo):
     K = w.n_kinds
     np.testing.assert_array_equal(got[:, :K + 1], want[:, :K + 1])      # counts and length exact
     np.testing.assert_allclose(got[:, K + 1:], want[:, K + 1:], rtol=2e-6, atol=2e-6)
+
+
+@pytest.mark.parametrize("B,T_max", [(64, 4096), (8192 + 3, 512), (16384 + 5, 512)])
+def test_phi_struct_long_sequences_accuracy(wm, B, T_max):
+    """The means of log2(params) over long sequences to float32 accuracy: terms
+    and mean rounded once each are 4e-8 relative rms; partial sums of up to 64
+    positive terms in a lane, completed pairwise over the lanes, add less than
+    that (their rounding errors are independent), and 1e-7 bounds the total.  Sums
+    of hundreds of terms in one lane exceed it."""
+    w = synth.scaled(synth.workload("ansor_round"), B=B, len_lo=T_max // 2, len_hi=T_max, T_max=T_max)
+    I = synth.make_inputs(w, 67)
+    t = to_dev(I, "cuda")
+    out = torch.empty((w.B, TR.phi_dim(w.n_kinds, w.n_params)), device="cuda")
+    wm.phi_struct(t["types"], t["params"], t["lens"], w.n_kinds, out)
+    pick = np.arange(0, B, max(1, B // 512))
+    want = TR.structured_phi(I["types"][pick], I["params"][pick], I["lens"][pick], w.n_kinds)
+    m = slice(w.n_kinds + 1, w.n_kinds + 1 + w.n_params)
+    got = out.cpu().numpy().astype(np.float64)[pick]
+    rms = np.sqrt(np.mean((got[:, m] / want[:, m] - 1.0) ** 2))
+    print(f"[phi_s] B={B} T={T_max}: rms {rms:.2e}", flush=True)
+    assert rms <= 1e-7
 
 
 @pytest.mark.parametrize("n_trees,depth", [(256, 8), (300, 6), (5, 1), (64, 12)])
