@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cmath>
 #include <type_traits>
 
 #include "wm_device.h"
@@ -4523,10 +4524,14 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_kernel(const float* __rest
 // before -> after: 65,536 scores, k = 256: 94 -> 26; 2,048, k = 64: 11.6 -> 5.4;
 // 256, k = 16: 8.1 -> 4.1.
 //
-// Where more than TOPK_CAP candidates reach the bound (many equal scores), a
-// most-significant-digit radix select finds the k-th largest key K*, a second
-// one over the (complemented) local index finds how many candidates tied at
-// K* to keep, lowest index first, and the k selected are sorted.
+// Otherwise a most-significant-digit radix select finds the k-th largest key K*,
+// a second one over the (complemented) local index finds how many candidates
+// tied at K* to keep, lowest index first, and the k selected are sorted.  It runs
+// over the candidates at the bound where those are too many to sort, and over all
+// scores where they are too many to collect (equal scores) or the segment is too
+// short for the bound to pay (topk_by_bound).  us, radix select for every call / this:
+// 16,384 scores, k = 1024 37 / 34, 65,536, k = 896 100 / 46, 1024 101 / 49; all equal,
+// k = 64: 2048 28 / 23, 65,536 430 / 173.
 
 __device__ __forceinline__ uint32_t score_key(float v) {
   if (v != v) return 0u;                // NaN ranks last
@@ -4537,8 +4542,12 @@ __device__ __forceinline__ uint32_t score_key(float v) {
 
 constexpr int TOPK_THREADS = 1024;
 constexpr int TOPK_WAVES = TOPK_THREADS / 64;
-constexpr int TOPK_CAP = 2048;          // candidates collected at the bound
-constexpr int TOPK_RANK = 512;          // of which are ordered by counting
+constexpr int TOPK_RANK = 512;          // candidates that are ordered by counting
+// Candidates collected at the bound: the whole segment up to 8192 scores (80 KiB of
+// LDS with the histograms: two workgroups per compute unit); past that 10,240, which
+// k = 1024 of scores in random order exceeds once in 20 segments and k = 1000 never.
+template <int KPT>
+constexpr int TOPK_CAP = KPT == 2 ? 2048 : KPT == 8 ? 8192 : 10240;
 
 // One 11-bit digit of the `need`-th largest of the threads' values whose upper
 // bits equal `prefix` (1-based; at least `need` such threads take part): returns
@@ -4581,7 +4590,9 @@ __device__ __forceinline__ uint32_t digit11_select(uint32_t v, bool in, int shif
 // Largest-first radix select over the keys that for_each(f) passes to f
 // (each thread its own elements): returns the `need`-th largest key (1-based)
 // and, in *rank_in_eq, how many elements equal to it must be taken.
-template <class ForEach>
+// TIES: the lanes that share the first one's digit are counted by one atomic
+// (equal scores would otherwise queue for one counter).
+template <bool TIES, class ForEach>
 __device__ uint32_t radix_select(int need, ForEach for_each, uint32_t* hist_w, int* shared_int,
                                  int* rank_in_eq) {
   const int tid = threadIdx.x, wave = tid >> 6;
@@ -4590,7 +4601,18 @@ __device__ uint32_t radix_select(int need, ForEach for_each, uint32_t* hist_w, i
     for (int i = tid; i < TOPK_WAVES * 256; i += TOPK_THREADS) hist_w[i] = 0;
     __syncthreads();
     for_each([&](uint32_t kk) {
-      if ((kk & mask) == prefix) atomicAdd(&hist_w[wave * 256 + ((kk >> shift) & 255)], 1u);
+      if ((kk & mask) != prefix) return;
+      const uint32_t digit = (kk >> shift) & 255;
+      uint32_t count = 1;
+      if constexpr (TIES) {
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane(digit);
+        const unsigned long long same = __ballot(digit == first);
+        if (digit == first) {
+          if (same & ((1ull << (tid & 63)) - 1)) return;     // a lower lane counts for all
+          count = (uint32_t)__popcll(same);
+        }
+      }
+      atomicAdd(&hist_w[wave * 256 + digit], count);
     });
     __syncthreads();
     // combine the per-wave histograms into the first
@@ -4642,14 +4664,15 @@ __device__ uint32_t radix_select(int need, ForEach for_each, uint32_t* hist_w, i
 
 // KPT > 0: the segment has at most KPT * TOPK_THREADS candidates and each
 // thread keeps its keys in registers across the passes; KPT = 0 reads the
-// scores again in every pass.
-template <int KPT>
+// scores again in every pass.  BOUND: see topk_by_bound.
+template <int KPT, bool BOUND>
 __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const float* __restrict__ scores,
                                                             int B, const SegTable seg, int k,
                                                             int P2, int32_t* __restrict__ idx,
                                                             float* __restrict__ val) {
   __shared__ uint32_t hist_w[TOPK_WAVES * 256];
-  __shared__ unsigned long long sel[TOPK_CAP];
+  constexpr int CAP = BOUND ? TOPK_CAP<KPT> : WM_MAX_K;
+  __shared__ unsigned long long sel[CAP];
   __shared__ int sh[4 + TOPK_WAVES];
   const int S = seg.n;
   const int j = blockIdx.x / S, s = blockIdx.x % S;
@@ -4709,78 +4732,93 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const float* __restr
     }
   };
 
-  // bound from the threads' maxima, candidates at or above it
-  {
-    uint32_t mx = 0;
-    each_key([&](uint32_t kk, int) { mx = kk > mx ? kk : mx; });
+  // the k best of the candidates that each(f) passes to f (at least k), by the radix select
+  auto take = [&](auto each) {
+    int need_eq = 0;
+    const uint32_t kstar = radix_select<BOUND>(k, [&](auto f) { each([&](uint32_t kk, int) { f(kk); }); }, hist_w, sh, &need_eq);
+    // count of keys equal to K*
+    if (tid == 0) { sh[2] = 0; sh[3] = 0; }
+    __syncthreads();
+    int my_eq = 0;
+    each([&](uint32_t kk, int) { my_eq += (kk == kstar); });
+    if (my_eq) atomicAdd(&sh[2], my_eq);
+    __syncthreads();
+    const int n_eq = sh[2];
+    // ties at K*: keep the need_eq lowest local indices (largest ~index)
+    uint32_t istar = 0;
+    if (need_eq < n_eq) {
+      int dummy = 0;
+      istar = radix_select<BOUND>(
+          need_eq,
+          [&](auto f) { each([&](uint32_t kk, int i) { if (kk == kstar) f(~(uint32_t)i); }); },
+          hist_w, sh, &dummy);
+    }
+    const uint32_t ilimit = (need_eq < n_eq) ? ~istar : 0xFFFFFFFFu;  // keep local index <= ilimit
     if (tid == 0) sh[3] = 0;
-    int need = k;
-    const uint32_t d0 = digit11_select(mx, tid < n, 21, hist_w, sh, need);
-    const uint32_t d1 = digit11_select(mx, tid < n && (mx >> 21) == d0, 10, hist_w, sh, need);
-    const uint32_t bound = (d0 << 21) | (d1 << 10);
-    each_key([&](uint32_t kk, int i) {
-      if (kk >= bound) {
+    for (int i = tid; i < P2; i += TOPK_THREADS) sel[i] = 0ull;
+    __syncthreads();
+    each([&](uint32_t kk, int i) {
+      if (kk > kstar || (kk == kstar && (uint32_t)i <= ilimit)) {
         const int slot = atomicAdd(&sh[3], 1);
-        if (slot < TOPK_CAP) sel[slot] = ((unsigned long long)kk << 32) | (unsigned long long)(~(uint32_t)i);
+        if (slot < k) sel[slot] = ((unsigned long long)kk << 32) | (unsigned long long)(~(uint32_t)i);
       }
     });
     __syncthreads();
-    const int m = sh[3];
-    if (m <= TOPK_RANK) {
-      if (tid < m) {
-        const unsigned long long e = sel[tid];
-        int r = 0;
-#pragma unroll 8
-        for (int q = 0; q < m; ++q) r += sel[q] > e;
-        if (r < k) put(r, e);
-      }
-      return;
-    }
-    if (m <= TOPK_CAP) {
-      int m2 = TOPK_RANK;
-      while (m2 < m) m2 <<= 1;
-      for (int i = m + tid; i < m2; i += TOPK_THREADS) sel[i] = 0ull;
-      __syncthreads();
-      bitonic(m2);
-      for (int r = tid; r < k; r += TOPK_THREADS) put(r, sel[r]);
-      return;
-    }
-    __syncthreads();
+    bitonic(P2);
+    for (int r = tid; r < k; r += TOPK_THREADS) put(r, sel[r]);
+  };
+  if constexpr (!BOUND) {
+    take(each_key);
+    return;
   }
 
-  int need_eq = 0;
-  const uint32_t kstar = radix_select(
-      k, [&](auto f) { each_key([&](uint32_t kk, int) { f(kk); }); }, hist_w, sh, &need_eq);
-  // count of keys equal to K*
-  if (tid == 0) { sh[2] = 0; sh[3] = 0; }
-  __syncthreads();
-  int my_eq = 0;
-  each_key([&](uint32_t kk, int) { my_eq += (kk == kstar); });
-  if (my_eq) atomicAdd(&sh[2], my_eq);
-  __syncthreads();
-  const int n_eq = sh[2];
-  // ties at K*: keep the need_eq lowest local indices (largest ~index)
-  uint32_t istar = 0;
-  if (need_eq < n_eq) {
-    int dummy = 0;
-    istar = radix_select(
-        need_eq,
-        [&](auto f) { each_key([&](uint32_t kk, int i) { if (kk == kstar) f(~(uint32_t)i); }); },
-        hist_w, sh, &dummy);
-  }
-  const uint32_t ilimit = (need_eq < n_eq) ? ~istar : 0xFFFFFFFFu;  // keep local index <= ilimit
+  // bound from the threads' maxima, candidates at or above it
+  uint32_t mx = 0;
+  each_key([&](uint32_t kk, int) { mx = kk > mx ? kk : mx; });
   if (tid == 0) sh[3] = 0;
-  for (int i = tid; i < P2; i += TOPK_THREADS) sel[i] = 0ull;
-  __syncthreads();
+  int need = k;
+  const uint32_t d0 = digit11_select(mx, tid < n, 21, hist_w, sh, need);
+  const uint32_t d1 = digit11_select(mx, tid < n && (mx >> 21) == d0, 10, hist_w, sh, need);
+  const uint32_t bound = (d0 << 21) | (d1 << 10);
   each_key([&](uint32_t kk, int i) {
-    if (kk > kstar || (kk == kstar && (uint32_t)i <= ilimit)) {
+    if (kk >= bound) {
       const int slot = atomicAdd(&sh[3], 1);
-      if (slot < k) sel[slot] = ((unsigned long long)kk << 32) | (unsigned long long)(~(uint32_t)i);
+      if (slot < CAP) sel[slot] = ((unsigned long long)kk << 32) | (unsigned long long)(~(uint32_t)i);
     }
   });
   __syncthreads();
-  bitonic(P2);
-  for (int r = tid; r < k; r += TOPK_THREADS) put(r, sel[r]);
+  const int m = sh[3];
+  if (m <= TOPK_RANK) {
+    if (tid < m) {
+      const unsigned long long e = sel[tid];
+      int r = 0;
+#pragma unroll 8
+      for (int q = 0; q < m; ++q) r += sel[q] > e;
+      if (r < k) put(r, e);
+    }
+  } else if (m <= 1024) {
+    for (int i = m + tid; i < 1024; i += TOPK_THREADS) sel[i] = 0ull;
+    __syncthreads();
+    bitonic(1024);
+    for (int r = tid; r < k; r += TOPK_THREADS) put(r, sel[r]);
+  } else if (m <= CAP) {
+    // select from the collected ones, held in registers (their place in LDS is taken by the k best)
+    unsigned long long own[CAP / TOPK_THREADS];
+#pragma unroll
+    for (int q = 0; q < CAP / TOPK_THREADS; ++q) {
+      const int i = tid + q * TOPK_THREADS;
+      own[q] = i < m ? sel[i] : 0ull;
+    }
+    __syncthreads();
+    take([&](auto f) {
+#pragma unroll
+      for (int q = 0; q < CAP / TOPK_THREADS; ++q)
+        if (tid + q * TOPK_THREADS < m) f((uint32_t)(own[q] >> 32), (int)~(uint32_t)own[q]);
+    });
+  } else if constexpr (CAP < KPT * TOPK_THREADS || KPT == 0) {
+    __syncthreads();
+    take(each_key);
+  }
 }
 
 // ==========================================================================
@@ -5164,6 +5202,21 @@ hipError_t launch_score(const DevModel& m, const float* zT, const float* phi, in
   return hipSuccess;
 }
 
+// Whether the k best of up to n scores are taken from the bound.  Of n scores in
+// random order, each of T = min(n, 1024) threads holding n / T, about
+// n (1 - (1 - k / T)^(T / n)) reach the k-th largest of the threads' maxima (within 2%
+// by simulation; 10% are allowed for).  Up to 512 are ranked by counting, more are
+// sorted or selected from; in short segments the radix select's passes over the
+// scores cost less than that.  us, bound / radix: 2048 scores, k = 256 8.8 / 14.2, 512
+// 18.9 / 17.3, 768 32 / 21.4; 4096, k = 512 20.4 / 20.2, 768 34 / 24.7; 8192, k = 512 21.4 / 22.6,
+// 1024 (5000 candidates) 30.4 / 28.1; 16,384, k = 1024 34 / 37, 65,536 49 / 101.
+bool topk_by_bound(int n, int k, int P2) {
+  if (n <= TOPK_THREADS || n > 8 * TOPK_THREADS) return true;
+  const double T = TOPK_THREADS, m = 1.1 * n * (1.0 - std::pow(1.0 - (k - 0.5) / T, T / n));
+  if (n >= 4096) return m <= (n > 4096 ? 4096.0 : 1024.0);
+  return m <= (P2 == 1024 ? 1024.0 : (double)TOPK_RANK);
+}
+
 hipError_t launch_topk(const float* scores, int32_t n_hw, int32_t B, const SegTable& seg,
                        int32_t k, int32_t* idx, float* val, hipStream_t st) {
   int P2 = 1;
@@ -5173,10 +5226,11 @@ hipError_t launch_topk(const float* scores, int32_t n_hw, int32_t B, const SegTa
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(n_hw * seg.n), dim3(TOPK_THREADS), 0, st, scores, B, seg, k, P2, idx, val);
   };
-  if (nmax <= 2 * TOPK_THREADS) go(topk_kernel<2>);
-  else if (nmax <= 8 * TOPK_THREADS) go(topk_kernel<8>);
-  else if (nmax <= 32 * TOPK_THREADS) go(topk_kernel<32>);
-  else go(topk_kernel<0>);
+  const bool bound = topk_by_bound(nmax, k, P2);
+  if (nmax <= 2 * TOPK_THREADS) bound ? go(topk_kernel<2, true>) : go(topk_kernel<2, false>);
+  else if (nmax <= 8 * TOPK_THREADS) bound ? go(topk_kernel<8, true>) : go(topk_kernel<8, false>);
+  else if (nmax <= 32 * TOPK_THREADS) go(topk_kernel<32, true>);
+  else go(topk_kernel<0, true>);
   return hipGetLastError();
 }
 

@@ -396,15 +396,22 @@ def test_separate_entry_points_match_fused(wm):
 
 @pytest.mark.parametrize("n,k,kind", [
     (1, 1, "normal"), (1023, 1023, "normal"), (1025, 1024, "normal"), (40000, 600, "normal"),
-    (65537, 1024, "normal"), (3000, 40, "equal"), (40000, 1000, "two"), (5000, 100, "nan"), (33000, 7, "one_bin")])
+    (65537, 1024, "normal"), (3000, 40, "equal"), (40000, 1000, "two"), (5000, 100, "nan"), (33000, 7, "one_bin"),
+    (2048, 300, "normal"), (2048, 512, "normal"), (4096, 512, "normal"), (2048, 768, "normal"), (2048, 1024, "normal"),
+    (32767, 768, "normal"), (32768, 768, "normal"), (65537, 900, "normal"), (1024, 1000, "equal"), (2048, 16, "equal"),
+    (2048, 1024, "equal"), (8192, 896, "normal"), (8192, 1024, "normal"), (8193, 1024, "normal"), (70000, 700, "equal"), (2048, 300, "levels"), (20000, 512, "levels"), (70000, 1024, "levels")])
 def test_topk_bound_paths(wm, n, k, kind):
-    """Each way out of the top-k's candidate collection: up to 512 candidates at
-    the bound (ranks counted), up to 2048 (sorted), more (equal scores: the radix
-    selects), more NaNs than numbers, scores that share their first 22 bits."""
+    """Each way through the top-k: up to 512 candidates at the bound (ranks
+    counted), up to 1024 or 2048 (sorted), more (equal scores: the radix selects
+    over those at the bound), the radix selects at once where the bound does not pay
+    (both sides of that rule's limits), more NaNs than numbers, scores that share
+    their first 22 bits."""
     rng = np.random.default_rng(n + k)
     y = rng.standard_normal((2, n)).astype(np.float32)
     if kind == "equal":
         y[:] = 1.5
+    elif kind == "levels":
+        y = np.round(y * 8) / np.float32(8)
     elif kind == "two":
         y = np.where(y > 2.2, np.float32(2.0), np.float32(-1.0))
     elif kind == "nan":
