@@ -335,10 +335,12 @@ wm_status wm_rollout(const wm_model* model, const float* z0, const int32_t* seg_
   uint8_t* w8 = static_cast<uint8_t*>(ws);
   int32_t* err = reinterpret_cast<int32_t*>(w8 + L.err);
   int2* perm = reinterpret_cast<int2*>(w8 + L.perm);
-  WM_TIMED(TK_BUCKET, st, launch_bucket(lens, B, T_max, seg, perm, reinterpret_cast<int32_t*>(w8 + L.hist), err, st));
+  int32_t* hist = reinterpret_cast<int32_t*>(w8 + L.hist);
+  const TileChoice choice = tile_choice(model->dm, B, T_max, hist);
+  WM_TIMED(TK_BUCKET, st, launch_bucket(lens, B, T_max, seg, perm, hist, err, st, choice));
   bool phi_done = false;
   WM_TIMED(TK_ROLLOUT, st, launch_rollout(model->dm, z0, perm, types, params, lens, B, T_max, zT, phi,
-                                          &phi_done, err, st));
+                                          &phi_done, err, st, choice));
   if (phi && !phi_done) WM_TIMED(TK_PHI, st, launch_phi(model->dm, types, params, lens, B, T_max, phi, st));
   return ok();
 }
@@ -409,13 +411,15 @@ wm_status wm_evaluate(const wm_model* model, const float* init, int32_t init_is_
   float* zTo = zT ? zT : reinterpret_cast<float*>(w8 + L.zT);
   float* phi = reinterpret_cast<float*>(w8 + L.phi);
   float* sc = scores ? scores : reinterpret_cast<float*>(w8 + L.scores);
-  WM_TIMED(TK_BUCKET, st, launch_bucket(lens, B, T_max, seg, perm, reinterpret_cast<int32_t*>(w8 + L.hist), err, st));
+  int32_t* hist = reinterpret_cast<int32_t*>(w8 + L.hist);
+  const TileChoice choice = tile_choice(model->dm, B, T_max, hist);
+  WM_TIMED(TK_BUCKET, st, launch_bucket(lens, B, T_max, seg, perm, hist, err, st, choice));
   bool phi_done = false;
   ScoreFuse sf{hw, n_hw, sc, false};
   WM_TIMED(TK_ROLLOUT, st, launch_rollout(model->dm, z0, perm, types, params, lens, B, T_max, zTo, phi,
-                                          &phi_done, err, st, &sf));
+                                          &phi_done, err, st, choice, &sf));
   if (!phi_done) WM_TIMED(TK_PHI, st, launch_phi(model->dm, types, params, lens, B, T_max, phi, st));
-  if (!sf.done) WM_TIMED(TK_SCORE, st, launch_score(model->dm, zTo, phi, B, hw, n_hw, sc, st));
+  if (!sf.done) WM_TIMED(TK_SCORE, st, launch_score(model->dm, zTo, phi, B, hw, n_hw, sc, st, sf.unless));
   WM_TIMED(TK_TOPK, st, launch_topk(sc, n_hw, B, seg, k, idx, val, st));
   return ok();
 }
@@ -442,7 +446,7 @@ wm_status wm_evaluate_noalloc(const wm_model* model, const float* init, int32_t 
   // scratch layout: permutation, bucketing histograms, encoded initial latents
   const size_t o_perm = 0;
   const size_t o_hist = align256(o_perm + (size_t)B * sizeof(int2));
-  const size_t o_z0 = align256(o_hist + (size_t)bucket_groups(B) * (size_t)(T_max + 1) * 4);
+  const size_t o_z0 = align256(o_hist + bucket_words(B, T_max) * 4);
   const size_t need = o_z0 + (init_is_feats ? (size_t)S * model->dm.dims.d * 4 : 0);
   if (need > WM_NOALLOC_SCRATCH_BYTES)
     return fail(WM_ERR_INVALID_ARGUMENT, "the batch needs " + std::to_string(need) +
@@ -458,14 +462,15 @@ wm_status wm_evaluate_noalloc(const wm_model* model, const float* init, int32_t 
     z0 = reinterpret_cast<float*>(sp + o_z0);
     WM_TIMED(TK_ENCODE, st, launch_encode(model->dm, init, S, z0, st));
   }
-  WM_TIMED(TK_BUCKET, st, launch_bucket(lens, B, T_max, seg, perm, reinterpret_cast<int32_t*>(sp + o_hist),
-                                        status, st));
+  int32_t* hist = reinterpret_cast<int32_t*>(sp + o_hist);
+  const TileChoice choice = tile_choice(model->dm, B, T_max, hist);
+  WM_TIMED(TK_BUCKET, st, launch_bucket(lens, B, T_max, seg, perm, hist, status, st, choice));
   bool phi_done = false;
   ScoreFuse sf{hw, n_hw, scores, false};
   WM_TIMED(TK_ROLLOUT, st, launch_rollout(model->dm, z0, perm, types, params, lens, B, T_max, zT, phi,
-                                          &phi_done, status, st, &sf));
+                                          &phi_done, status, st, choice, &sf));
   if (!phi_done) WM_TIMED(TK_PHI, st, launch_phi(model->dm, types, params, lens, B, T_max, phi, st));
-  if (!sf.done) WM_TIMED(TK_SCORE, st, launch_score(model->dm, zT, phi, B, hw, n_hw, scores, st));
+  if (!sf.done) WM_TIMED(TK_SCORE, st, launch_score(model->dm, zT, phi, B, hw, n_hw, scores, st, sf.unless));
   WM_TIMED(TK_TOPK, st, launch_topk(scores, n_hw, B, seg, k, idx, val, st));
   return ok();
 }
@@ -587,10 +592,12 @@ wm_status wm_evaluate_trees(const wm_model* model, const wm_forest* forest, cons
   float* zTo = zT ? zT : reinterpret_cast<float*>(w8 + L.zT);
   float* phs = reinterpret_cast<float*>(w8 + L.phi_s);
   float* sc = scores ? scores : reinterpret_cast<float*>(w8 + L.scores);
-  WM_TIMED(TK_BUCKET, st, launch_bucket(lens, B, T_max, seg, perm, reinterpret_cast<int32_t*>(w8 + L.hist), err, st));
+  int32_t* hist = reinterpret_cast<int32_t*>(w8 + L.hist);
+  const TileChoice choice = tile_choice(model->dm, B, T_max, hist);
+  WM_TIMED(TK_BUCKET, st, launch_bucket(lens, B, T_max, seg, perm, hist, err, st, choice));
   bool phi_done = false;
   WM_TIMED(TK_ROLLOUT, st, launch_rollout(model->dm, z0, perm, types, params, lens, B, T_max, zTo, nullptr,
-                                          &phi_done, err, st));
+                                          &phi_done, err, st, choice));
   WM_TIMED(TK_PHI_STRUCT, st, launch_phi_struct(types, params, lens, B, T_max, dm.n_kinds, dm.n_params, phs, st));
   WM_TIMED(TK_TREES, st, launch_score_trees(forest->df, zTo, dm.d, phs, phi_dim, B, hw, n_hw, dm.hw_dim, sc, st));
   WM_TIMED(TK_TOPK, st, launch_topk(sc, n_hw, B, seg, k, idx, val, st));

@@ -280,6 +280,8 @@ struct RollArgs {
   float* scores;
   float bc2;
   int n_hw, HW, C;
+  const int32_t* choice;    // where the lengths decide (TileChoice): run only if *choice == want
+  int32_t want;
   int lds_resident;         // narrow rollout: LDS byte offset of the resident weight groups
 };
 

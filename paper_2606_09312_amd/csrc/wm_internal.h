@@ -16,27 +16,40 @@ namespace wm {
 // zero n int32 words (a kernel rather than hipMemsetAsync, so the call is
 // safe under stream capture)
 hipError_t launch_clear_words(int32_t* p, int n, hipStream_t st);
-// hist: bucket_groups(B) * (T_max + 1) ints of workspace (unused when 0)
+// Batches in which either rollout kernel can be the faster one, depending on the
+// lengths: the bucketing writes which to `word` (1: narrow tiles, 0: the other), both are
+// launched, and the one that was not chosen returns at once.  word = null: the batch
+// size alone decides (launch_rollout).  Narrow tiles are chosen where all steps of the
+// batch are at most per_step (steps that the other kernel walks one after another - fixed).
+struct TileChoice {
+  int32_t* word = nullptr;
+  float per_step = 0.0f, fixed = 0.0f;
+};
+TileChoice tile_choice(const DevModel& m, int32_t B, int32_t T_max, int32_t* hist);
+// hist: bucket_words(B, T_max) ints of workspace (unused when 0)
 hipError_t launch_bucket(const int32_t* lens, int32_t B, int32_t T_max, const SegTable& seg,
-                         int2* perm, int32_t* hist, int32_t* err, hipStream_t st);
+                         int2* perm, int32_t* hist, int32_t* err, hipStream_t st, const TileChoice& choice = {});
 // Scores requested with a rollout (wm_evaluate): the narrow kernel computes
-// them itself when it runs and sets `done`; otherwise launch_score does.
+// them itself when it runs and sets `done`; otherwise launch_score does, on the device
+// only where *unless is 0 (when not null).
 struct ScoreFuse {
   const float* hw;
   int32_t n_hw;
   float* scores;
   bool done;
+  const int32_t* unless = nullptr;
 };
 // phi (may be null): the kernel families that can also sum the action
 // features write them and set *phi_done; otherwise launch_phi computes them.
 hipError_t launch_rollout(const DevModel& m, const float* z0, const int2* perm,
                           const int32_t* types, const int32_t* params, const int32_t* lens,
                           int32_t B, int32_t T_max, float* zT, float* phi, bool* phi_done,
-                          int32_t* err, hipStream_t st, ScoreFuse* sf = nullptr);
+                          int32_t* err, hipStream_t st, const TileChoice& choice, ScoreFuse* sf = nullptr);
 hipError_t launch_phi(const DevModel& m, const int32_t* types, const int32_t* params,
                       const int32_t* lens, int32_t B, int32_t T_max, float* phi, hipStream_t st);
 hipError_t launch_score(const DevModel& m, const float* zT, const float* phi, int32_t B,
-                        const float* hw, int32_t n_hw, float* scores, hipStream_t st);
+                        const float* hw, int32_t n_hw, float* scores, hipStream_t st,
+                        const int32_t* unless = nullptr);
 hipError_t launch_topk(const float* scores, int32_t n_hw, int32_t B, const SegTable& seg,
                        int32_t k, int32_t* idx, float* val, hipStream_t st);
 hipError_t launch_encode(const DevModel& m, const float* feats, int32_t S, float* z0,

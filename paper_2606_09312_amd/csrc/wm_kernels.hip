@@ -101,12 +101,24 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* wsum) {
   return wsum[w] + x - v;
 }
 
+// Length of the candidate at sorted position r (base: first position of each length).
+__device__ __forceinline__ int length_at(const int* base, int T_max, int r) {
+  int lo = 0, hi = T_max;                  // the last j with base[T_max - j] <= r
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (base[T_max - mid] <= r) lo = mid; else hi = mid - 1;
+  }
+  return T_max - lo;
+}
+
 __global__ __launch_bounds__(1024) void bucket_scan_kernel(int T_max, int groups,
-                                                            int32_t* __restrict__ hist) {
+                                                            int32_t* __restrict__ hist, int B, TileChoice choice) {
+  __shared__ int steps, chain;             // of all candidates; one after another past narrow tiles
   extern __shared__ int bsm[];
   int* base = bsm;                       // [nb]: first position of each length
   int* wsum = bsm + (T_max + 1);         // [16]
   const int nb = T_max + 1, tid = threadIdx.x, nt = blockDim.x;
+  if (tid == 0) { steps = 0; chain = 0; }
   // thread tid owns positions [tid*per, tid*per + per) of the length order
   // T_max, T_max - 1, ..., 0 (longest first)
   const int per = (nb + nt - 1) / nt;
@@ -124,8 +136,20 @@ __global__ __launch_bounds__(1024) void bucket_scan_kernel(int T_max, int groups
     const int tot = base[L];
     base[L] = run;
     run += tot;
+    if (choice.word && tot > 0) atomicAdd(&steps, L * tot);
   }
   __syncthreads();
+  if (choice.word) {
+    // workgroups of 128 candidates, one per compute unit: the second round's start in
+    // order where the first round's end, shortest first
+    const int second = (B + 127) / 128 - 256;
+    if (tid < max(second, 1))
+      atomicMax(&chain, second > 0 ? length_at(base, T_max, 128 * (255 - tid)) + length_at(base, T_max, 128 * (256 + tid))
+                                   : 0);
+    if (tid == 0) atomicMax(&chain, length_at(base, T_max, 0));
+    __syncthreads();
+    if (tid == 0) *choice.word = (float)steps <= choice.per_step * ((float)chain - choice.fixed) ? 1 : 0;
+  }
   // per-chunk cursors: chunks in order within each length
   for (int L = tid; L < nb; L += nt) {
     int c = base[L];
@@ -541,6 +565,7 @@ constexpr bool persistent_phi_ok() {
 
 template <class PR, int D, int E, int WAVES, bool NORM>
 __global__ __launch_bounds__(64 * WAVES, 1) void rollout_kernel(const RollArgs a) {
+  if (a.choice && *a.choice != a.want) return;
   using R = Roll<PR, D, E>;
   using Frag = typename PR::Frag;
   constexpr int KF = PR::KF, SL = PR::SL;
@@ -1792,6 +1817,7 @@ constexpr int NARROW_REG = NC <= 16 ? (NORM ? 16 : 22) : 18;
 constexpr int NARROW_SCORE_HW = 2;      // hardware vectors per fused launch
 template <class NP, int D, int E, int NC, int W, bool NORM, bool TRAIN = false, bool SCORE = false>
 __global__ __launch_bounds__(64 * W, 1) void rollout_narrow_kernel(const RollArgs a) {
+  if (a.choice && *a.choice != a.want) return;
   static_assert(!(TRAIN && SCORE), "scores belong to the evaluator");
   using NG = NarrowGeom<NP, D, E, NC, W>;
   using XF = typename NP::XF;
@@ -4232,6 +4258,7 @@ struct ScoreArgs {
   float* scores;      // [n_hw][B]
   float bc2;
   int B, C, HW, j0, nj, chunk_bytes;
+  const int32_t* unless;   // not null: the narrow tiles scored the batch where this is set
 };
 
 template <class PR, int D, int E>
@@ -4277,6 +4304,7 @@ struct ScoreStep {
 
 template <class PR, int D, int E, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 1) void score_kernel(const ScoreArgs a) {
+  if (a.unless && *a.unless) return;
   using SS = ScoreStep<PR, D, E>;
   using Frag = typename PR::Frag;
   constexpr int KF = PR::KF, SL = PR::SL;
@@ -4902,7 +4930,7 @@ hipError_t launch_clear_words(int32_t* p, int n, hipStream_t st) {
 }
 
 hipError_t launch_bucket(const int32_t* lens, int32_t B, int32_t T_max, const SegTable& seg,
-                         int2* perm, int32_t* hist, int32_t* err, hipStream_t st) {
+                         int2* perm, int32_t* hist, int32_t* err, hipStream_t st, const TileChoice& choice) {
   const int groups = bucket_groups(B);
   if (groups == 0) {
     const int lds = 2 * (T_max + 1) * (int)sizeof(int);
@@ -4914,7 +4942,7 @@ hipError_t launch_bucket(const int32_t* lens, int32_t B, int32_t T_max, const Se
   hipLaunchKernelGGL(bucket_count_kernel, dim3(groups), dim3(1024), lds, st, lens, B, T_max, chunk,
                      hist, err);
   hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(1024), lds + 16 * (int)sizeof(int), st, T_max,
-                     groups, hist);
+                     groups, hist, B, choice);
   hipLaunchKernelGGL(bucket_scatter_kernel, dim3(groups), dim3(1024), lds, st, lens, B, T_max, chunk,
                      seg, hist, perm);
   return hipGetLastError();
@@ -4973,28 +5001,41 @@ hipError_t launch_rollout_de(const DevModel& m, const RollArgs& a, int tiles, in
 // wavefronts; bf16 with hidden widths 512 and 1024, fp32 with 512) and d = 64,
 // e = 32 (2 wavefronts, hidden width 128), both transition forms.  A compute
 // unit takes the tiles one after another, longest first, so their time grows
-// with the batch (the steps of all candidates), while a 32-candidate tile per
-// SIMD takes as long as its longest sequence from one tile to 1024 of them (B =
-// 32,768), then twice that.  Lengths uniform in 1..48, narrow / other, us:
-//   bf16 H = 512          B = 12,000 346 / 1237, 32,768 893 / 1200, 49,152 1280 / 1257
-//        paper form       24,000 991 / 1272, 32,768 1307 / 1285
-//   bf16 H = 1024         32,768 1919 / 2099, 49,152 2762 / 2233
-//        paper form       24,000 1737 / 2114, 32,768 2295 / 2167
-//   fp32 H = 512          12,000 1647 / 7714, 65,536 7427 / 8207 (paper form 8433 / 9192)
-//   d = 64 bf16           12,000 110 / 250, 65,536 274 / 312 (paper form 335 / 341)
-//   d = 64 fp32           12,000 278 / 839, 65,536 716 / 1077
-// (score included).  The training kernels store every step's activations and
-// meet earlier (T = 32, forward, loss, backward and gradients): bf16 residual
-// H = 512 12,000 1703 / 1820, 16,384 2248 / 2239, H = 1024 2872 / 2900, 3692 / 3560;
-// paper form 16,384 2663 / 2641, H = 1024 4243 / 4359; fp32 16,384 5244 / 5553.
-int narrow_max_candidates(const DevModel& m, bool train) {
-  constexpr int NO_LIMIT = 0x7FFFFFFF;
-  if (m.prec == WM_FP32) return NO_LIMIT;
+// with the steps of all candidates.  The other kernels take 32 candidates per
+// wavefront, and 1, 2 or 4 wavefronts per workgroup from 1, 512 and 1024 such tiles
+// (B = 32,737) on: one workgroup per compute unit, so a batch costs its longest
+// sequence for the first round of 256 workgroups and the longest of the rest for the
+// next.  Whole evaluations of up to 48 steps, narrow / other (the other as it was when
+// it still took every batch past 8192), us, lengths uniform in 1..48 then all 48:
+//   bf16 H = 512     B = 12,288 305 / 1316, 524 / 2559; 24,576 555 / 1205, 1020 / 2331;
+//                    32,736 738 / 1213, 1354 / 2354; 32,768 738 / 1213, 1357 / 1250;
+//                    40,000 900 / 1250, 1665 / 2496; 45,056 1000 / 1260, 1860 / 2441
+//        paper form  24,576 897 / 1345, 1666 / 2579; 28,672 1057 / 1347, 1940 / 2595
+//   bf16 H = 1024    24,576 1251 / 2116, 2405 / 4193; 32,736 1649 / 2260, 3132 / 4170;
+//                    32,768 1646 / 2139, 3140 / 2194; 34,816 1752 / 2163, 3539 / 4598
+//        paper form  24,576 1528 / 2256, 2909 / 4465; 28,672 1802 / 2263, 3395 / 4443
+//   fp32 H = 512     12,288 1548 / 7792, 2657 / 15,269; 32,768 3717 / 7598, 7065 / 7468;
+//                    131,072 14,712 / 15,982, 28,141 / 30,038 (paper form alike)
+//   d = 64 bf16      32,768 138 / 324, 264 / 341; 65,536 244 / 394, 455 / 496 (paper form 296 /
+//                    428, 538 / 528)
+//   d = 64 fp32      32,768 405 / 833, 760 / 862; 131,072 1238 / 1739, 2439 / 2928
+// So up to 32,736 candidates narrow tiles win whatever the lengths are (d = 64, paper
+// form, past 64,000 and all of one length: 2% behind).  From 32,737,
+// where all candidates are one round of the other kernel or little more, the lengths
+// decide, which only the device knows (tile_choice).
+// The training kernels store every step's activations and meet earlier (T = 32,
+// forward, loss, backward and gradients; uniform, then all 32): bf16 residual H =
+// 512 12,288 1527 / 1954, 2781 / 3521, H = 1024 2577 / 3093, 5188 / 5876; paper form 16,000
+// 2417 / 2840, 4483 / 4976, H = 1024 3861 / 4528, 7852 / 8312; fp32 16,000 5195 / 5634, 9981 /
+// 10,239, 32,768 10,582 / 11,027, 20,069 / 20,446.
+bool narrow_batch(const DevModel& m, int B, bool train) {
+  if (B <= 0 || !m.trans_n) return false;
+  if (m.prec == WM_FP32) return true;
   const bool l2 = m.dims.norm == WM_NORM_L2;
-  if (train) return l2 ? 16000 : 12288;
-  if (m.dims.d == 64) return 65536;
-  if (m.dims.trans_hidden <= 512) return l2 ? 30720 : 45056;
-  return l2 ? 28672 : 34816;
+  if (train) return B <= (l2 ? 16000 : 12288);
+  if (m.dims.d == 64) return B <= 65536;
+  if (l2) return B <= (m.dims.trans_hidden <= 512 ? 30720 : 28672);
+  return B <= (m.dims.trans_hidden <= 512 ? TILE_CHOICE_MAX : 34816);
 }
 template <class NP, int NC, bool NORM, bool TRAIN = false, bool SCORE = false, int D = 256, int E = 64,
           int W = 8>
@@ -5015,10 +5056,32 @@ hipError_t launch_rollout_narrow(const DevModel& m, RollArgs a, int tiles, hipSt
   return hipGetLastError();
 }
 
+// The bf16 residual batches at d = 256 from 32,737 candidates on.  Whole evaluations, us:
+// narrow tiles 95 + 3.29 per 4096 steps of all candidates (H = 512), 88 + 7.95 (H = 1024);
+// the other kernel 57 + 23.0, -88 + 44.8 per step that its longest chain of sequences
+// walks.  Equal at steps = per_step (chain - fixed).  Chosen by that (6 to 9 us for the
+// launches that return at once) / narrow tiles by the batch size alone / the other kernel, as
+// above, for lengths uniform in 1..48, all 48, and 32,768 of 48 with the rest of 1:
+//   H = 512, 32,768 749 / 742 / 1222, 1159 / 1360 / 1245; 40,000 907 / 897 / 1254, 1673 / 1670 /
+//            2427, 1197 / 1385 / 1305
+//   H = 1024, 32,768 1653 / 1648 / 2137, 2043 / 3151 / 2181; 34,816 1762 / 1756 / 2168, 3517 /
+//             3499 / 4552, 2095 / 3164 / 2255
+TileChoice tile_choice(const DevModel& m, int32_t B, int32_t T_max, int32_t* hist) {
+  TileChoice c;
+  const int H = m.dims.trans_hidden;
+  if (m.prec != WM_BF16 || m.dims.norm == WM_NORM_L2 || m.dims.d != 256 || m.dims.embed_dim != 64 ||
+      (H != 512 && H != 1024) || B <= 32736 || !narrow_batch(m, B, false))
+    return c;
+  c.word = hist + bucket_words(B, T_max) - 1;
+  c.per_step = H == 512 ? 28600.0f : 23080.0f;
+  c.fixed = H == 512 ? 1.7f : 3.9f;
+  return c;
+}
+
 hipError_t launch_rollout(const DevModel& m, const float* z0, const int2* perm,
                           const int32_t* types, const int32_t* params, const int32_t* lens,
                           int32_t B, int32_t T_max, float* zT, float* phi, bool* phi_done,
-                          int32_t* err, hipStream_t st, ScoreFuse* sf) {
+                          int32_t* err, hipStream_t st, const TileChoice& choice, ScoreFuse* sf) {
   RollArgs a{};
   a.w1 = m.trans_w1; a.w2 = m.trans_w2; a.wh = m.trans_wh; a.tab = m.roll_tab; a.z0 = z0; a.perm = perm; a.types = types;
   a.params = params; a.lens = lens; a.zT = zT; a.phi = phi; a.err = err; a.B = B; a.T_max = T_max;
@@ -5034,7 +5097,9 @@ hipError_t launch_rollout(const DevModel& m, const float* z0, const int2* perm,
   const bool norm = m.dims.norm == WM_NORM_L2;
   *phi_done = false;
   const int ntiles = (B + 15) / 16;
-  const bool narrow_ok = m.trans_n && B > 0 && B <= narrow_max_candidates(m, false);
+  const bool narrow_ok = narrow_batch(m, B, false);
+  a.choice = choice.word;
+  a.want = 1;
   // Scores fused into the narrow kernel: phi sums present, the narrow cost blob,
   // at most two hardware vectors of at most 32 features.  At d = 64 the launch
   // that it saves is what counts (sequences of up to 16 steps, separate / fused,
@@ -5052,7 +5117,8 @@ hipError_t launch_rollout(const DevModel& m, const float* z0, const int2* perm,
     if (fuse) {
       a.costn = m.cost_n; a.hw = sf->hw; a.scores = sf->scores; a.bc2 = m.bc2;
       a.n_hw = sf->n_hw; a.HW = m.dims.hw_dim; a.C = m.dims.cost_hidden;
-      sf->done = true;
+      sf->done = !choice.word;
+      sf->unless = choice.word;
       return launch_rollout_narrow<NPT, NCT, NT, false, true, DT, ET, WT>(m, a, ntiles, st);
     }
     return launch_rollout_narrow<NPT, NCT, NT, false, false, DT, ET, WT>(m, a, ntiles, st);
@@ -5069,9 +5135,17 @@ hipError_t launch_rollout(const DevModel& m, const float* z0, const int2* perm,
     };
     using I16 = std::integral_constant<int, 16>;
     using I32 = std::integral_constant<int, 32>;
-    if (prec == WM_BF16 && NC == 16) return go(NarrowBF16{}, I16{});
-    if (prec == WM_BF16 && NC == 32) return go(NarrowBF16{}, I32{});
-    if (prec == WM_FP32 && NC == 16) return go(NarrowF32{}, I16{});
+    if (choice.word) {         // both kernels: the lengths decide
+      const hipError_t err2 = NC == 16 ? go(NarrowBF16{}, I16{}) : go(NarrowBF16{}, I32{});
+      if (err2 != hipSuccess) return err2;
+      a.want = 0;
+    } else if (prec == WM_BF16 && NC == 16) {
+      return go(NarrowBF16{}, I16{});
+    } else if (prec == WM_BF16 && NC == 32) {
+      return go(NarrowBF16{}, I32{});
+    } else if (prec == WM_FP32 && NC == 16) {
+      return go(NarrowF32{}, I16{});
+    }
   }
   if (d == 64 && e == 32 && narrow_ok && m.dims.trans_hidden == 128) {
     auto go = [&](auto np) {
@@ -5174,7 +5248,7 @@ hipError_t launch_score_trees(const DevForest& f, const float* zT, int32_t d, co
 }
 
 hipError_t launch_score(const DevModel& m, const float* zT, const float* phi, int32_t B,
-                        const float* hw, int32_t n_hw, float* scores, hipStream_t st) {
+                        const float* hw, int32_t n_hw, float* scores, hipStream_t st, const int32_t* unless) {
   const int tiles = (B + 31) / 32;
   const int waves = pick_waves(tiles);
   const int blocks = (tiles + waves - 1) / waves;
@@ -5185,6 +5259,7 @@ hipError_t launch_score(const DevModel& m, const float* zT, const float* phi, in
     a.B = B; a.C = m.dims.cost_hidden; a.HW = m.dims.hw_dim; a.j0 = j0;
     a.nj = (n_hw - j0) < SCORE_HW_PER_LAUNCH ? (n_hw - j0) : SCORE_HW_PER_LAUNCH;
     a.chunk_bytes = m.cost_chunk_bytes;
+    a.unless = unless;
     hipError_t err = hipErrorInvalidValue;
 #define WM_SCORE(PR, D, E)                                                       \
   {                                                                              \
@@ -5349,7 +5424,7 @@ hipError_t launch_train_fwd(const DevModel& m, const TrainIO& io, hipStream_t st
   const int tiles = (io.B + 31) / 32;
   const bool norm = m.dims.norm == WM_NORM_L2;
   const int ntiles = (io.B + 15) / 16;
-  const bool narrow_ok = m.trans_n && m.trans_nt && io.B <= narrow_max_candidates(m, true);
+  const bool narrow_ok = m.trans_nt && narrow_batch(m, io.B, true);
   if (m.dims.d == 256 && m.dims.embed_dim == 64 && narrow_ok) {
     const int NC = m.dims.trans_hidden / 32;
     const RollArgs r = train_roll_args(m, io, norm);
@@ -5418,7 +5493,7 @@ hipError_t launch_train_bwd(const DevModel& m, const TrainIO& io, hipStream_t st
   const int tiles = (io.B + 31) / 32;
   const bool norm = m.dims.norm == WM_NORM_L2;
   const int ntiles = (io.B + 15) / 16;
-  const bool narrow_ok = m.trans_n && m.trans_nt && io.B <= narrow_max_candidates(m, true);
+  const bool narrow_ok = m.trans_nt && narrow_batch(m, io.B, true);
   if (m.dims.d == 256 && m.dims.embed_dim == 64 && narrow_ok) {
     const int NC = m.dims.trans_hidden / 32;
     if (norm) {

@@ -241,6 +241,14 @@ inline int bucket_groups(int B) {
   return B <= BUCKET_SINGLE_MAX ? 0 : (B + bucket_chunk(B) - 1) / bucket_chunk(B);
 }
 
+// Largest batch whose rollout kernel can be chosen on the device (by the lengths); the
+// choice is the word after the histograms.
+constexpr int TILE_CHOICE_MAX = 45056;
+inline size_t bucket_words(int B, int T_max) {
+  const size_t n = (size_t)bucket_groups(B) * (size_t)(T_max + 1);
+  return n > 0 && B <= TILE_CHOICE_MAX ? n + 1 : n;
+}
+
 // Device error bits (workspace error word).
 enum : int { ERRBIT_LEN = 1, ERRBIT_TYPE = 2, ERRBIT_PARAM = 4, ERRBIT_TOKEN = 8 };
 

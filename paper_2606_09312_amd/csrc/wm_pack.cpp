@@ -298,7 +298,7 @@ WsLayout ws_layout(const DevModel& m, int B, int T_max, int S, int n_hw) {
   size_t o = 0;
   L.err = o; o += 256;
   L.perm = o; o = align256(o + (size_t)B * 2 * sizeof(int32_t));   // (candidate, subgraph) pairs
-  L.hist = o; o = align256(o + (size_t)bucket_groups(B) * (size_t)(T_max + 1) * 4);
+  L.hist = o; o = align256(o + bucket_words(B, T_max) * 4);
   L.z0 = o; o = align256(o + (size_t)S * m.dims.d * 4);
   L.zT = o; o = align256(o + (size_t)B * m.dims.d * 4);
   L.phi = o; o = align256(o + (size_t)B * m.dims.embed_dim * 4);

@@ -189,3 +189,43 @@ def test_batches_between_one_round_and_one_tile_per_simd(wm, prec, norm, H, B):
     assert rel.max() <= tol_z and srel.max() <= tol_s, (rel.max(), srel.max())
     assert rel.mean() <= SHORT_MEAN and srel.mean() <= SHORT_MEAN, (rel.mean(), srel.mean())
     check_topk_self_consistent(g["idx"], g["val"], g["scores"], I["seg_off"], base.k)
+
+
+@pytest.mark.parametrize("H,B", [(512, 32737), (512, 32768), (512, 40000 + 3), (512, 45056), (1024, 32737),
+                                 (1024, 34816)])
+@pytest.mark.parametrize("law", ["few", "all"])
+def test_lengths_choose_the_rollout_kernel(wm, H, B, law):
+    """Residual bf16 batches past one round of 32-candidate tiles: few steps in all
+    take narrow tiles, equal lengths the other kernel.  Whole evaluations against the oracle,
+    and the kernel that ran from the bits: candidates are independent, so those of narrow
+    tiles have the bits that they have in a batch of 300, and the other kernel's
+    order of sums leaves other bits."""
+    import dataclasses
+    base = dataclasses.replace(synth.workload("ansor_round"), H=H)
+    w = synth.scaled(base, B=B, T_max=6, len_lo=0, len_hi=6)
+    W = synth.make_weights(w, 1000)
+    model = wm.Model(wm.model_dims(w), W, precision="bf16")
+    I = synth.make_inputs(w, 4500 + H, pad="garbage")
+    rng = np.random.default_rng(B)
+    I2 = synth.make_inputs(synth.scaled(w, B=B, len_lo=6, len_hi=6), 4500 + H)
+    I = dict(I2, lens=np.full(B, 2, np.int32)) if law == "all" else dict(I2, lens=np.zeros(B, np.int32))
+    pick = np.sort(rng.choice(B, 300, replace=False))
+    if law == "few":
+        I["lens"][rng.choice(B, 4000, replace=False)] = 6
+        I["lens"][pick] = 6
+    print(f"[choice] H={H} B={B} {law}", flush=True)
+    g = run_evaluate(model, w, I, base.k)
+    assert g["status"] == 0
+    part = {k: (v[pick] if k in ("types", "params", "lens") else v) for k, v in I.items()}
+    part["seg_off"] = np.array([0, 300], np.int32)
+    p = run_evaluate(model, synth.scaled(w, B=300), part, base.k)
+    same = np.mean(np.all(p["zT"] == g["zT"][pick], axis=1))
+    print(f"  {same:.3f} of the picked candidates have the bits of narrow tiles", flush=True)
+    assert same == 1.0 if law == "few" else same < 0.5
+    ref = oracle_full(W, I, "bf16", base.k)
+    tol_z, tol_s = bounds("bf16", (0.0, 0.0))
+    rel = latent_rel(g["zT"], ref["zT"])
+    srel = score_rel(g["scores"], ref["scores"], I["seg_off"])
+    assert rel.max() <= tol_z and srel.max() <= tol_s, (rel.max(), srel.max())
+    assert rel.mean() <= SHORT_MEAN and srel.mean() <= SHORT_MEAN, (rel.mean(), srel.mean())
+    check_topk_self_consistent(g["idx"], g["val"], g["scores"], I["seg_off"], base.k)

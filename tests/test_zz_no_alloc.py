@@ -25,7 +25,8 @@ def wm():
 
 
 @pytest.mark.parametrize("name,prec,sizes", [
-    ("ansor_round", "bf16", [(12000, 1), (3000, 1)]),      # persistent kernel, then narrow tiles
+    ("ansor_round", "bf16", [(12000, 1), (3000, 1)]),      # narrow tiles, both ways of bucketing
+    ("ansor_round", "bf16", [(46000, 1), (33000, 1)]),     # persistent kernel, then chosen by the lengths
     ("multi_subgraph", "bf16", [(32 * 200, 32), (8 * 100, 8)]),   # encoder into the scratch
 ])
 def test_noalloc_matches_evaluate(wm, name, prec, sizes):
