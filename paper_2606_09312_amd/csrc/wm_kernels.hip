@@ -2579,12 +2579,17 @@ constexpr int TREEW_CPB = 64, TREEW_WAVES = 16, TREEW_TREES = 4;
 constexpr int TREEW_COLUMNS = 640;                     // 64 floats each: 160 KiB of LDS
 constexpr int TREEW_MIN_BATCH = 8192;
 
+// blockIdx.y: vectors 2 y and 2 y + 1 of n_hw (the last two where that would pass the end:
+// one of them is then formed twice, by two workgroups that write the same value).
 template <int NHW>
 __global__ __launch_bounds__(64 * TREEW_WAVES) void score_trees_wide_kernel(
     const int2* __restrict__ nodes, const float* __restrict__ leaves, int NT, int depth, float base,
     const float* __restrict__ zT, int d, const float* __restrict__ phi_s, int phi_dim,
-    const float* __restrict__ hw, int hw_dim, int B, float* __restrict__ scores) {
+    const float* __restrict__ hw, int hw_dim, int n_hw, int B, float* __restrict__ scores) {
   extern __shared__ __attribute__((aligned(16))) float tsm[];
+  const int j0 = min(NHW * (int)blockIdx.y, n_hw - NHW);
+  hw += (size_t)j0 * hw_dim;
+  scores += (size_t)j0 * B;
   const int Fx = d + phi_dim;                          // features that differ by candidate
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -5209,30 +5214,37 @@ hipError_t launch_score_trees(const DevForest& f, const float* zT, int32_t d, co
                               int32_t hw_dim, float* scores, hipStream_t st) {
   if (B == 0) return hipSuccess;
   // Lanes over candidates where 64 candidates' features fit the LDS and the
-  // batch fills half of the compute units with such workgroups; a smaller batch
-  // is spread wider by 8 candidates per workgroup (d = 256, us for 1 / 2
-  // hardware vectors, 8 per workgroup against 64: B = 4096 19 / 33 against 24 / 41
-  // (before the scalar levels), 8192 33 / 60 against 19 / 33, 65,536 229 / 447
-  // against 86 / 132).
-  if (d + phi_dim + 2 * hw_dim <= TREEW_COLUMNS && B >= TREEW_MIN_BATCH) {
+  // batch fills half of the compute units with such workgroups, three quarters of them
+  // for many trees of few levels (a tree per lane reads few lines there); a smaller batch
+  // is spread wider by 8 candidates per workgroup.  d = 256, us for 1 / 2 hardware
+  // vectors, 8 per workgroup against 64: depth 8, B = 8192 33 / 61 against 19 / 32, 65,536
+  // 235 / 462 against 78 / 130; depth 2 (1000 trees), 8192 19 / 32 against 23 / 40, 12,288 25 / 46
+  // against 23 / 41.
+  const int groups = (B + TREEW_CPB - 1) / TREEW_CPB, all = groups * ((n_hw + 1) / 2);
+  if (d + phi_dim + 2 * hw_dim <= TREEW_COLUMNS && B >= TREEW_MIN_BATCH &&
+      (all >= 192 || f.n_trees <= 256 || f.depth > 2)) {
     const int cols = d + phi_dim + (n_hw > 1 ? 2 : 1) * hw_dim;
     const int rows = cols > 2 * TREEW_WAVES ? cols : 2 * TREEW_WAVES;
-    auto go = [&](auto kern, int j) -> hipError_t {
+    // vectors j .. j + n - 1 in `pairs` rows of workgroups
+    auto go = [&](auto kern, int j, int n, int pairs) -> hipError_t {
       const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, rows * 256);
       if (e != hipSuccess) {
         (void)hipGetLastError();
         return e;
       }
-      hipLaunchKernelGGL(kern, dim3((B + TREEW_CPB - 1) / TREEW_CPB), dim3(64 * TREEW_WAVES), rows * 256, st,
+      hipLaunchKernelGGL(kern, dim3(groups, pairs), dim3(64 * TREEW_WAVES), rows * 256, st,
                          static_cast<const int2*>(f.nodes), f.leaves, f.n_trees, f.depth, f.base, zT, d, phi_s,
-                         phi_dim, hw + (size_t)j * hw_dim, hw_dim, B, scores + (size_t)j * B);
+                         phi_dim, hw + (size_t)j * hw_dim, hw_dim, n, B, scores + (size_t)j * B);
       return hipGetLastError();
     };
-    for (int j = 0; j < n_hw; j += 2) {
-      const hipError_t e = j + 1 < n_hw ? go(score_trees_wide_kernel<2>, j) : go(score_trees_wide_kernel<1>, j);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    if (n_hw == 1) return go(score_trees_wide_kernel<1>, 0, 1, 1);
+    // an odd number: the last vector rides in a pair more while all workgroups run at
+    // once, else it has a launch of its own (256 trees of depth 2, three vectors, us riding /
+    // alone: B = 8192 14.5 / 22.7, 12,288 22.8 / 19.9)
+    const bool ride = n_hw % 2 && groups * (n_hw / 2 + 1) <= 256;
+    const hipError_t e = go(score_trees_wide_kernel<2>, 0, n_hw - (n_hw % 2 && !ride), n_hw / 2 + ride);
+    if (e != hipSuccess || n_hw % 2 == 0 || ride) return e;
+    return go(score_trees_wide_kernel<1>, n_hw - 1, 1, 1);
   }
   const int lds = (TREE_CPB * (d + phi_dim + hw_dim) + (TREE_THREADS / 64) * TREE_CPB) * (int)sizeof(float);
   hipError_t e = hipFuncSetAttribute((const void*)score_trees_kernel,

@@ -94,14 +94,18 @@ def test_score_trees_exact_decisions(wm, n_trees, depth):
     np.testing.assert_allclose(got, want, rtol=0, atol=1e-6 * n_trees)
 
 
-@pytest.mark.parametrize("d,n_hw,n_trees,depth", [(256, 1, 70, 8), (256, 3, 17, 3), (7, 2, 5, 2), (512, 2, 64, 9)])
-def test_score_trees_lanes_over_candidates(wm, d, n_hw, n_trees, depth):
+@pytest.mark.parametrize("d,n_hw,n_trees,depth,B", [
+    (256, 1, 70, 8, 8192 + 37), (256, 3, 17, 3, 8192 + 37), (7, 2, 5, 2, 8192 + 37), (512, 2, 64, 9, 8192 + 37),
+    (64, 5, 33, 2, 8192 + 37), (64, 4, 33, 1, 8192 + 37), (7, 2, 5, 2, 12288), (64, 1, 20, 3, 12288 + 1),
+    (64, 3, 20, 5, 16384 + 1), (64, 2, 20, 3, 8191)])
+def test_score_trees_lanes_over_candidates(wm, d, n_hw, n_trees, depth, B):
     """Batches from 8192 candidates walk a tree with a candidate per lane: a
     partial last workgroup, one, two and an odd number of hardware vectors, tree
     counts off the wavefront count, depths below, at and above the three levels
-    that are chosen from scalars, latent widths off the 16-byte loads."""
+    that are chosen from scalars, latent widths off the 16-byte loads; both sides of
+    the rule for few levels, odd numbers of vectors as a pair more and as a launch more."""
     base = synth.workload("ansor_round")
-    B, K, P, HW = 8192 + 37, base.n_kinds, base.n_params, base.hw_dim
+    K, P, HW = base.n_kinds, base.n_params, base.hw_dim
     rng = np.random.default_rng(depth * 100 + d)
     F = d + TR.phi_dim(K, P) + HW
     n_int = 2 ** depth - 1
