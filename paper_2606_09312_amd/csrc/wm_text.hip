@@ -72,9 +72,11 @@ __device__ __forceinline__ float wave_max(float x) {
 }
 
 // x as three bf16 planes, x = hi + mid + lo to 2^-24 |x| (each remainder is
-// exact in float32): the operand form of the float32 products below.
+// exact in float32): the operand form of the float32 products below.  Past the
+// largest bf16 (3.39e38, below the largest float32) hi stays there: rounding to
+// infinity would leave no remainder.  NaN and infinities give NaN.
 __device__ __forceinline__ void split3(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
-  hi = (__bf16)x;
+  hi = (__bf16)__builtin_amdgcn_fmed3f(x, -0x1.fep127f, 0x1.fep127f);
   const float r = x - (float)hi;
   mid = (__bf16)r;
   lo = (__bf16)(r - (float)mid);
@@ -1099,11 +1101,12 @@ __global__ __launch_bounds__(256, 2) void attention32_kernel(const float* __rest
       }
       bm = fmaxf(bm, __shfl_xor(bm, 32));
       const float nm = fmaxf(mx, bm);
-      const float f = exp2_of(mx - nm);        // 0 at the first block
+      const float at = nm == -INFINITY ? 0.0f : nm;   // only keys of weight 0 so far (scores that overflowed)
+      const float f = exp2_of(mx - at);        // 0 at the first block
       float bs = 0.0f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        s[r] = exp2_of(s[r] - nm);
+        s[r] = exp2_of(s[r] - at);
         bs += s[r];
       }
       sum = fmaf(sum, f, bs);

@@ -141,6 +141,49 @@ def test_float32_product_tiles(wm, S, n, hidden, heads, ffn):
     assert rel.max() <= 5e-6, f"z0 rel err {rel.max():.3e}"
 
 
+def test_float32_overflowing_scores(wm):
+    """Scores that overflow to -inf have weight 0, also where they fill the first
+    key blocks: the first 40 tokens' keys against every query, then 50 ordinary ones."""
+    H, W_ = 64, 96
+    w = synth.TextWorkload(name="inf", S=1, vocab=3, hidden=H, heads=2, ffn=64, layers=1, window=W_, stride=W_, d=32,
+                           len_lo=90, len_hi=90)
+    W = {k: np.array(v) for k, v in synth.make_text_weights(w, 97).items()}
+    # tokens 0 and 1 have no feature 0 after the LayerNorm (mean 0), token 2 has
+    W["pos_emb"][:] = 0
+    W["tok_emb"][:] = np.where(np.arange(H) % 2, -1.0, 1.0)
+    W["tok_emb"][1, 8:] *= 2.0
+    W["tok_emb"][:2, :2] = 0
+    W["tok_emb"][2, :2] = 4.0, -4.0
+    W["ln0_g"][:], W["ln0_b"][:] = 1, 0
+    wqkv = W["wqkv"][0]
+    wqkv[0, :], wqkv[H, :] = 0, 0                 # q[0] = 1e20, k[0] = -1e20 h[0]
+    W["bqkv"][0, 0], W["bqkv"][0, H] = 1e20, 0
+    wqkv[H, 0] = -1e20
+    model = wm.TextModel(w, W, precision="fp32")
+    tokens = np.concatenate([np.full(40, 2), np.tile([0, 1], 25)]).astype(np.int32)
+    off = np.array([0, 90], np.int32)
+    g = run(wm, model, tokens, off)
+    ref = TE.encode(W, [tokens], w.window, w.stride, w.heads, "fp32")
+    assert np.isfinite(ref).all()
+    rel = latent_rel(g, ref)
+    assert rel.max() <= 5e-6, f"z0 rel err {rel.max():.3e}"
+
+
+def test_float32_values_past_the_largest_bf16(wm):
+    """A hidden value between the largest bf16 and the largest float32 that no
+    output takes up (its column of W2 is zero) changes nothing."""
+    w = synth.TextWorkload(name="big", S=1, vocab=50, hidden=64, heads=2, ffn=96, layers=1, window=64, stride=64, d=32,
+                           len_lo=60, len_hi=60)
+    W = {k: np.array(v) for k, v in synth.make_text_weights(w, 99).items()}
+    W["w2"][0, :, 5] = 0
+    tokens = np.random.default_rng(9).integers(0, 50, 60).astype(np.int32)
+    off = np.array([0, 60], np.int32)
+    a = run(wm, wm.TextModel(w, W, precision="fp32"), tokens, off)
+    W["b1"][0, 5] = 3.4e38
+    b = run(wm, wm.TextModel(w, W, precision="fp32"), tokens, off)
+    np.testing.assert_array_equal(a, b)
+
+
 def test_token_out_of_range_is_reported(wm):
     model, W, w = model_for(wm, "tiny_text", "fp32")
     off = np.array([0, 5], dtype=np.int32)
