@@ -34,7 +34,9 @@ struct wm_text_model {
   const float *tok_emb, *pos_emb, *ln0_g, *ln0_b;
   const float *wqkv, *bqkv, *wo, *bo, *ln1_g, *ln1_b, *w1, *b1, *w2, *b2, *ln2_g, *ln2_b;
   const float *wp, *bp;
-  const __bf16 *wqkv16, *wo16, *w116, *w216;   // the layer matrices as bf16 (WM_FP32: three planes)
+  // packed paths: the layer matrices as bf16 (WM_FP32: three planes) in the place of the
+  // float32 ones, which are then null
+  const __bf16 *wqkv16, *wo16, *w116, *w216;
 };
 
 namespace wm {
@@ -1319,51 +1321,48 @@ wm_status wm_text_model_create(const wm_text_dims* dims, const wm_text_weights* 
       {w->w2, L * H * F, true, 0}, {w->b2, L * H, false, 0},
       {w->ln2_g, L * H, false, 0}, {w->ln2_b, L * H, false, 0},
       {w->wp, (size_t)d.d * H, true, 0}, {w->bp, (size_t)d.d, false, 0}};
-  size_t total = 0;
-  for (auto& p : parts) { p.off = total; total = al256(total + p.n * 4); }
-  // bf16 copies of wqkv, wo, w1, w2 (parts 4, 6, 10, 12); float32 on the packed
-  // path: their three planes
+  // Packed paths hold wqkv, wo, w1, w2 (parts 4, 6, 10, 12) as bf16, in float32 as three
+  // planes: 2 or 6 bytes per weight.  They are formed on the device from float32 copies
+  // that are held one at a time.
   const int mats[4] = {4, 6, 10, 12};
-  const bool w16 = bf || packed_path(d);
+  const int mat_n[4] = {3 * d.hidden, d.hidden, d.ffn, d.hidden}, mat_k[4] = {d.hidden, d.hidden, d.hidden, d.ffn};
+  const bool packed = packed_path(d);
   const size_t planes = bf ? 1 : 3;
-  size_t off16[4] = {0, 0, 0, 0};
-  if (w16)
-    for (int i = 0; i < 4; ++i) { off16[i] = total; total = al256(total + parts[mats[i]].n * 2 * planes); }
-  void* dev = nullptr;
-  if (hipMalloc(&dev, total) != hipSuccess) {
+  auto staged = [&](size_t i) { return packed && (i == 4 || i == 6 || i == 10 || i == 12); };
+  size_t total = 0, stage = 0;
+  for (size_t i = 0; i < parts.size(); ++i) {
+    Part& p = parts[i];
+    p.off = total;
+    total = al256(total + p.n * (staged(i) ? 2 * planes : 4));
+    if (staged(i) && p.n * 4 > stage) stage = p.n * 4;
+  }
+  void *dev = nullptr, *tmp_dev = nullptr;
+  if (hipMalloc(&dev, total) != hipSuccess || (stage > 0 && hipMalloc(&tmp_dev, stage) != hipSuccess)) {
     (void)hipGetLastError();
+    (void)hipFree(dev);
     return set_error(WM_ERR_OUT_OF_MEMORY, "hipMalloc of the encoder failed");
   }
   uint8_t* base = static_cast<uint8_t*>(dev);
   std::vector<float> tmp;
-  for (const auto& p : parts) {
+  hipError_t e = hipSuccess;
+  for (size_t i = 0; i < parts.size() && e == hipSuccess; ++i) {
+    const Part& p = parts[i];
     if (p.n == 0) continue;
     tmp.assign(p.src, p.src + p.n);
     if (p.matrix)
       for (auto& v : tmp) v = rnd(v);
-    if (hipMemcpy(base + p.off, tmp.data(), p.n * 4, hipMemcpyHostToDevice) != hipSuccess) {
-      (void)hipFree(dev);
-      return set_error(WM_ERR_DEVICE, "hipMemcpy of the encoder weights failed");
-    }
-  }
-  if (w16) {
-    // the matrices' bf16 values (planes) are formed on the device from the
-    // uploaded float32 ones
-    const int mat_n[4] = {3 * d.hidden, d.hidden, d.ffn, d.hidden}, mat_k[4] = {d.hidden, d.hidden, d.hidden, d.ffn};
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < 4 && e == hipSuccess; ++i) {
-      const Part& p = parts[mats[i]];
-      if (p.n == 0) continue;
-      hipLaunchKernelGGL(split_planes_kernel, dim3(2048), dim3(256), 0, nullptr,
-                         reinterpret_cast<const float*>(base + p.off), p.n, mat_n[i], mat_k[i], (int)planes,
-                         reinterpret_cast<__bf16*>(base + off16[i]));
-      e = hipGetLastError();
-    }
+    e = hipMemcpy(staged(i) ? tmp_dev : base + p.off, tmp.data(), p.n * 4, hipMemcpyHostToDevice);
+    if (!staged(i) || e != hipSuccess) continue;
+    const int q = i == 4 ? 0 : i == 6 ? 1 : i == 10 ? 2 : 3;
+    hipLaunchKernelGGL(split_planes_kernel, dim3(2048), dim3(256), 0, nullptr, static_cast<const float*>(tmp_dev), p.n,
+                       mat_n[q], mat_k[q], (int)planes, reinterpret_cast<__bf16*>(base + p.off));
+    e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-    if (e != hipSuccess) {
-      (void)hipFree(dev);
-      return set_error(WM_ERR_DEVICE, std::string("rounding the encoder weights: ") + hipGetErrorString(e));
-    }
+  }
+  (void)hipFree(tmp_dev);
+  if (e != hipSuccess) {
+    (void)hipFree(dev);
+    return set_error(WM_ERR_DEVICE, std::string("copying the encoder weights: ") + hipGetErrorString(e));
   }
   wm_text_model* m = new (std::nothrow) wm_text_model;
   if (!m) {
@@ -1375,9 +1374,11 @@ wm_status wm_text_model_create(const wm_text_dims* dims, const wm_text_weights* 
   const float** dst[] = {&m->tok_emb, &m->pos_emb, &m->ln0_g, &m->ln0_b, &m->wqkv, &m->bqkv, &m->wo,
                          &m->bo, &m->ln1_g, &m->ln1_b, &m->w1, &m->b1, &m->w2, &m->b2, &m->ln2_g,
                          &m->ln2_b, &m->wp, &m->bp};
-  for (size_t i = 0; i < parts.size(); ++i) *dst[i] = reinterpret_cast<const float*>(base + parts[i].off);
+  for (size_t i = 0; i < parts.size(); ++i)
+    *dst[i] = staged(i) ? nullptr : reinterpret_cast<const float*>(base + parts[i].off);
   const __bf16** dst16[] = {&m->wqkv16, &m->wo16, &m->w116, &m->w216};
-  for (int i = 0; i < 4; ++i) *dst16[i] = w16 ? reinterpret_cast<const __bf16*>(base + off16[i]) : nullptr;
+  for (int i = 0; i < 4; ++i)
+    *dst16[i] = packed ? reinterpret_cast<const __bf16*>(base + parts[mats[i]].off) : nullptr;
   *out = m;
   return clear_error();
 }

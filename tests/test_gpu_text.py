@@ -184,6 +184,26 @@ def test_float32_values_past_the_largest_bf16(wm):
     np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("prec,per", [("fp32", 6), ("bf16", 2)])
+def test_model_memory(wm, prec, per):
+    """A model of the packed paths holds its layer matrices once, as the products
+    read them: 6 bytes per weight (three bf16 planes) in float32, 2 in bf16; everything
+    else is float32.  16 MiB are allowed for the allocator's granularity."""
+    w = synth.TextWorkload(name="mem", S=1, vocab=1000, hidden=768, heads=12, ffn=3072, layers=6, window=512,
+                           stride=256, d=256, len_lo=1, len_hi=1)
+    W = synth.make_text_weights(w, 95)
+    mats = sum(W[k].size for k in ("wqkv", "wo", "w1", "w2"))
+    rest = sum(v.size for v in W.values()) - mats
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    model = wm.TextModel(w, W, precision=prec)
+    used = before - torch.cuda.mem_get_info()[0]
+    model.close()
+    print(f"[text] memory {prec}: {used / 2 ** 20:.0f} MiB for {mats} matrix weights", flush=True)
+    assert used <= per * mats + 4 * rest + (16 << 20)
+
+
 def test_token_out_of_range_is_reported(wm):
     model, W, w = model_for(wm, "tiny_text", "fp32")
     off = np.array([0, 5], dtype=np.int32)
