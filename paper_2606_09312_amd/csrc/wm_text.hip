@@ -125,16 +125,17 @@ __device__ __forceinline__ void chunk_span(const TTable& tt, int c, int window, 
   len = min(window, tt.tok_off[s + 1] - first);
   row = tt.row_off[s] + k * window;
 }
-// Chunk and position of row r.
-__device__ __forceinline__ void row_place(const TTable& tt, int r, int window, int& c, int& p) {
+// Position of row r in its chunk, the chunk's first token and token count.
+__device__ __forceinline__ void row_span(const TTable& tt, int r, int window, int stride, int& p, int& first, int& len) {
   int lo = 0, hi = tt.S - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (tt.row_off[mid] <= r) lo = mid; else hi = mid - 1;
   }
   const int k = min((r - tt.row_off[lo]) / window, tt.chunk_off[lo + 1] - tt.chunk_off[lo] - 1);
-  c = tt.chunk_off[lo] + k;
   p = r - tt.row_off[lo] - k * window;
+  first = tt.tok_off[lo] + k * stride;
+  len = min(window, tt.tok_off[lo + 1] - first);
 }
 
 // ---------------------------------------------------------------------------
@@ -181,11 +182,10 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int32_t* __restrict
                                                        __bf16* __restrict__ hb, size_t plane,
                                                        float2* __restrict__ stats, int32_t* err) {
   const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int r = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: scalar search
   if (r >= rows) return;
-  int c, p, first, len, row;
-  row_place(tt, r, window, c, p);
-  chunk_span(tt, c, window, stride, first, len, row);
+  int p, first, len;
+  row_span(tt, r, window, stride, p, first, len);
   if (p >= len) {                                 // general path only: padding
     for (int f = lane; f < H; f += 64) h[(size_t)r * H + f] = 0.0f;
     return;
