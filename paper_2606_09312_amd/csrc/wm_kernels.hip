@@ -1159,11 +1159,9 @@ __global__ __launch_bounds__(64 * SPLIT, 1) void rollout_split_kernel(const Roll
 }
 
 // ==========================================================================
-// Row-owned rollout (d = 256, 32-candidate tiles): the training forward of
-// the rollout loss above 8192 candidates (narrow tiles take every smaller
-// batch, and every evaluator batch this kernel could take, so its evaluator
-// form, TRAIN = false, is not dispatched).  One workgroup of W wavefronts per
-// tile, two per SIMD in bf16.  Wavefront w computes the first
+// Row-owned training forward of the rollout loss (bf16, d = 256, 32-candidate
+// tiles): batches past the narrow tiles' limit (narrow_batch).  One workgroup of W
+// wavefronts per tile, two per SIMD.  Wavefront w computes the first
 // product and GELU of the hidden chunks w, w + W, ... and writes the GELU
 // outputs as operand fragments to LDS; after one barrier it forms the update
 // of its own NB/W latent blocks over all NC chunks, reading every chunk's GELU
@@ -1188,13 +1186,13 @@ struct RowsGeom {
   // groups in flight: the ring wraps into the next step, so item j must sit
   // in slot j % RD in every step, which needs RD to divide NI
   static constexpr int ring_depth() {
-    const int cap = G == 1 ? 12 : 8;
-    for (int r = cap; r > 1; --r)
+    for (int r = 12; r > 1; --r)
       if (NI % r == 0) return r;
     return 1;
   }
   static constexpr int RD = ring_depth();
   static_assert(NB % W == 0 && NC % W == 0, "even split");
+  static_assert(G == 1, "float32 batches run in narrow tiles");
   // LDS: [table][GELU fragments: NC * GB KiB][X fragments: NZ / G KiB]
   //      [embedding fragments: NE / G KiB][dots]
   static constexpr int GELU_BYTES = NC * GB * 1024;
@@ -1203,8 +1201,8 @@ struct RowsGeom {
   static constexpr int XE_BYTES = NEG * 1024;
 };
 
-template <class PR, int D, int E, int NC, int W, bool NORM, bool TRAIN = false>
-__global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs a) {
+template <class PR, int D, int E, int NC, int W, bool NORM>
+__global__ __launch_bounds__(64 * W, 1) void train_fwd_rows_kernel(const RollArgs a) {
   using R = Roll<PR, D, E>;
   using RG = RowsGeom<PR, D, E, NC, W>;
   using Frag = typename PR::Frag;
@@ -1226,18 +1224,12 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
   uint8_t* xbuf = gbuf + RG::GELU_BYTES;                            // X fragments
   uint8_t* xebuf = xbuf + RG::X_BYTES;                              // embedding fragments
   float* dots = reinterpret_cast<float*>(xebuf + RG::XE_BYTES);     // [W][3][32]
-  // action features: the running sum of each owned embedding fragment, per
-  // candidate row (rows padded by one float against bank conflicts)
-  float* phib = dots + (NORM ? W * 3 * 32 : 0);                      // [32][E + 1]
-  const bool do_phi = !TRAIN && a.phi != nullptr;
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int n = lane & 31, h = lane >> 5;
 
   stage_to_lds(reinterpret_cast<const uint8_t*>(a.tab), reinterpret_cast<uint8_t*>(tab),
                a.tab_bytes, tid, NT);
-  if (do_phi)
-    for (int i = tid; i < 32 * (E + 1); i += NT) phib[i] = 0.0f;
 
   const int pos = blockIdx.x * 32 + n;
   const bool valid = pos < a.B;
@@ -1247,7 +1239,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
   const int T_wg = __builtin_amdgcn_readfirstlane(
       clampi(a.lens[a.perm[blockIdx.x * 32].x], 0, a.T_max));
   constexpr int IN = D + E;
-  const size_t row0 = (TRAIN && valid) ? (size_t)a.off[cand] : 0;
+  const size_t row0 = valid ? (size_t)a.off[cand] : 0;
 
   // owned latent blocks (fp32) and the full X operand
   const float* zs = a.z0 + (size_t)pc.y * D;
@@ -1318,14 +1310,8 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
 #pragma unroll
     for (int j = 0; j < SL; ++j) ev[j] = (ev[j] + tmp[j]) * af;
   };
-  // running sum of fragment q's features (inactive steps add zero)
-  auto phi_add = [&](int q, const float (&ev)[SL]) {
-    float* ph = phib + n * (E + 1) + KF * q + SL * h;
-#pragma unroll
-    for (int j = 0; j < SL; ++j) ph[j] += ev[j];
-  };
   // all fragments in this wavefront (paper form: the normal map needs them
-  // before the step's exchange); the owner of each fragment group sums it
+  // before the step's exchange); the owner of each fragment group stores it
   auto embed_step = [&](int s, Frag (&xe)[NE]) {
     int ty;
     float u[PMAX], af;
@@ -1335,13 +1321,10 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
       float ev[SL];
       embed_vals(ty, u, af, q, ev);
       xe[q] = PR::cvt(ev);
-      if (do_phi && (q / G) % W == w) phi_add(q, ev);
-      if constexpr (TRAIN) {
-        if ((q / G) % W == w && s < len) {
-          const size_t xo = (row0 + s) * IN + D + KF * q + SL * h;
+      if ((q / G) % W == w && s < len) {
+        const size_t xo = (row0 + s) * IN + D + KF * q + SL * h;
 #pragma unroll
-          for (int j = 0; j < SL; ++j) store_op<PR::G == 1>(a.X, xo + j, ev[j]);
-        }
+        for (int j = 0; j < SL; ++j) store_op<PR::G == 1>(a.X, xo + j, ev[j]);
       }
     }
   };
@@ -1359,13 +1342,10 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
         float ev[SL];
         embed_vals(ty, u, af, q, ev);
         *reinterpret_cast<Frag*>(xebuf + frag_offset<PR>(q, lane, 0)) = PR::cvt(ev);
-        if (do_phi) phi_add(q, ev);
-        if constexpr (TRAIN) {
-          if (s < len) {
-            const size_t xo = (row0 + s) * IN + D + KF * q + SL * h;
+        if (s < len) {
+          const size_t xo = (row0 + s) * IN + D + KF * q + SL * h;
 #pragma unroll
-            for (int j = 0; j < SL; ++j) store_op<PR::G == 1>(a.X, xo + j, ev[j]);
-          }
+          for (int j = 0; j < SL; ++j) store_op<PR::G == 1>(a.X, xo + j, ev[j]);
         }
       }
     }
@@ -1377,7 +1357,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
 #pragma unroll
     for (int i = 0; i < NBW * GPB; ++i) whq[i] = HY::group(a.wh, w * NBW * GPB + i, lane);
   }
-  // Training mode: the unit-length prediction of the finished step t and
+  // The unit-length prediction of the finished step t and
   // |u| go to row t, the next step's v, v.z and v.v to row t + 1.
   auto boundary = [&](const Frag (&xe)[NE], bool renorm, bool project, int t) {
     f32x16 vq[NBW];
@@ -1415,27 +1395,25 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
     }
     const float sc = (renorm && zz > 0.0f) ? rsqrtf(zz) : 1.0f;
     const float al = (project && vv > 0.0f) ? vz / vv : 0.0f;
-    if constexpr (TRAIN) {
-      if (renorm) {              // step t was active
-        const size_t rt = row0 + t;
+    if (renorm) {              // step t was active
+      const size_t rt = row0 + t;
 #pragma unroll
-        for (int bq = 0; bq < NBW; ++bq) {
-          f32x16 pv;
+      for (int bq = 0; bq < NBW; ++bq) {
+        f32x16 pv;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) pv[r] = zq[bq][r] * sc;
-          store_acc(a.Pz + rt * D + 32 * (w * NBW + bq), pv, h);
-        }
-        if (w == 0 && h == 0) a.SC[rt * 4 + 2] = sqrtf(zz);
+        for (int r = 0; r < 16; ++r) pv[r] = zq[bq][r] * sc;
+        store_acc(a.Pz + rt * D + 32 * (w * NBW + bq), pv, h);
       }
-      if (project) {             // step t + 1 is active
-        const size_t rs = row0 + (t + 1);
+      if (w == 0 && h == 0) a.SC[rt * 4 + 2] = sqrtf(zz);
+    }
+    if (project) {             // step t + 1 is active
+      const size_t rs = row0 + (t + 1);
 #pragma unroll
-        for (int bq = 0; bq < NBW; ++bq) store_acc(a.V + rs * D + 32 * (w * NBW + bq), vq[bq], h);
-        if (w == 0 && h == 0) {
-          a.SC[rs * 4 + 0] = vz * sc;
-          a.SC[rs * 4 + 1] = vv;
-          a.SC[rs * 4 + 3] = 0.0f;
-        }
+      for (int bq = 0; bq < NBW; ++bq) store_acc(a.V + rs * D + 32 * (w * NBW + bq), vq[bq], h);
+      if (w == 0 && h == 0) {
+        a.SC[rs * 4 + 0] = vz * sc;
+        a.SC[rs * 4 + 1] = vv;
+        a.SC[rs * 4 + 3] = 0.0f;
       }
     }
 #pragma unroll
@@ -1503,12 +1481,10 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
     gu8* pB = baseB;
     asm volatile("" : "+v"(pA), "+v"(pB));
     const size_t row = row0 + t;
-    if constexpr (TRAIN) {
-      if (active) {            // X = [z; e]: the owned latent blocks (e: embed_share)
+    if (active) {              // X = [z; e]: the owned latent blocks (e: embed_share)
 #pragma unroll
-        for (int bq = 0; bq < NBW; ++bq) store_op_acc<PR::G == 1>(a.X, row * IN + 32 * (w * NBW + bq), zq[bq], h);
-        if (w == 0 && h == 0) a.row_src[row] = cand * a.T_max + t;
-      }
+      for (int bq = 0; bq < NBW; ++bq) store_op_acc<PR::G == 1>(a.X, row * IN + 32 * (w * NBW + bq), zq[bq], h);
+      if (w == 0 && h == 0) a.row_src[row] = cand * a.T_max + t;
     }
 
     f32x16 acc = {};
@@ -1544,20 +1520,14 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
           for (int r4 = 0; r4 < 4; ++r4)
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[4 * r4 + j] += b1v[r4][j];
-          if constexpr (TRAIN) {
-            f32x16 gv;
+          f32x16 gv;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) gv[r] = op_value<PR>(gelu_as<PR::G == 1>(acc[r]));
+          for (int r = 0; r < 16; ++r) gv[r] = op_value<PR>(gelu_as<PR::G == 1>(acc[r]));
 #pragma unroll
-            for (int q = 0; q < 8; ++q) gp[q] = PR::pack2(gv[2 * q], gv[2 * q + 1], amask);
-            if (active) {
-              store_acc(a.A + row * a.H + 32 * c, acc, h);
-              store_op_acc<PR::G == 1>(a.G, row * a.H + 32 * c, gv, h);
-            }
-          } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-              gp[q] = PR::pack2(gelu_as<PR::G == 1>(acc[2 * q]), gelu_as<PR::G == 1>(acc[2 * q + 1]), amask);
+          for (int q = 0; q < 8; ++q) gp[q] = PR::pack2(gv[2 * q], gv[2 * q + 1], amask);
+          if (active) {
+            store_acc(a.A + row * a.H + 32 * c, acc, h);
+            store_op_acc<PR::G == 1>(a.G, row * a.H + 32 * c, gv, h);
           }
 #pragma unroll
           for (int f = 0; f < NF2; ++f)
@@ -1577,10 +1547,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
 #pragma unroll
         for (int ww = 0; ww < G; ++ww) {
           const int f = gg2 * G + ww;             // GELU fragment of chunk c
-          const u32x4 gf = gcur[(f * SL * PR::ES) / 16];
-          Frag b;
-          if constexpr (G == 1) b = PR::pick(gf, 0);
-          else b = PR::pick(gf, f % G);
+          const Frag b = PR::pick(gcur[(f * SL * PR::ES) / 16], 0);
           dz[bq] = PR::mfma(PR::pick(grp, ww), b, dz[bq]);
         }
         if (k == N2 - 1) {
@@ -1601,7 +1568,7 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
       const int b = w * NBW + bq;
 #pragma unroll
       for (int r = 0; r < 16; ++r) zq[bq][r] += dz[bq][r] + t_b2[(b * 2 + h) * 16 + r] * actf;
-      if constexpr (TRAIN && !NORM) {
+      if constexpr (!NORM) {
         if (active) store_acc(a.Pz + row * D + 32 * b, zq[bq], h);
       }
     }
@@ -1614,28 +1581,6 @@ __global__ __launch_bounds__(64 * W, 1) void rollout_rows_kernel(const RollArgs 
     exchange_x();
   }
   if (errbits) atomicOr(a.err, errbits);
-  if (do_phi && valid) {         // phi = sum / len over the owned fragments (0 when empty)
-    const float inv = len > 0 ? 1.0f / (float)len : 0.0f;
-#pragma unroll
-    for (int q = 0; q < NE; ++q) {
-      if ((q / G) % W != w) continue;
-      const float* ph = phib + n * (E + 1) + KF * q + SL * h;
-#pragma unroll
-      for (int j = 0; j < SL; ++j) a.phi[(size_t)cand * E + KF * q + SL * h + j] = ph[j] * inv;
-    }
-  }
-  if (valid && !TRAIN) {
-    float* zo = a.zT + (size_t)cand * D;
-#pragma unroll
-    for (int bq = 0; bq < NBW; ++bq)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        f32x4 v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = zq[bq][4 * r4 + i];
-        *reinterpret_cast<f32x4*>(zo + 32 * (w * NBW + bq) + acc_row(h, 4 * r4)) = v;
-      }
-  }
 }
 
 // ==========================================================================
@@ -1668,7 +1613,6 @@ constexpr int SCORE_MAX_HW = 32;        // hardware-vector width limit
 struct NarrowBF16 {
   using XF = bf16x8;
   static constexpr int GPK = 1;                 // 1 KiB groups per fragment
-  static __device__ __forceinline__ float op(float v) { return (float)(__bf16)v; }
   static __device__ __forceinline__ XF cvt(const float (&v)[8]) {
     XF f;
 #pragma unroll
@@ -1695,7 +1639,6 @@ struct NarrowBF16 {
 struct NarrowF32 {
   using XF = f32x8n;
   static constexpr int GPK = 2;
-  static __device__ __forceinline__ float op(float v) { return v; }
   static __device__ __forceinline__ XF cvt(const float (&v)[8]) {
     XF f;
 #pragma unroll
@@ -3328,13 +3271,13 @@ struct BwdRowsGeom {
   static constexpr int NA = NCW * NP1;                    // phase-1 items
   static constexpr int NI = NA + NC * NBW * GF;           // items per step
   static constexpr int ring_depth() {
-    const int cap = G == 1 ? 8 : 12;
-    for (int r = cap; r > 1; --r)
+    for (int r = 8; r > 1; --r)
       if (NI % r == 0) return r;
     return 1;
   }
   static constexpr int RD = ring_depth();
   static_assert(NB % W == 0 && NC % W == 0 && NF2 % G == 0, "even split");
+  static_assert(G == 1, "float32 batches run in narrow tiles");
   // LDS: [table-free] [dA fragments: NC * GF KiB][delta fragments: NZ / G KiB]
   //      [dE partials: W * NBE * 4 KiB]
   static constexpr int DA_BYTES = NC * GF * 1024;
@@ -3511,10 +3454,7 @@ __global__ __launch_bounds__(64 * W, 1) void train_bwd_rows_kernel(const TrainAr
 #pragma unroll
         for (int ww = 0; ww < G; ++ww) {
           const int f = fg * G + ww;
-          const u32x4 gf = dcur[(f * SL * PR::ES) / 16];
-          Frag b;
-          if constexpr (G == 1) b = PR::pick(gf, 0);
-          else b = PR::pick(gf, f % G);
+          const Frag b = PR::pick(dcur[(f * SL * PR::ES) / 16], 0);
           dq[bq] = PR::mfma(PR::pick(grp, ww), b, dq[bq]);
         }
         if (bq == NBW - 1 && fg == GF - 1) {
@@ -5420,7 +5360,7 @@ hipError_t launch_train_fwd_rows(const DevModel& m, const TrainIO& io, int tiles
   const RollArgs a = train_roll_args(m, io, NORM);
   using RG = RowsGeom<PR, 256, 64, NC, W>;
   const int lds = m.roll_tab_bytes + RG::GELU_BYTES + RG::X_BYTES + RG::XE_BYTES + (NORM ? W * 3 * 32 * 4 : 0);
-  auto kern = rollout_rows_kernel<PR, 256, 64, NC, W, NORM, true>;
+  auto kern = train_fwd_rows_kernel<PR, 256, 64, NC, W, NORM>;
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) {
     (void)hipGetLastError();
