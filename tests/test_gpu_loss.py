@@ -230,10 +230,8 @@ def test_loss_terms(wm, prec, lam, gamma, mode):
                                          ("ansor_round", "fp32", 9000), ("tiny", "fp32", 9000)])
 def test_loss_short_sequences_rowwise(wm, name, prec, B):
     """At most two steps: every gradient row (and, in fp32, element)
-    against the oracle's.  Up to 8192 candidates the forward and backward
-    run in 16-candidate tiles (5000: two per compute unit); 9000 take the
-    32-candidate row-owned kernels (d = 256) or one wavefront per tile
-    (d = 64).  The per-element rule is for the small batches: an element of
+    against the oracle's, in 16-candidate tiles (one, two and three rounds of
+    them).  The per-element rule is for the small batches: an element of
     a weight gradient over thousands of rows is an fp32 sum of as many terms
     of mixed sign, whose rounding (about sqrt(rows) ulp of the terms)
     exceeds 1e-4 of the element scale where the terms cancel.  For the same
@@ -251,11 +249,14 @@ def test_loss_short_sequences_rowwise(wm, name, prec, B):
 
 
 @pytest.mark.parametrize("name,norm,B", [("ansor_round", "none", 12288 + 21), ("long_schedule", "none", 12288 + 21),
-                                         ("ansor_round", "l2", 16000 + 21)])
+                                         ("ansor_round", "l2", 16000 + 21), ("ansor_round", "none", 12288),
+                                         ("ansor_round", "none", 12289), ("ansor_round", "l2", 16000),
+                                         ("long_schedule", "l2", 16001), ("tiny", "none", 12288),
+                                         ("tiny", "none", 12289), ("tiny", "l2", 16001)])
 def test_loss_past_the_narrow_tiles(wm, name, norm, B):
-    """bf16 batches past the narrow-tile limit (12288 candidates, paper form
-    16000): the 32-candidate row-owned kernels, a partial last tile, sequences of
-    at most two steps, per tensor against the oracle."""
+    """bf16 batches on both sides of the narrow-tile limit (12288 candidates, paper form
+    16000); past it the 32-candidate row-owned kernels (d = 64: a wavefront per tile), a
+    partial last tile, sequences of at most two steps, per tensor against the oracle."""
     w = synth.scaled(synth.workload(name), B=B, lengths="uniform", len_lo=0, len_hi=2, T_max=2)
     print(f"[loss past narrow] {name} {norm} B={B}", flush=True)
     model, W = model_for(wm, name, "bf16", norm)
@@ -278,8 +279,8 @@ def test_loss_negative_counts(wm, n_neg):
 
 
 def test_loss_narrow_limit(wm):
-    """8192 candidates of at most two steps, bf16: the largest batch of
-    narrow tiles (two per compute unit).  Per-candidate losses and the
+    """8192 candidates of at most two steps, bf16: two narrow tiles per
+    compute unit.  Per-candidate losses and the
     per-tensor rule with the bf16 bound from the oracle's own sensitivity;
     the per-row rule is not applied: one row of the z0 gradient measured
     2.07e-2 from the oracle's, and one seeded 1e-7 relative perturbation of
@@ -297,18 +298,22 @@ def test_loss_narrow_limit(wm):
 
 
 @pytest.mark.parametrize("norm", ["none", "l2"])
-def test_loss_other_hidden_width(wm, norm):
-    """A hidden width without narrow-tile kernels (d = 64, H = 256): the
-    one-wavefront-per-tile training kernels, against the oracle."""
-    base = dataclasses.replace(synth.workload("tiny"), H=256)
-    w = synth.scaled(base, B=200, lengths="uniform", len_lo=0, len_hi=3)
-    print(f"[loss other H] tiny H=256 fp32 {norm}", flush=True)
+@pytest.mark.parametrize("name,H,prec,B", [("tiny", 256, "fp32", 200), ("tiny", 256, "bf16", 200),
+                                           ("ansor_round", 320, "bf16", 200), ("ansor_round", 320, "fp32", 130),
+                                           ("tiny", 256, "bf16", 16384 + 21)])
+def test_loss_other_hidden_width(wm, name, H, prec, B, norm):
+    """Hidden widths without narrow-tile kernels: the one-wavefront-per-tile
+    training kernels (one and two wavefronts per workgroup), which store the weight
+    gradients' operands for both precisions, against the oracle."""
+    base = dataclasses.replace(synth.workload(name), H=H)
+    w = synth.scaled(base, B=B, lengths="uniform", len_lo=0, len_hi=3 if B < 1000 else 2)
+    print(f"[loss other H] {name} H={H} {prec} B={B} {norm}", flush=True)
     W = synth.make_weights(w, 1000)
-    model = wm.Model(wm.model_dims(w), W, precision="fp32", norm=norm)
+    model = wm.Model(wm.model_dims(w), W, precision=prec, norm=norm)
     I = synth.make_inputs(w, 7400, pad="garbage")
-    tgt, neg = margin_targets(W, I, "fp32", 3, 85, 0.3, norm=norm)
+    tgt, neg = margin_targets(W, I, prec, 3, 85, 0.3, norm=norm)
     g = run_loss(wm, model, I, tgt, neg, 0.5, 0.3)
-    check_against_oracle(g, W, I, tgt, neg, 0.5, 0.3, "fp32", rows=True, elems=True, norm=norm)
+    check_against_oracle(g, W, I, tgt, neg, 0.5, 0.3, prec, rows=prec == "fp32", elems=prec == "fp32", norm=norm)
 
 
 def test_loss_full_size_ansor(wm):

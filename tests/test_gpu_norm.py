@@ -88,8 +88,8 @@ def test_l2_parity_scaled(wm, name, prec, B, S):
     print(f"  z_T max rel {rel.max():.2e}, score max rel {srel.max():.2e}", flush=True)
 
 
-# More than 256 tiles of the small model: the persistent kernel with 1 and 2
-# wavefronts per workgroup (normal map in LDS), oracle on the whole batch.
+# The small model past 8192 and 16,384 candidates (narrow tiles; the persistent
+# kernel at d = 64 is in test_gpu_full), oracle on the whole batch.
 @pytest.mark.parametrize("prec,B", [("fp32", 8224), ("bf16", 16448)])
 def test_l2_parity_persistent_small_model(wm, prec, B):
     w = synth.scaled(synth.workload("tiny"), B=B)

@@ -88,8 +88,9 @@ def test_parity_full_size_sampled(wm, name, prec):
     check_sampled(wm, name, prec, w, 2000)
 
 
-# The batch sizes where the rollout changes kernels: 8192 candidates are 512
-# narrow tiles (two per compute unit), 8193 the first batch past them.
+# 8192 candidates are the largest batch of the single-workgroup bucketing, 8193 the
+# first in chunks; both roll out in narrow tiles.  The limits where the rollout
+# changes kernels are in test_gpu_full.
 @pytest.mark.parametrize("B", [8192, 8193])
 @pytest.mark.parametrize("name,prec", [("ansor_round", "bf16"), ("ansor_round", "fp32"), ("tiny", "fp32")])
 def test_parity_narrow_limit_sampled(wm, name, prec, B):
@@ -490,27 +491,44 @@ def test_large_batch_bucketing(wm, lens_kind):
 
 # The action features come from the rollout kernel itself (narrow tiles, and
 # the persistent kernel where its LDS has room) or from the phi kernel
-# (split kernel, d = 512, fp32 at d = 256): every family against the oracle.
+# (split kernel, d = 512, the persistent kernel in fp32 at d = 256): every family
+# against the oracle.
 PHI_CASES = [
     ("tiny", "fp32", 200, "none"),            # narrow tiles, d = 64
-    ("tiny", "fp32", 8224, "none"),           # persistent, sums in the kernel
+    ("tiny", "fp32", 8224, "none"),           # narrow tiles, d = 64, chunked bucketing
     ("ansor_round", "bf16", 300, "none"),     # narrow tiles (16 candidates)
     ("ansor_round", "fp32", 300, "none"),     # narrow tiles, fp32
     ("ansor_round", "bf16", 4096, "none"),    # narrow tiles, 256 full tiles
     ("ansor_round", "bf16", 5000, "none"),    # narrow tiles, two per compute unit
     ("long_schedule", "bf16", 300, "none"),   # narrow tiles, hidden width 1024
     ("ansor_round", "bf16", 300, "l2"),       # narrow tiles, paper form
-    ("ansor_round", "bf16", 9000, "none"),    # persistent d = 256
-    ("ansor_round", "bf16", 9000, "l2"),      # persistent d = 256, paper form
-    ("ansor_round", "fp32", 9000, "none"),    # persistent fp32 d = 256 + phi kernel
+    ("ansor_round", "bf16", 9000, "none"),    # narrow tiles, three per compute unit
+    ("ansor_round", "bf16", 9000, "l2"),
+    ("ansor_round", "fp32", 9000, "none"),
     ("large_latent", "bf16", 300, "none"),    # d = 512 + phi kernel
 ]
 
 
 @pytest.mark.parametrize("name,prec,B,norm", PHI_CASES)
 def test_rollout_phi_every_kernel_family(wm, name, prec, B, norm):
-    w = synth.scaled(synth.workload(name), B=B, S=1)
-    print(f"[phi] {name} {prec} B={B} {norm}", flush=True)
+    check_phi(wm, synth.scaled(synth.workload(name), B=B, S=1), prec, norm)
+
+
+@pytest.mark.parametrize("name,H,prec,B,norm", [
+    ("tiny", 256, "fp32", 300, "none"), ("tiny", 256, "bf16", 300, "l2"),
+    ("tiny", 256, "fp32", 8224, "none"), ("tiny", 256, "fp32", 8224, "l2"), ("tiny", 256, "bf16", 8224, "none"),
+    ("tiny", 256, "bf16", 16448, "l2"), ("tiny", 256, "bf16", 33000, "none"), ("ansor_round", 320, "bf16", 9000, "none"),
+    ("ansor_round", 320, "bf16", 16448, "l2"), ("ansor_round", 320, "fp32", 9000, "none")])
+def test_rollout_phi_hidden_widths_without_narrow_tiles(wm, name, H, prec, B, norm):
+    """The split kernel (300 candidates, + phi kernel) and the persistent kernel with
+    1, 2 and 4 wavefronts per workgroup (sums in the kernel, float32 at d = 256 +
+    phi kernel)."""
+    check_phi(wm, dataclasses.replace(synth.scaled(synth.workload(name), B=B, S=1), H=H), prec, norm)
+
+
+def check_phi(wm, w, prec, norm):
+    name, B = w.name, w.B
+    print(f"[phi] {name} H={w.H} {prec} B={B} {norm}", flush=True)
     W = synth.make_weights(w, 1000)
     model = wm.Model(wm.model_dims(w), W, precision=prec, norm=norm)
     I = synth.make_inputs(w, 4100 + B, pad="garbage")
