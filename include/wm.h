@@ -366,7 +366,9 @@ typedef struct wm_text_weights {
 typedef struct wm_text_model wm_text_model;
 
 /* Copy the encoder to the current device (matrices rounded to bfloat16 in
- * WM_BF16).  Synchronous.  Errors: INVALID_ARGUMENT, UNSUPPORTED,
+ * WM_BF16).  The layer matrices take 2 bytes per weight in WM_BF16 and 6 in WM_FP32
+ * (4 in both for head widths other than 32 and 64, and for windows past 512 in
+ * WM_BF16), everything else 4.  Synchronous.  Errors: INVALID_ARGUMENT, UNSUPPORTED,
  * OUT_OF_MEMORY, DEVICE. */
 wm_status wm_text_model_create(const wm_text_dims* dims, const wm_text_weights* weights,
                                wm_text_model** out);
@@ -378,8 +380,9 @@ int32_t wm_text_chunks(const wm_text_model* model, const int32_t* tok_off, int32
 
 /* Workspace bytes of wm_encode_text for a batch of n_chunks chunks (caller
  * allocated, 256-byte aligned, zeroed once; same error-word rules as
- * wm_workspace_bytes).  About 4 (6 hidden + ffn + heads window) bytes per
- * chunk position. */
+ * wm_workspace_bytes).  Bytes per chunk position: with a head width of 32 or 64, 28
+ * hidden + 6 ffn + 8 in WM_FP32, 14 hidden + 2 ffn + 8 in WM_BF16 up to a window of 512;
+ * otherwise 4 (6 hidden + ffn + heads window). */
 size_t wm_text_workspace_bytes(const wm_text_model* model, int32_t n_chunks);
 
 /* z0 [S][d] float32 out, from the concatenated token ids tokens [tok_off[S]]

@@ -10,7 +10,8 @@
 //  score_kernel    cost model y = wc2 GELU(Wc1 [z_T; phi; h] + bc1) + bc2 (Eq. 3)
 //  encode_kernel   initial latents from program features (Sec. 3.3, Eq. 4)
 //  topk_kernel     per (hardware vector, subgraph) top-k by (-y, index)
-//                  (Sec. 3.5): radix select + bitonic sort in LDS
+//                  (Sec. 3.5): candidates above a bound, ordered in LDS, or a
+//                  radix select
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

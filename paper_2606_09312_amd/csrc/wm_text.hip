@@ -868,9 +868,10 @@ __global__ __launch_bounds__(1024) void attention_kernel(const __bf16* __restric
 // are added through LDS at the end, each group finishing half of the rows.  With
 // two workgroups per compute unit that is four wavefronts per SIMD.  A slice's
 // fragments are read while the products of the slice before run.  Copies from
-// L2 bound it (a third of the cycles are products): operands in slices (op_at)
-// took the products of 2400 rows of 768 columns from 3.74 to 3.37 ms over 12
-// layers.  128 x 64 tiles, which read a quarter fewer bytes from LDS but leave two
+// L2 bound it (64,263 rows: matrix cores 44% of the SIMD cycles, 29 bytes per clock
+// and compute unit from L2, the rest of the time waiting): operands in slices (op_at)
+// took the products of 2400 rows of 768 columns from 3.74 to 3.37 ms over 12 layers.
+// 128 x 64 tiles, which read a quarter fewer bytes from LDS but leave two
 // wavefronts per SIMD, are slower (encoder calls, 64 / 128 rows, ms: 300 rows 1.83
 // / 1.91, 1200 2.69 / 2.76, 1600 3.33 / 3.61, 2000 3.79 / 4.12).  A call of 2400 rows, with
 // 4 wavefronts on 64 x 64 tiles of row-major operands, then this kernel: 5.22, 4.65
